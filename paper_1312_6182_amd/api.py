@@ -342,7 +342,9 @@ def quantize(A: torch.Tensor, dtype: torch.dtype, stream: Optional[torch.cuda.St
     M = matrix(A)
     p, n = A.shape
     ldq = (p + 15) // 16 * 16
-    store = torch.zeros((n, ldq), dtype=dtype, device=A.device)
+    store = torch.empty((n, ldq), dtype=dtype, device=A.device)
+    if ldq > p:
+        store.view(torch.uint8).view(n, -1)[:, p * store.element_size():].zero_()
     scale = torch.empty(n, dtype=torch.float32, device=A.device) \
         if dtype == torch.float8_e4m3fn else None
     to = L.BF16 if dtype == torch.bfloat16 else L.F8E4M3

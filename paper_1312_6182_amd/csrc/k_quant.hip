@@ -26,6 +26,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 
 namespace gpspca {
 
@@ -64,28 +65,140 @@ __device__ __forceinline__ uint32_t e4m3_rne(float v) {
     return sign | code;
 }
 
+// Four FP32 values -> four codes of one quad.  e4m3 goes through the gfx950
+// converter after the magnitude is clamped to 448 on the bit pattern, which is
+// e4m3_rne's saturation (NaN included); both round to nearest even.
 template <int TO>
+struct QuadCode { using T = uint2; };
+template <>
+struct QuadCode<kStF8> { using T = uint32_t; };
+
+__device__ __forceinline__ float clamp448(float v) {
+    const uint32_t u = __float_as_uint(v);
+    const uint32_t mag = u & 0x7FFFFFFFu;
+    return __uint_as_float((u & 0x80000000u) | (mag < 0x43E00000u ? mag : 0x43E00000u));
+}
+
+template <int TO>
+__device__ __forceinline__ typename QuadCode<TO>::T quad_code(const f4q& a, float sc) {
+    if constexpr (TO == kStBF16) {
+        return uint2{bf16_rne(a[0]) | (bf16_rne(a[1]) << 16),
+                     bf16_rne(a[2]) | (bf16_rne(a[3]) << 16)};
+    } else {
+        int w = 0;
+        w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[0] / sc), clamp448(a[1] / sc), w, false);
+        w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[2] / sc), clamp448(a[3] / sc), w, true);
+        return (uint32_t)w;
+    }
+}
+
+template <int TO>
+__device__ __forceinline__ uint32_t one_code(float v, float sc) {
+    if constexpr (TO == kStBF16) return bf16_rne(v);
+    else return e4m3_rne(v / sc);
+}
+
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// One read of A: T threads hold a whole column in registers (KQ quads each, so
+// p <= 4 T KQ), reduce its maximum and write the codes.  The work cannot do
+// without 4 + 1 (2) bytes per element; every load of a column is issued before
+// the first is used, 10 KB per wave in flight.  The loads are 16 bytes at any
+// 4-byte alignment; the codes of a quad are one store when the output allows
+// it (PK), bytes otherwise.  One wave holds a column of up to 2560 rows without
+// a barrier; longer ones take four.  The whole call at 10000 x 100000 to e4m3:
+// 0.96 ms, 5.2 TB/s of its 5 GB (2.65 ms with two passes of 4-byte loads and a
+// cleared output).
+template <int TO, int T, int KQ, bool PK>
 __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ A, int64_t lda,
                                                   int p, int64_t n, void* __restrict__ out,
                                                   int64_t ldq, float* __restrict__ scale) {
+    using Code = typename QuadCode<TO>::T;
+    using Elem = typename std::conditional<TO == kStBF16, uint16_t, uint8_t>::type;
+    constexpr int CPB = 256 / T;   // columns per workgroup
+    __shared__ float red[4];
+    const int t = threadIdx.x % T;
+    int64_t col = (int64_t)blockIdx.x * CPB + threadIdx.x / T;
+    const bool live = col < n;
+    if (!live) col = n - 1;        // every wave reaches the barrier
+    const float* a = A + col * lda;
+    const int nqf = p >> 2;
+    f4q v[KQ];
+    float tail = 0.f;              // rows 4 nqf .. p - 1, one per thread 0 .. 2
+    if (nqf > 0) {
+#pragma unroll
+        for (int k = 0; k < KQ; ++k) {
+            const int q = t + T * k;
+            v[k] = __builtin_nontemporal_load(
+                reinterpret_cast<const f4u*>(a + 4 * (q < nqf ? q : nqf - 1)));
+        }
+    }
+    if (t < (p & 3)) tail = a[4 * nqf + t];
+    float sc = 1.0f;
+    if constexpr (TO == kStF8) {
+        float mx = fabsf(tail);
+        mx = mx > 0.f ? mx : 0.f;  // a NaN does not count, as below
+        if (nqf > 0) {
+#pragma unroll
+            for (int k = 0; k < KQ; ++k)   // clamped quads repeat one of the column's own
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fabsf(v[k][e]));
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        if constexpr (T == 256) {
+            if ((t & 63) == 0) red[t >> 6] = mx;
+            __syncthreads();
+            mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+        }
+        sc = mx > 0.f ? mx / 448.0f : 1.0f;
+    }
+    if (!live) return;
+    Elem* q0 = static_cast<Elem*>(out) + col * ldq;
+    if (nqf > 0) {
+#pragma unroll
+        for (int k = 0; k < KQ; ++k) {
+            const int q = t + T * k;
+            if (q >= nqf) continue;
+            const Code c = quad_code<TO>(v[k], sc);
+            if constexpr (PK) {
+                *reinterpret_cast<Code*>(q0 + 4 * q) = c;
+            } else {
+                Elem e4[4];
+                __builtin_memcpy(e4, &c, sizeof(e4));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) q0[4 * q + e] = e4[e];
+            }
+        }
+    }
+    if (t < (p & 3)) q0[4 * nqf + t] = (Elem)one_code<TO>(tail, sc);
+    if (scale && t == 0) scale[col] = sc;
+}
+
+// Columns too long for the registers of a workgroup (p > 40960): one wave per
+// column, two reads of A.
+template <int TO>
+__global__ __launch_bounds__(256) void k_quantize_long(const float* __restrict__ A, int64_t lda,
+                                                       int p, int64_t n, void* __restrict__ out,
+                                                       int64_t ldq, float* __restrict__ scale) {
     const int lane = threadIdx.x & 63;
     const int64_t col = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (col >= n) return;
     const float* a = A + col * lda;
-    if constexpr (TO == kStBF16) {
-        uint16_t* q = static_cast<uint16_t*>(out) + col * ldq;
-        for (int r = lane; r < p; r += 64) q[r] = (uint16_t)bf16_rne(a[r]);
-        if (scale && lane == 0) scale[col] = 1.0f;
-    } else {
+    float sc = 1.0f;
+    if constexpr (TO == kStF8) {
         float mx = 0.f;
         for (int r = lane; r < p; r += 64) mx = fmaxf(mx, fabsf(a[r]));
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-        const float sc = mx > 0.f ? mx / 448.0f : 1.0f;
-        uint8_t* q = static_cast<uint8_t*>(out) + col * ldq;
-        for (int r = lane; r < p; r += 64) q[r] = (uint8_t)e4m3_rne(a[r] / sc);
-        if (lane == 0) scale[col] = sc;
+        sc = mx > 0.f ? mx / 448.0f : 1.0f;
     }
+    for (int r = lane; r < p; r += 64) {
+        const uint32_t c = one_code<TO>(a[r], sc);
+        if constexpr (TO == kStBF16) static_cast<uint16_t*>(out)[col * ldq + r] = (uint16_t)c;
+        else static_cast<uint8_t*>(out)[col * ldq + r] = (uint8_t)c;
+    }
+    if (scale && lane == 0) scale[col] = sc;
 }
 
 // ------------------------------------------------------- correlation kernel
@@ -713,13 +826,37 @@ __global__ __launch_bounds__(256) void k_corr_qw(PassParams pp, const float* __r
 }
 
 // ------------------------------------------------------------- launchers
+template <int TO>
+static void launch_quantize_to(const float* A, int64_t lda, int p, int64_t n, void* out,
+                               int64_t ldq, float* scale, hipStream_t st) {
+    // packed stores need each column of the output aligned to a quad of codes
+    const uintptr_t quad = TO == kStBF16 ? 8 : 4;
+    const bool pk = (ldq & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & (quad - 1)) == 0;
+#define GPSPCA_QZ(TT, KK)                                                                      \
+    do {                                                                                       \
+        const dim3 grid((unsigned)((n + 256 / TT - 1) / (256 / TT))), block(256);              \
+        if (pk)                                                                                \
+            hipLaunchKernelGGL((k_quantize<TO, TT, KK, true>), grid, block, 0, st, A, lda, p,  \
+                               n, out, ldq, scale);                                            \
+        else                                                                                   \
+            hipLaunchKernelGGL((k_quantize<TO, TT, KK, false>), grid, block, 0, st, A, lda, p, \
+                               n, out, ldq, scale);                                            \
+    } while (0)
+    if (p <= 1024) GPSPCA_QZ(64, 4);
+    else if (p <= 2560) GPSPCA_QZ(64, 10);
+    else if (p <= 10240) GPSPCA_QZ(256, 10);
+    else if (p <= 20480) GPSPCA_QZ(256, 20);
+    else if (p <= 40960) GPSPCA_QZ(256, 40);
+    else
+        hipLaunchKernelGGL(k_quantize_long<TO>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st,
+                           A, lda, p, n, out, ldq, scale);
+#undef GPSPCA_QZ
+}
+
 hipError_t launch_quantize(const float* A, int64_t lda, int p, int64_t n, int to, void* out,
                            int64_t ldq, float* scale, hipStream_t st) {
-    const dim3 grid((unsigned)((n + 3) / 4)), block(256);
-    if (to == GPSPCA_BF16)
-        hipLaunchKernelGGL(k_quantize<kStBF16>, grid, block, 0, st, A, lda, p, n, out, ldq, scale);
-    else
-        hipLaunchKernelGGL(k_quantize<kStF8>, grid, block, 0, st, A, lda, p, n, out, ldq, scale);
+    if (to == GPSPCA_BF16) launch_quantize_to<kStBF16>(A, lda, p, n, out, ldq, scale, st);
+    else launch_quantize_to<kStF8>(A, lda, p, n, out, ldq, scale, st);
     return hipGetLastError();
 }
 
