@@ -46,6 +46,12 @@ int fail(int code, const std::string& msg) {
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Workgroups of k_colnorm: four per CU (16 waves with 16 KB of loads in flight
+// each), and at least one batch of 4 columns per wave.
+static int colnorm_grid(int64_t n, int ncu) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(4LL * ncu, cdiv(n, 16)));
+}
+
 // GPSPCA_MFMA_BALANCE=0 turns the balanced partition of the matrix-core
 // correlation off (every wave then takes whole tiles only).
 static bool mfma_balance_enabled() {
@@ -963,7 +969,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     } else if (path && multistart) {
         // problem j starts at the column of the j-th largest norm (ties to the
         // lower index), normalized on its own
-        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(2LL * ncu, cdiv(A->n, 16)));
+        const int grid = colnorm_grid(A->n, ncu);
         if (!norms_in) GPSPCA_HIP(launch_colnorm(pp, A->dtype, P.norms, grid, st));
         GPSPCA_HIP(launch_topm(pl, norms_in ? norms_in : P.norms, P.cand_v, P.cand_i, P.idx, st));
         GPSPCA_HIP(launch_gather(pl, pp, P.idx, P.g64, st));
@@ -978,7 +984,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
         p1.gram_grid = pl.gram_grid;
         p1.gram_rows = pl.gram_rows;
         p1.topm_grid = pl.topm_grid;
-        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(2LL * ncu, cdiv(A->n, 16)));
+        const int grid = colnorm_grid(A->n, ncu);
         if (!norms_in) GPSPCA_HIP(launch_colnorm(pp, A->dtype, P.norms, grid, st));
         GPSPCA_HIP(launch_topm(p1, norms_in ? norms_in : P.norms, P.cand_v, P.cand_i, P.idx, st));
         PassParams pp1 = pp;
@@ -991,7 +997,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
         if (il) GPSPCA_HIP(launch_x_interleave(pl, P.x[0], P.xil[0], st));
     } else {
         // the m columns of largest norm (ties to the lower index)
-        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(2LL * ncu, cdiv(A->n, 16)));
+        const int grid = colnorm_grid(A->n, ncu);
         if (!norms_in) GPSPCA_HIP(launch_colnorm(pp, A->dtype, P.norms, grid, st));
         GPSPCA_HIP(launch_topm(pl, norms_in ? norms_in : P.norms, P.cand_v, P.cand_i, P.idx, st));
         GPSPCA_HIP(launch_gather(pl, pp, P.idx, P.g64, st));
@@ -1534,7 +1540,7 @@ int gpspca_column_norms(const gpspca_matrix* A, double* norms, void* stream) {
     Plan pl;
     make_plan(A, GPSPCA_SL1, 1, 1, ncu, &pl);
     const PassParams pp = make_params(A, pl, 0.0, nullptr);
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(2LL * ncu, cdiv(A->n, 16)));
+    const int grid = colnorm_grid(A->n, ncu);
     GPSPCA_HIP(launch_colnorm(pp, A->dtype, norms, grid, static_cast<hipStream_t>(stream)));
     return GPSPCA_OK;
 }

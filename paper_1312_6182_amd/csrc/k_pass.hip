@@ -32,6 +32,9 @@ namespace gpspca {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
+typedef uint32_t u4n __attribute__((ext_vector_type(4)));
+typedef uint32_t u4na __attribute__((ext_vector_type(4), aligned(4)));
+
 __device__ __forceinline__ f4 zero4() { return f4{0.f, 0.f, 0.f, 0.f}; }
 
 // Quad q (rows 4q..4q+3) of one column.  Full quads use one 16-byte load when
@@ -914,40 +917,96 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 // ---------------------------------------------------------------------------
-// k_colnorm: ||a_i||_2 with FP64 accumulation; one wavefront per column range,
-// four columns in flight.
+// k_colnorm: ||a_i||_2 with FP64 accumulation; one wavefront per column range.
+// One read of A and nothing else, so it is bound by the bytes in flight: a wave
+// issues 16 unconditional 16-byte loads (CN columns x CU segments of 1 KB) before
+// it uses the first, and four such workgroups share a CU.  A lane's segments
+// are 4 FP32, 8 bfloat16 or 16 e4m3 rows; addresses past the last full segment
+// are clamped into the column and their values dropped.
 // ---------------------------------------------------------------------------
+template <int ST>
+__device__ __forceinline__ double sumsq16(const u4n& w) {
+    if constexpr (ST == kStF32) {
+        const double x = __uint_as_float(w[0]), y = __uint_as_float(w[1]);
+        const double z = __uint_as_float(w[2]), v = __uint_as_float(w[3]);
+        return x * x + y * y + z * z + v * v;
+    } else {
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (ST == kStBF16) {
+                const double x = __uint_as_float(w[e] << 16);
+                const double y = __uint_as_float(w[e] & 0xFFFF0000u);
+                s += x * x + y * y;
+            } else {
+                const qf2 a = e4m3_pair(w[e], false), b = e4m3_pair(w[e], true);
+                // the square of an e4m3 value (4 significant bits) is exact in FP32
+                s += (double)(a.x * a.x) + (double)(a.y * a.y) + (double)(b.x * b.x) +
+                     (double)(b.y * b.y);
+            }
+        }
+        return s;
+    }
+}
+
 template <bool VEC, int ST>
 __global__ __launch_bounds__(256) void k_colnorm(PassParams pp, double* __restrict__ norms) {
     const int lane = threadIdx.x & 63;
     const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int64_t nw = (int64_t)gridDim.x * 4;
     const int64_t cb = pp.n * wave / nw, ce = pp.n * (wave + 1) / nw;
-    const int p = pp.p, nqf = p >> 2, nq = (p + 3) >> 2;
-    constexpr int C = 4;
-    for (int64_t c0 = cb; c0 < ce; c0 += C) {
-        double s[C];
-        const void* colp[C];
+    constexpr int ES = ST == kStF32 ? 4 : ST == kStBF16 ? 2 : 1;
+    constexpr int R = 16 / ES;                 // rows of a segment
+    const int p = pp.p, nsf = p / R;
+    constexpr int CN = 4, CU = 4;
+    for (int64_t c0 = cb; c0 < ce; c0 += CN) {
+        double s[CN];
+        const uint8_t* colp[CN];
 #pragma unroll
-        for (int b = 0; b < C; ++b) {
+        for (int b = 0; b < CN; ++b) {
             s[b] = 0.0;
             const int64_t c = (c0 + b < ce) ? c0 + b : ce - 1;
-            colp[b] = column_ptr<ST>(pp, c);
+            colp[b] = static_cast<const uint8_t*>(column_ptr<ST>(pp, c));
         }
-        for (int q = lane; q < nq; q += 64) {
+        for (int q0 = 0; q0 < nsf; q0 += 64 * CU) {
+            u4n w[CU][CN];
 #pragma unroll
-            for (int b = 0; b < C; ++b) {
-                f4 a;
-                if constexpr (ST == kStF32)
-                    a = load_quad<VEC>(static_cast<const float*>(colp[b]), q, nqf, p);
-                else
-                    a = load_quad_st<ST>(colp[b], q, nqf, p);
-                s[b] += (double)a.x * a.x + (double)a.y * a.y + (double)a.z * a.z +
-                        (double)a.w * a.w;
+            for (int u = 0; u < CU; ++u) {
+                const int q = q0 + 64 * u + lane;
+                const int64_t at = 16 * (int64_t)(q < nsf ? q : nsf - 1);
+#pragma unroll
+                for (int b = 0; b < CN; ++b) {
+                    if constexpr (VEC)
+                        w[u][b] = __builtin_nontemporal_load(reinterpret_cast<const u4n*>(colp[b] + at));
+                    else
+                        w[u][b] = __builtin_nontemporal_load(reinterpret_cast<const u4na*>(colp[b] + at));
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < CU; ++u) {
+                const bool in = q0 + 64 * u + lane < nsf;
+#pragma unroll
+                for (int b = 0; b < CN; ++b) {
+                    const double v = sumsq16<ST>(w[u][b]);
+                    s[b] += in ? v : 0.0;
+                }
+            }
+        }
+        // the rows past the last full segment, one per lane
+        const int r = nsf * R + lane;
+        if (r < p) {
+#pragma unroll
+            for (int b = 0; b < CN; ++b) {
+                double v;
+                if constexpr (ST == kStF32) v = reinterpret_cast<const float*>(colp[b])[r];
+                else if constexpr (ST == kStBF16)
+                    v = bf16_value(reinterpret_cast<const uint16_t*>(colp[b])[r]);
+                else v = e4m3_value(colp[b][r]);
+                s[b] += v * v;
             }
         }
 #pragma unroll
-        for (int b = 0; b < C; ++b) {
+        for (int b = 0; b < CN; ++b) {
             const double tot = wave_allreduce_sum(s[b]);
             if (lane == 0 && c0 + b < ce) {
                 const double sc = (ST == kStF32) ? 1.0 : (double)column_scale(pp, c0 + b);

@@ -9,7 +9,7 @@ import torch
 import oracle as O
 from workloads import generators as W
 
-from _util import to_device
+from _util import TD, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +49,22 @@ def test_quantize_column_lengths(gpu, p, to, pad):
         assert not (got[3, 1:p] & 0x7F).any()
     else:
         assert (sc == 1.0).all() and got[3, 0] == 0x7F80
+
+
+@pytest.mark.parametrize("p", [1, 3, 5, 15, 17, 63, 255, 257, 1023, 1025, 4100])
+def test_column_norms_lengths(gpu, p):
+    """FP64 norms of every storage type around the 16-byte segments, their
+    64-lane rows and the 4-segment batches; an odd leading dimension in FP32."""
+    n = 133
+    A = W.gaussian(p, n, 50 + p)
+    A[:, 3] = 0.0
+    ref = np.sqrt((A.astype(np.float64) ** 2).sum(axis=0))
+    for lda in (p, (p + 3) // 4 * 4 + 4):
+        got = gpu.column_norms(to_device(A, lda=lda)).cpu().numpy()
+        np.testing.assert_allclose(got, ref, rtol=1e-14, atol=0)
+    for to in (O.BF16, O.E4M3):
+        Aq, sc = gpu.quantize(to_device(A), TD[to])
+        codes, scale = O.quantize(A, to)
+        deq = O.dequantize(codes, to, scale, p)
+        got = gpu.column_norms(Aq, col_scale=sc).cpu().numpy()
+        np.testing.assert_allclose(got, np.sqrt((deq ** 2).sum(axis=0)), rtol=1e-14, atol=0)
