@@ -156,7 +156,7 @@ static Tune env_tune() {
         const std::string fk = f;
         t.kernel = fk == "mfma" ? kTuneMfma : fk == "vx" ? kTuneVx : fk == "valu" ? kTuneValu
                  : fk == "rd" ? kTuneRd : fk == "rd128" ? kTuneRd128 : fk == "wg" ? kTuneWg
-                 : fk == "x3" ? kTuneX3 : fk == "qw" ? kTuneQw
+                 : fk == "x3" ? kTuneX3 : fk == "qw" ? kTuneQw : fk == "sh" ? kTuneSh
                  : fk == "mv" ? -1 : kTuneDefault;
     }
     if (const char* e = std::getenv("GPSPCA_MFMA_STAGES")) t.stages = std::atoi(e);
@@ -188,6 +188,26 @@ static int backproj_threshold(const gpspca_matrix* A, int m, int vec4, int restr
     const int st = A->dtype == GPSPCA_BF16 ? 1 : A->dtype == GPSPCA_F8E4M3 ? 2 : 0;
     const int groups = std::min(4, (m + 15) / 16);
     return thr[st][groups - 1];
+}
+
+// Whether k_corr_sh is the default correlation.  Its eight-wave workgroups pay
+// from a matrix that gives every wave work; below, one-wave or vector-ALU
+// workgroups spread a small matrix better.  Measured as whole 12-pass solves on
+// p x 10 p (the other kernel / k_corr_sh, in time):
+//   FP32, aligned   m 5-16: 0.96 at 1600, 1.15 at 3200, 1.01-1.03 at 4000 and
+//                   10000; m 17-32: 1.00 at 100-400, 1.05-1.10 at 800-6000;
+//                   m > 32: 0.97 up to 4000, 1.17 at 6000, 1.3 at 10000
+//   FP32, unaligned m 2-4: 0.94 at 400, 1.13 at 1600, 1.5 at 6000; m 5-8: 0.92
+//                   up to 1600, 1.0 at 2000-3200, 1.07 at 6000; m 9-16: 0.96 at
+//                   400, 1.12 at 1600, 1.9 at 6000; m > 16: 1.02 at 100, 3 at 6000
+//   bfloat16        0.97-1.05 up to 800, 1.03-1.16 above
+//   e4m3, m <= 32   0.97 up to 800, 1.02-1.07 at 2000-3200, 1.1-1.2 at 10000
+static bool sh_default(const gpspca_matrix* A, int m, int vec4, int path) {
+    const double e = (double)A->p * (double)A->n;
+    if (A->dtype == GPSPCA_BF16) return true;
+    if (A->dtype == GPSPCA_F8E4M3) return e >= 3e7;
+    if (vec4) return m > 32 ? e >= 2.5e8 : m > 16 ? true : (m >= 5 || path) && e >= 4e7;
+    return m > 16 ? true : m > 8 ? e >= 1e7 : m > 4 ? e >= 4e7 : m >= 2 && e >= 2e7;
 }
 
 // ----------------------------------------------------------------------- plan
@@ -229,9 +249,8 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
         // correlation kernel.  Choice: an explicit configuration (the autotuner
         // trying candidates), else the environment (tests, benchmarks), else the
         // autotuner's table, else the measured default -- register-resident X
-        // for m <= 4, the FP32 matrix cores up to m = 32, and the FP32 values
-        // split into bfloat16 parts on the bfloat16 matrix cores beyond (m = 64
-        // on 10000 x 100000: 1243 us against 1301 for the best FP32 kernel).
+        // for m <= 4, k_corr_sh where sh_default says so, else LDS DMA on the
+        // FP32 matrix cores (m > 32: their bfloat16 parts).
         Tune tn{kTuneDefault, 0, 0};
         if (force) {
             tn = *force;
@@ -245,6 +264,12 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
         const bool vx_ok = f32 && pl->vec4 && m >= 2 && m <= 8 && A->p <= 10240 && A->p >= 4 && !path;
         const bool mv_ok = f32 && pl->vec4 && m <= 16 && A->p >= 4;
         if (restricted) {}
+        else if (corr_sh_ok(*pl) &&
+                 (tn.kernel == kTuneSh || (tn.kernel == kTuneDefault && tn.stages == 0 &&
+                                           tn.waves == 0 && sh_default(A, m, pl->vec4, path)))) {
+            pl->use_sh = 1;
+            (f32 ? pl->use_mfma : pl->use_q) = 1;
+        }
         else if (!f32) pl->use_q = 1;
         else if (tn.kernel == -1 && mv_ok) pl->use_mv = 1;
         else if (tn.kernel == kTuneVx && vx_ok) pl->use_vx = 1;
@@ -255,9 +280,15 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
         else if (tn.kernel == kTuneWg && pl->vec4) pl->use_mfma = pl->use_wg = 1;
         else if (tn.kernel == kTuneValu) {}
         else if (vx_ok && m <= 4) pl->use_vx = 1;
-        else if (m > 32 && pl->vec4) pl->use_mfma = pl->use_x3 = 1;   // FP32 matrix cores are the bound
+        else if (m > 32 && pl->vec4) pl->use_mfma = pl->use_x3 = 1;
         else pl->use_mfma = pl->vec4;
-        if (pl->use_q && tn.kernel != kTuneMfma) {
+        if (pl->use_sh) {
+            // eight-wave workgroups sharing X, one per CU
+            pl->corr_M = 16;
+            pl->waves_per_cu = corr_sh_waves();
+            pl->corr_grid = corr_sh_grid(A->n, ncu);
+            pl->nwave_part = pl->corr_grid * corr_sh_waves();
+        } else if (pl->use_q && tn.kernel != kTuneMfma) {
             // 16/8-bit storage, four-wave workgroups sharing X (the default): one
             // per CU.  Staging: 2 stages of up to 8 tiles per wave, 3 stages of
             // 4 tiles (stages = 3), or for e4m3 2 stages of 4 tiles (stages = 2)
@@ -376,7 +407,7 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
     // tiles, one or two component groups): when the waves do not divide the tiles,
     // each takes q whole tiles and an equal row share of the leftover ones
     pl->bal = pl->bal_q = pl->bal_rem = 0;
-    if (pl->use_mfma && !pl->use_rd && !pl->use_x3 && !pl->use_wg && !pl->use_mv &&
+    if (pl->use_mfma && !pl->use_sh && !pl->use_rd && !pl->use_x3 && !pl->use_wg && !pl->use_mv &&
         !pl->use_q && !pl->use_qw && !pl->use_vx && !pl->fused_m1 && !pl->restricted &&
         m <= 32 && pl->mfma_stages == 8 && A->p >= 64 && mfma_balance_enabled()) {
         const int64_t ntile = cdiv(A->n, 16), W = pl->corr_grid;
@@ -427,12 +458,28 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
     pl->total = o;
 }
 
+// The plan of a solve in ws_bytes of workspace: the default configuration, or,
+// where only that one's buffers are too large, the leaner correlation kernel of
+// the same problem (fewer objective partials, no interleaved X for unaligned
+// columns).
+static void make_plan_fit(const gpspca_matrix* A, int form, int m, int max_iter, int ncu, Plan* pl,
+                          int path, int restricted, size_t ws_bytes) {
+    make_plan(A, form, m, max_iter, ncu, pl, path, restricted);
+    if (pl->total <= ws_bytes || !pl->use_sh) return;
+    const Tune lean{A->dtype != GPSPCA_F32 ? kTuneQw : !pl->vec4 ? kTuneValu
+                    : m > 32 ? kTuneX3 : kTuneMfma, 0, 0};
+    Plan alt;
+    make_plan(A, form, m, max_iter, ncu, &alt, path, restricted, &lean);
+    if (alt.total <= ws_bytes) *pl = alt;
+}
+
 // Configurations the autotuner tries for this problem (the default first).
 static std::vector<Tune> tune_candidates(const gpspca_matrix* A, int m, int path) {
     std::vector<Tune> c;
     c.push_back(Tune{kTuneDefault, 0, 0});
     const bool vec = ((A->lda & 3) == 0) && ((reinterpret_cast<uintptr_t>(A->data) & 15) == 0);
     if (A->dtype != GPSPCA_F32) {
+        c.push_back(Tune{kTuneQw, 8, 0});
         c.push_back(Tune{kTuneQw, 3, 0});
         if (A->dtype == GPSPCA_F8E4M3) c.push_back(Tune{kTuneQw, 2, 0});
         c.push_back(Tune{kTuneMfma, 2, 4});
@@ -441,7 +488,11 @@ static std::vector<Tune> tune_candidates(const gpspca_matrix* A, int m, int path
         return c;
     }
     if (m == 1 && !path && A->p <= 20480) return c;  // the fused single-unit pass
-    if (!vec) return c;
+    if (!vec) {
+        if (m >= 2) c.push_back(Tune{kTuneValu, 0, 0});
+        return c;
+    }
+    if (m <= 16) c.push_back(Tune{kTuneSh, 0, 0});
     if (m <= 16) {
         for (int st = 2; st <= 4; ++st) c.push_back(Tune{kTuneMfma, st, 4});
         c.push_back(Tune{kTuneMfma, 8, 4});   // 2 stages of 8-tile chunks
@@ -672,6 +723,9 @@ static int enqueue_pass(const Plan& pl, const PassParams& pp, const Ptrs& P, int
             GPSPCA_HIP(launch_corr_vx(pl, pp, Xk, P.S, P.act, P.fpart, P.nnzpart, P.ctrl, st));
         else if (pl.use_mv)
             GPSPCA_HIP(launch_corr_mv(pl, pp, Xk, P.S, P.act, P.fpart, P.nnzpart, P.ctrl, st));
+        else if (pl.use_sh)
+            GPSPCA_HIP(launch_corr_sh(pl, pp, Xk, P.xil[k & 1], P.S, P.act, P.fpart, P.nnzpart,
+                                      P.ctrl, st));
         else if (pl.use_qw)
             GPSPCA_HIP(launch_corr_qw(pl, pp, Xk, P.xil[k & 1], P.S, P.act, P.fpart, P.nnzpart,
                                       P.ctrl, st));
@@ -872,6 +926,7 @@ static int run_passes(const Plan& pl, const PassParams& pp, const Ptrs& P, int m
     tl.collect(pl.fused_m1 ? "k_pass_m1"
                            : pl.use_vx ? "k_corr_vx"
                            : pl.use_mv ? "k_corr_mv"
+                           : pl.use_sh ? "k_corr_sh"
                            : pl.use_qw ? "k_corr_qw"
                            : pl.use_q ? "k_corr_q"
                            : pl.use_x3 ? "k_corr_x3"
@@ -911,7 +966,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     if (rc) return rc;
     const int pform = path ? (form == GPSPCA_SL0 ? GPSPCA_BL0 : GPSPCA_BL1) : form;
     Plan pl;
-    make_plan(A, pform, m, max_iter, ncu, &pl, path, mask ? 1 : 0);
+    make_plan_fit(A, pform, m, max_iter, ncu, &pl, path, mask ? 1 : 0, ws_bytes);
     if (ws_bytes < pl.total) return fail(GPSPCA_ENOMEM, "workspace too small");
     pl.defl_q = defl_q;
     pl.defl_k = defl_q ? defl_k : 0;
@@ -1169,7 +1224,7 @@ int gpspca_solve_noalloc(const gpspca_matrix* A, int form, int m, double gamma,
     rc = device_cus(&ncu);
     if (rc) return rc;
     Plan pl;  // the plan solve_core will make
-    make_plan(A, form, m, max_iter, ncu, &pl);
+    make_plan_fit(A, form, m, max_iter, ncu, &pl, 0, 0, GPSPCA_NOALLOC_SCRATCH_BYTES);
     if (pl.total > GPSPCA_NOALLOC_SCRATCH_BYTES)
         return fail(GPSPCA_ENOMEM, "problem needs " + std::to_string(pl.total) +
                                        " bytes of scratch, more than GPSPCA_NOALLOC_SCRATCH_BYTES (" +
@@ -1466,6 +1521,7 @@ static int time_config(const gpspca_matrix* A, int pform, int m, double gamma, i
 static std::string tune_text(const Plan& pl) {
     char b[96];
     const char* k = pl.fused_m1 ? "k_pass_m1" : pl.use_vx ? "k_corr_vx"
+                  : pl.use_sh ? "k_corr_sh"
                   : pl.use_x3 ? "k_corr_x3"
                   : pl.use_rd ? (pl.rd128 ? "k_corr_rd(128-byte lines)" : "k_corr_rd")
                   : pl.use_wg ? "k_corr_wg"

@@ -71,7 +71,7 @@ struct BalArgs {
 
 // A configuration of the correlation kernel: the autotuner's unit of choice.
 enum TuneKernel { kTuneDefault = 0, kTuneMfma = 1, kTuneVx = 2, kTuneValu = 3, kTuneRd = 4,
-                  kTuneWg = 5, kTuneRd128 = 6, kTuneX3 = 7, kTuneQw = 8 };
+                  kTuneWg = 5, kTuneRd128 = 6, kTuneX3 = 7, kTuneQw = 8, kTuneSh = 9 };
 struct Tune {
     int kernel;            // TuneKernel
     int stages;            // LDS stages (matrix-core kernels), 0 = default
@@ -113,6 +113,8 @@ struct Plan {
     int waves_per_cu;      // resident matrix-core workgroups per CU
     int use_rd;            // matrix-core correlation with register-direct operand loads
     int use_x3;            // FP32 correlation on the bfloat16 matrix cores (three-part split)
+    int use_sh;            // correlation by eight-wave workgroups sharing X (any storage, any
+                           // alignment), A through registers; with use_mfma or use_q
     int use_wg;            // matrix-core correlation, four waves sharing X per workgroup
     int rd_depth;          // its software-pipeline depth (stages of 32 rows)
     int rd128;             // register-direct loads of whole 128-byte lines (8 columns each)
@@ -151,6 +153,14 @@ hipError_t launch_corr_x3(const Plan& pl, const PassParams& pp, const float* X, 
                           float* S, uint8_t* act, double* fpart, int* nnzpart, const Ctrl* ctrl,
                           hipStream_t st);
 int corr_mfma_blocks_per_cu(int m, int stages);
+// eight-wave workgroups sharing X (k_corr_sh.hip): its grid, waves per workgroup
+// (one objective partial each) and whether it takes the plan's matrix
+int corr_sh_grid(int64_t n, int ncu);
+int corr_sh_waves();
+bool corr_sh_ok(const Plan& pl);
+hipError_t launch_corr_sh(const Plan& pl, const PassParams& pp, const float* X, const float* Xil,
+                          float* S, uint8_t* act, double* fpart, int* nnzpart, const Ctrl* ctrl,
+                          hipStream_t st);
 hipError_t launch_corr_mv(const Plan& pl, const PassParams& pp, const float* X, float* S,
                           uint8_t* act, double* fpart, int* nnzpart, const Ctrl* ctrl,
                           hipStream_t st);

@@ -9,7 +9,7 @@ import torch
 import oracle as O
 from workloads import generators as W
 
-from _util import TD, to_device
+from _util import (TD, corr_band, fp32_round, rel, tie_mask, to_device, x_to_device)
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +68,91 @@ def test_column_norms_lengths(gpu, p):
         deq = O.dequantize(codes, to, scale, p)
         got = gpu.column_norms(Aq, col_scale=sc).cpu().numpy()
         np.testing.assert_allclose(got, np.sqrt((deq ** 2).sum(axis=0)), rtol=1e-14, atol=0)
+
+
+# (p, n, m): fewer rows than one stage or slot, one row past a stage, fewer tiles
+# than waves, one tile past a round of 32, ragged tiles, every component group
+SH_SHAPES = [(3, 40, 2), (17, 16, 16), (63, 700, 5), (65, 130, 17), (128, 4099, 33),
+             (257, 8193 * 16 + 1, 8), (1003, 3001, 32), (1025, 2000, 64)]
+
+
+@pytest.mark.parametrize("store", ["f32", "odd", "bf16", "e4m3"])
+@pytest.mark.parametrize("p,n,m", SH_SHAPES)
+def test_shared_x_correlation(gpu, p, n, m, store, monkeypatch):
+    """One pass of k_corr_sh in every mode and component group against FP64."""
+    if m > p:
+        m = p
+    print(f"\n[corr sh] {store} p={p} n={n} m={m}", flush=True)
+    monkeypatch.setenv("GPSPCA_CORR_KERNEL", "sh")
+    A = W.gaussian(p, n, p + m)
+    scale = None
+    if store in ("f32", "odd"):
+        Ad = to_device(A, lda=(p + 3) // 4 * 4 if store == "f32" else p | 1)
+        A64 = A.astype(np.float64)
+    else:
+        to = O.BF16 if store == "bf16" else O.E4M3
+        Ad, scale = gpu.quantize(to_device(A), TD[to])
+        A64 = O.dequantize(*((c := O.quantize(A, to))[0], to, c[1], p))
+    X = fp32_round(W.random_orthonormal(p, m, 7))
+    gamma, mu = 0.9, np.linspace(1.0, 0.7, m)
+    out = gpu.step(Ad, O.BL1, x_to_device(X), gamma, mu=list(mu), col_scale=scale)
+    ref = O.step(A64, O.BL1, X, gamma, mu=mu)
+    S = out.S.cpu().numpy().astype(np.float64)
+    ties = tie_mask(A64, X, O.BL1, gamma, mu)
+    np.testing.assert_array_equal((S != 0)[~ties], (ref["S"] != 0)[~ties])
+    assert np.all(np.abs(S - ref["S"]) <= corr_band(A64, X) * mu[None, :] + 1e-7 * np.abs(ref["S"]))
+    assert rel(out.G.cpu().numpy(), ref["G"]) <= 1e-5
+    np.testing.assert_allclose(out.f, ref["f"], rtol=1e-5)
+
+
+@pytest.mark.parametrize("store", ["f32", "odd", "bf16"])
+def test_shared_x_correlation_non_finite(gpu, store, monkeypatch):
+    """An infinity or an entry near the FP32 limit keeps the meaning it has in
+    plain FP32 products (the split parts of both are NaN); a NaN marks no entry."""
+    monkeypatch.setenv("GPSPCA_CORR_KERNEL", "sh")
+    p, n, m = 261, 200, 40
+    A = W.gaussian(p, n, 5)
+    # bfloat16's largest finite value is 3.39e38; 3.4e38 would round to infinity
+    A[7, 3], A[8, 4], A[9, 5] = np.inf, 3.38e38 if store == "bf16" else 3.4e38, np.nan
+    Ad = to_device(A, lda=264 if store == "f32" else 261)
+    if store == "bf16":
+        Ad, _ = gpu.quantize(to_device(A), torch.bfloat16)
+        A = Ad.t().contiguous().float().cpu().numpy().T
+    X = fp32_round(W.random_orthonormal(p, m, 8))
+    with pytest.raises(gpu.GpspcaError):
+        gpu.step(Ad, O.BL1, x_to_device(X), 0.5)
+    keep = [c for c in range(n) if c != 3]
+    B = np.ascontiguousarray(A[:, keep])
+    Bd = to_device(B, lda=264 if store == "f32" else 261)
+    if store == "bf16":
+        Bd, _ = gpu.quantize(Bd, torch.bfloat16)
+    S = gpu.step(Bd, O.BL1, x_to_device(X * 2.0 ** -20), 0.5).S.cpu().numpy()
+    big = keep.index(4)
+    want = B[:, big].astype(np.float64) @ (X * 2.0 ** -20)
+    np.testing.assert_allclose(S[big], np.sign(want) * np.maximum(np.abs(want) - 0.5, 0), rtol=1e-6)
+    assert not S[keep.index(5)].any()
+
+
+def test_noalloc_limit_of_unaligned_columns(gpu, monkeypatch):
+    """The largest problem that fits the library's scratch with the vector-ALU
+    correlation still fits when the default kernel needs more."""
+    p, m = 101, 8
+    hi = 1_600_000
+    buf = torch.randn((hi, p), device="cuda")
+
+    def fits(n):
+        try:
+            gpu.solve_noalloc(buf[:n].t(), gpu.BL1, m, 1e3, tol=0.0, max_iter=1)
+            return True
+        except gpu.GpspcaError as e:
+            assert e.code == gpu.ENOMEM
+            return False
+
+    monkeypatch.setenv("GPSPCA_CORR_KERNEL", "valu")
+    lo = 1_000_000
+    assert fits(lo) and not fits(hi)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if fits(mid) else (lo, mid)
+    monkeypatch.delenv("GPSPCA_CORR_KERNEL")
+    assert fits(lo)
