@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libgpspca.so")
 SCHED_LIB = os.path.join(HERE, "libgpspca_sched.so")
-SOURCES = ["k_pass.hip", "k_corr_mfma.hip", "k_corr_sh.hip", "k_quant.hip", "k_reduce.hip", "k_init_fin.hip",
+SOURCES = ["k_pass.hip", "k_corr_mfma.hip", "k_corr_sh.hip", "k_quant.hip", "k_reduce.hip", "k_small.hip", "k_init_fin.hip",
            "gpspca_abi.cpp", "serve.cpp"]
 ARCH = "gfx950"
 

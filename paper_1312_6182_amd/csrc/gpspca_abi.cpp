@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -458,6 +459,11 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
     pl->total = o;
 }
 
+// Whether a solve may run as one persistent kernel: not while launches are timed
+// or when a kernel, a tuned configuration or the graph setting was asked for
+// (those name the launches of a pass).  GPSPCA_SMALL=0 turns it off.
+static bool small_enabled(const gpspca_matrix* A, int m, int path);
+
 // The plan of a solve in ws_bytes of workspace: the default configuration, or,
 // where only that one's buffers are too large, the leaner correlation kernel of
 // the same problem (fewer objective partials, no interleaved X for unaligned
@@ -636,6 +642,17 @@ struct Prof {
     std::string name;
 };
 static Prof g_prof;
+
+static bool small_enabled(const gpspca_matrix* A, int m, int path) {
+    const char* e = std::getenv("GPSPCA_SMALL");
+    if ((e && e[0] == '0') || std::getenv("GPSPCA_GRAPH") || std::getenv("GPSPCA_BACKPROJ")) return false;
+    const Tune tn = env_tune();
+    Tune tt;
+    if (tn.kernel != kTuneDefault || tn.stages || tn.waves || tune_lookup(tune_key(A, m, path), &tt))
+        return false;
+    std::lock_guard<std::mutex> lk(g_prof.mu);
+    return !g_prof.on;
+}
 
 thread_local KernelEvents g_kev;
 
@@ -871,6 +888,77 @@ static int capture_pair(const Plan& pl, const PassParams& pp, const Ptrs& P, Pas
     return GPSPCA_OK;
 }
 
+// Admission of the persistent solves (k_small.hip) of this process: their
+// workgroups wait for each other, so all of a solve's must be resident at once.
+// Workgroup i of a launch goes to XCD i mod 8, and one takes a CU's LDS, so a
+// solve with nb workgroups holds ceil(nb / 8) CUs of an XCD at most; the solves
+// in flight on a device never hold more than its XCDs have.  A thread that
+// finds no room waits for another's solve to end.  Other kernels end by
+// themselves; should workgroups wait in vain all the same (another process's
+// persistent kernels), the kernel's bounded wait ends it.
+class SmallRoom {
+  public:
+    SmallRoom(int nb, int ncu, int dev) : need_(nb > 1 ? (nb + 7) / 8 : 0), dev_(dev & 63) {
+        if (!need_) return;
+        std::unique_lock<std::mutex> lk(mu());
+        const int cap = std::max(need_, ncu / 8);
+        cv().wait(lk, [&] { return used()[dev_] + need_ <= cap; });
+        used()[dev_] += need_;
+    }
+    ~SmallRoom() {
+        if (!need_) return;
+        {
+            std::lock_guard<std::mutex> lk(mu());
+            used()[dev_] -= need_;
+        }
+        cv().notify_all();
+    }
+    SmallRoom(const SmallRoom&) = delete;
+    SmallRoom& operator=(const SmallRoom&) = delete;
+
+  private:
+    static std::mutex& mu() { static std::mutex m; return m; }
+    static std::condition_variable& cv() { static std::condition_variable c; return c; }
+    static int* used() { static int u[64] = {0}; return u; }
+    int need_, dev_;
+};
+
+// Passes of one k_small launch: a long solve is cut so that the host sees it end.
+constexpr int kSmallChunk = 256;
+constexpr int kSmallAborted = 1000;   // internal: run the passes as separate launches
+
+static int run_small(const Plan& pl, const PassParams& pp, const Ptrs& P, int max_iter, int ncu,
+                     hipStream_t st, Ctrl* fin, bool noalloc, const std::function<int()>& tail) {
+    int dev = 0;
+    GPSPCA_HIP(hipGetDevice(&dev));
+    Ctrl stack_snap;
+    Ctrl* snap = &stack_snap;
+    int rc = noalloc ? GPSPCA_OK : pinned_ctrl(&snap);
+    if (rc) return rc;
+    // GPSPCA_SMALL_WAIT: the barriers' limit in ticks of the 100 MHz clock (tests)
+    const char* we = std::getenv("GPSPCA_SMALL_WAIT");
+    const int64_t wait = we ? std::atoll(we) : 200000000;
+    SmallRoom room(pl.small_nb, ncu, dev);
+    uint32_t bar0 = 0;
+    for (int kk = 0; kk < max_iter; kk += kSmallChunk) {
+        const int c = std::min(kSmallChunk, max_iter - kk);
+        GPSPCA_HIP(launch_small(pl, pp, P.x[0], P.x[1], P.S, P.gpart, P.fpart, P.nnzpart, P.g64,
+                                P.trace, P.coef + 5 * (size_t)pl.m * pl.m, P.pstate, P.ctrl, c,
+                                bar0, wait, st));
+        bar0 += (uint32_t)c * (uint32_t)pl.small_nb * (pl.small_whole ? 1u : 2u);
+        if (kk + c >= max_iter) break;
+        GPSPCA_HIP(hipMemcpyAsync(snap, P.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+        GPSPCA_HIP(hipStreamSynchronize(st));
+        if (snap->done || snap->abort) break;
+    }
+    rc = tail();
+    if (rc) return rc;
+    GPSPCA_HIP(hipMemcpyAsync(snap, P.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+    GPSPCA_HIP(hipStreamSynchronize(st));
+    *fin = *snap;
+    return snap->abort ? kSmallAborted : GPSPCA_OK;
+}
+
 // Enqueue passes in growing chunks; the stopping rule runs on the device and
 // the host reads the control block once per chunk (with tol = 0 every pass is
 // enqueued at once).  Pairs of passes go through a captured graph when the
@@ -960,7 +1048,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
                double tol, int max_iter, void* workspace, size_t ws_bytes, hipStream_t st,
                float* X, float* Z, uint32_t* support, double* obj_trace, int* n_iter,
                int* status_out, const double* norms_in, int multistart, const double* defl_q,
-               int defl_k, int exact, int noalloc) {
+               int defl_k, int exact, int noalloc, int no_small) {
     int ncu = 0;
     int rc = device_cus(&ncu);
     if (rc) return rc;
@@ -971,6 +1059,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     pl.defl_q = defl_q;
     pl.defl_k = defl_q ? defl_k : 0;
     pl.exact = (exact && !path) ? 1 : 0;
+    if (!no_small && small_enabled(A, m, path)) pl.small_nb = small_workgroups(pl, &pl.small_whole);
     const Ptrs P = carve(pl, workspace);
     PassParams pp = make_params(A, pl, gamma, mu, gammas);
     pp.nact = &P.ctrl->nact;
@@ -1084,7 +1173,15 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
         return GPSPCA_OK;
     };
     Ctrl fin;
-    rc = run_passes(pl, pp, P, max_iter, tol, st, &fin, noalloc != 0, &outputs);
+    if (pl.small_nb) {
+        rc = run_small(pl, pp, P, max_iter, ncu, st, &fin, noalloc != 0, outputs);
+        if (rc == kSmallAborted)
+            return solve_core(A, form, m, gamma, mu, gammas, path, mask, X0, tol, max_iter,
+                              workspace, ws_bytes, st, X, Z, support, obj_trace, n_iter, status_out,
+                              norms_in, multistart, defl_q, defl_k, exact, noalloc, 1);
+    } else {
+        rc = run_passes(pl, pp, P, max_iter, tol, st, &fin, noalloc != 0, &outputs);
+    }
     if (rc) return rc;
     if (fin.status < 0) return fail(fin.status, status_text(fin.status));
     if (fin.n_iter < 1) return fail(GPSPCA_EDEVICE, "solve ended without a pass");

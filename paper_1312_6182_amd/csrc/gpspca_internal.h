@@ -30,6 +30,8 @@ struct Ctrl {
     int warm;              // the previous retraction's eigenvectors may seed the next
     int nact;              // columns with any active component in the current pass (the
                            // correlation kernels add to it; the stop kernel clears it)
+    uint32_t bar;          // grid barrier of k_small: arrivals so far
+    int abort;             // ... 1 once a wait ran out
     double tol;
     double last_F;
 };
@@ -103,6 +105,9 @@ struct Plan {
     int topm_grid;
     int vec4;              // float4 loads of A are legal
     int dtype;             // storage of A (GPSPCA_F32 | BF16 | F8E4M3)
+    int small_nb;          // workgroups of the persistent kernel that runs every pass of the
+                           // solve (k_small.hip), 0: one launch per kernel and pass
+    int small_whole;       // ... every workgroup sums all of G itself
     int use_q;             // 16/8-bit storage: bfloat16 matrix-core correlation
     int use_qw;            // ... by four-wave workgroups that share each X stage
     int restricted;        // frozen-support passes over a column list (VALU correlation)
@@ -208,6 +213,19 @@ hipError_t launch_corr_qw(const Plan& pl, const PassParams& pp, const float* X, 
                          uint8_t* act, double* fpart, int* nnzpart, const Ctrl* ctrl,
                          hipStream_t st);
 
+// Every pass of a solve on a small matrix in one launch (k_small.hip): the
+// workgroups for the plan (0: not taken), and `passes` passes from the control
+// block's state; bar0: barrier arrivals of the solve's earlier launches.
+constexpr int kSmallTiles = 8;                        // tiles of 16 columns per workgroup, at least
+constexpr int kSmallWgs = 64;                         // most workgroups
+constexpr int64_t kSmallWhole = 16384;                // partial entries each workgroup sums alone
+struct PathState;
+int small_workgroups(const Plan& pl, int* whole);
+hipError_t launch_small(const Plan& pl, const PassParams& pp, float* x0, float* x1, float* S,
+                        float* gpart, double* fpart, int* nnzpart, double* g64, double* trace,
+                        double* vprev, PathState* ps, Ctrl* ctrl, int passes, uint32_t bar0,
+                        int64_t wait_ticks, hipStream_t st);
+
 // reductions, retraction, stop test (k_reduce.hip)
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st);
 hipError_t launch_ctrl_reset(Ctrl* ctrl, int max_iter, double tol, hipStream_t st);
@@ -305,6 +323,6 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
                float* X, float* Z, uint32_t* support, double* obj_trace, int* n_iter,
                int* status_out, const double* norms_in, int multistart = 0,
                const double* defl_q = nullptr, int defl_k = 0, int exact = 0,
-               int noalloc = 0);
+               int noalloc = 0, int no_small = 0);
 
 }  // namespace gpspca

@@ -156,3 +156,95 @@ def test_noalloc_limit_of_unaligned_columns(gpu, monkeypatch):
         lo, hi = (mid, hi) if fits(mid) else (lo, mid)
     monkeypatch.delenv("GPSPCA_CORR_KERNEL")
     assert fits(lo)
+
+
+def _small_case(gpu, kind, Ad, scale, A64, m, iters):
+    """(GPU call, oracle results per problem) of one persistent solve."""
+    top = np.sqrt((A64 ** 2).sum(axis=0)).max()
+    if kind in ("path", "multi"):
+        form = O.SL1
+        order = np.argsort(-(A64 ** 2).sum(axis=0), kind="stable")
+        gams = [0.1 * top * (1 + 0.4 * (j if kind == "path" else 0)) for j in range(m)]
+        starts = [order[0 if kind == "path" else j] for j in range(m)]
+        refs = [O.solve(A64, form, 1, gams[j],
+                        X0=(A64[:, starts[j]] / np.linalg.norm(A64[:, starts[j]]))[:, None],
+                        tol=0.0, max_iter=iters) for j in range(m)]
+        if kind == "path":
+            return (lambda: gpu.solve_path(Ad, form, gams, tol=0.0, max_iter=iters, col_scale=scale),
+                    refs)
+        return (lambda: gpu.solve_multistart(Ad, form, m, gams[0], tol=0.0, max_iter=iters,
+                                             col_scale=scale), refs)
+    form = {"SL1": O.SL1, "BL1": O.BL1, "BL1X": O.BL1X}[kind]
+    gamma = 0.1 * top
+    X0 = O.init(A64, m)[0]
+    ref = O.solve(A64, form, m, gamma, X0=X0, tol=0.0, max_iter=iters)
+    return (lambda: gpu.solve(Ad, int(form), m, gamma, tol=0.0, max_iter=iters, col_scale=scale),
+            [ref])
+
+
+# (p, n): one row, fewer columns than a tile, one workgroup, one tile past the
+# workgroups' shares, ragged quads, rows past the threads' quads, the LDS limit
+@pytest.mark.parametrize("store", ["f32", "bf16", "e4m3"])
+@pytest.mark.parametrize("kind,m", [("SL1", 1), ("BL1", 5), ("BL1", 8), ("BL1X", 2), ("path", 6),
+                                    ("multi", 16)])
+@pytest.mark.parametrize("p,n", [(9, 15), (17, 129), (63, 1041), (101, 1003), (258, 2100),
+                                 (2100, 300)])
+def test_small_persistent_solve(gpu, p, n, kind, m, store, monkeypatch):
+    """Solves that run as one persistent kernel (and those just past its limits)
+    against the oracle, twice bitwise the same, and in pieces of one launch."""
+    m = min(m, p, n)
+    iters = 7
+    print(f"\n[small] {kind} {store} p={p} n={n} m={m}", flush=True)
+    A = W.planted_block(p, n, 2, p + n, k=max(2, n // 20))[0]
+    scale = None
+    if store == "f32":
+        Ad, A64 = to_device(A, lda=p | 1), A.astype(np.float64)
+    else:
+        to = O.BF16 if store == "bf16" else O.E4M3
+        Ad, scale = gpu.quantize(to_device(A), TD[to])
+        codes, sc = O.quantize(A, to)
+        A64 = O.dequantize(codes, to, sc, p)
+    fn, refs = _small_case(gpu, kind, Ad, scale, A64, m, iters)
+    a, b = fn(), fn()
+    assert torch.equal(a.X, b.X) and torch.equal(a.Z, b.Z) and torch.equal(a.support, b.support)
+    if len(refs) == 1 and kind not in ("path", "multi"):
+        assert rel(a.X.cpu().numpy(), refs[0]["X"]) <= 1e-5
+        np.testing.assert_allclose(a.trace, refs[0]["trace"], rtol=1e-5)
+        assert a.n_iter == refs[0]["n_iter"]
+    else:
+        for j, ref in enumerate(refs):
+            assert rel(a.X[:, j].cpu().numpy(), ref["X"][:, 0]) <= 1e-5
+            np.testing.assert_allclose(a.traces[j], ref["trace"], rtol=1e-5)
+    # a barrier that never waits long enough: the passes run as separate launches
+    monkeypatch.setenv("GPSPCA_SMALL_WAIT", "0")
+    c = fn()
+    assert rel(c.X.cpu().numpy(), a.X.cpu().numpy()) <= 1e-5 and c.n_iter == a.n_iter
+
+
+def test_small_solve_of_many_passes_and_threads(gpu):
+    """More passes than one launch holds, stopped by the tolerance or not, from
+    several threads on their own streams at once: bitwise the solo results."""
+    import threading
+    A = to_device(W.planted_block(150, 1500, 2, 3, k=40)[0])
+    top = float(A.norm(dim=0).max())
+    jobs = [(g, f, m, tol) for g in (0.05, 0.12) for f, m in ((gpu.SL1, 1), (gpu.BL1, 4))
+            for tol in (0.0, 1e-9)]
+
+    def run(job):
+        g, f, m, tol = job
+        return gpu.solve(A, f, m, g * top, tol=tol, max_iter=600)
+
+    solo = [run(j) for j in jobs]
+    assert any(r.n_iter == 600 for r in solo)
+    got = [None] * len(jobs)
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            got[i] = run(jobs[i])
+
+    torch.cuda.synchronize()
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    for a, b in zip(solo, got):
+        assert torch.equal(a.X, b.X) and torch.equal(a.Z, b.Z) and a.trace == b.trace
