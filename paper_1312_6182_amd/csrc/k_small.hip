@@ -42,6 +42,9 @@
 
 namespace gpspca {
 
+static_assert(offsetof(Ctrl, bar) % 8 == 0 && offsetof(Ctrl, abort) == offsetof(Ctrl, bar) + 4,
+              "read as one word");
+
 namespace {
 
 typedef float f4c __attribute__((ext_vector_type(4)));
@@ -153,13 +156,15 @@ __device__ bool grid_barrier(Ctrl* ctrl, uint32_t target, int64_t limit, int* fl
         __hip_atomic_fetch_add(&ctrl->bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int64_t began = wall_clock64();
         int ok = 1;
-        while ((int32_t)(get(&ctrl->bar) - target) < 0) {
-            if (get(&ctrl->abort) || wall_clock64() - began > limit) {
+        for (;;) {
+            // arrivals and the abort flag in one read
+            const uint64_t v = get(reinterpret_cast<const uint64_t*>(&ctrl->bar));
+            if ((int32_t)((uint32_t)v - target) >= 0) break;
+            if ((v >> 32) || wall_clock64() - began > limit) {
                 put(&ctrl->abort, 1);
                 ok = 0;
                 break;
             }
-            __builtin_amdgcn_s_sleep(1);
         }
         *flag = ok;
     }
