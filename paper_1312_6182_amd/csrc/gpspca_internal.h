@@ -30,7 +30,7 @@ struct Ctrl {
     int warm;              // the previous retraction's eigenvectors may seed the next
     int nact;              // columns with any active component in the current pass (the
                            // correlation kernels add to it; the stop kernel clears it)
-    int pad;
+    int no_newton;         // the Newton retraction once did not converge in this solve
     uint32_t bar;          // grid barrier of k_small: arrivals so far (8-byte aligned, read
     int abort;             // together with), 1 once a wait ran out
     double tol;

@@ -55,6 +55,7 @@ __device__ __forceinline__ void ctrl_reset_fields(Ctrl* ctrl, int max_iter, doub
     ctrl->max_iter = max_iter;
     ctrl->warm = 0;
     ctrl->nact = 0;
+    ctrl->no_newton = 0;
     ctrl->bar = 0;
     ctrl->abort = 0;
     ctrl->tol = tol;
@@ -942,7 +943,7 @@ hipError_t launch_stop(const Plan& pl, const double* fpart, const int* nnzpart,
     // threads: the Jacobi steps of m = 64 have 32 x 32 blocks plus 64 x 32 rotated pairs of V;
     // m = 1 needs no eigen-solver: one wave makes every barrier free
     const int threads = pl.m > 1 ? jacobi_threads(pl.m) : 64;
-    const size_t shm = (pl.m > 1) ? (size_t)3 * (pl.m + (pl.m & 1)) * LDM * sizeof(double) : 0;
+    const size_t shm = (pl.m > 1) ? (size_t)retract_lds(pl.m) : 0;
     static const bool lds_once = (set_lds_limit((const void*)k_stop), true);
     (void)lds_once;
     hipLaunchKernelGGL(k_stop, dim3(1), dim3(threads), shm, st, pl.m, pl.nwave_part, fpart,
@@ -1104,7 +1105,7 @@ hipError_t launch_project_diag(const Plan& pl, const double* gram, double* coef,
 
 // Projection of a starting point onto the feasible set: Omega = (G^T G)^{-1/2}
 // (or 1/||g||); a rank-deficient start fails with GPSPCA_EINVAL.
-__global__ void k_project(int m, double* __restrict__ coef, Ctrl* __restrict__ ctrl) {
+__global__ __launch_bounds__(1024) void k_project(int m, double* __restrict__ coef, Ctrl* __restrict__ ctrl) {
     if (ctrl->done) return;
     __shared__ StopShared ss;
     extern __shared__ double dyn[];
@@ -1123,6 +1124,14 @@ __global__ void k_project(int m, double* __restrict__ coef, Ctrl* __restrict__ c
                 ctrl->status = GPSPCA_EINVAL;
                 ctrl->done = 1;
             }
+        }
+        return;
+    }
+    if (newton_root<false>(m, coef + 2 * mm, coef, A0, ss.lam)) {
+        for (int e = t; e < mm; e += nt) coef[mm + e] = 0.0;
+        if (t == 0) {
+            ctrl->ndead = 0;
+            ctrl->warm = 0;
         }
         return;
     }
@@ -1153,7 +1162,7 @@ hipError_t launch_project(const Plan& pl, const double* gram, double* coef, Ctrl
     hipError_t e = launch_gram_sum(pl, pl.m * pl.m, pl.gram_grid, gram, coef, ctrl, st);
     if (e != hipSuccess) return e;
     const int threads = jacobi_threads(pl.m);
-    const size_t shm = (pl.m > 1) ? (size_t)3 * (pl.m + (pl.m & 1)) * LDM * sizeof(double) : 0;
+    const size_t shm = (pl.m > 1) ? (size_t)retract_lds(pl.m) : 0;
     static const bool lds_once = (set_lds_limit((const void*)k_project), true);
     (void)lds_once;
     hipLaunchKernelGGL(k_project, dim3(1), dim3(threads), shm, st, pl.m, coef, ctrl);

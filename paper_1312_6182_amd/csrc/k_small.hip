@@ -15,7 +15,7 @@
 //      that it writes back, with a second barrier before all of G is read
 //   3  in every workgroup alike: the objective, the stopping rule and the
 //      retraction (m = 1 and gamma paths: g / ||g||, deflated: P g / ||P g||,
-//      blocks: the polar factor, its Jacobi eigensolve on one wave), X_{k+1}
+//      blocks: the polar factor, its small matrices on one wave), X_{k+1}
 //      into LDS.  Equal inputs in equal order give every workgroup the same X
 //      and the same decision, so neither has to be communicated.
 //
@@ -95,7 +95,7 @@ __host__ __device__ inline SmallLds small_lds(int p, int m, int path, int64_t n,
     int o = 0;
     L.a = o;    o += 16 * L.sq * 16 * tw;
     L.g = o;    o += 8 * p * m;
-    L.jac = o;  o += block ? 3 * (m + (m & 1)) * LDM * 8 : 0;
+    L.jac = o;  o += block ? retract_lds(m) : 0;
     L.coef = o; o += block ? 6 * m * m * 8 : 0;
     L.x = o = (o + 15) / 16 * 16; o += 16 * nq4 * m;
     L.gp = o;   o += m == 1 ? 16 * kSmT : 4 * kSmW * 64 * m;
@@ -170,96 +170,6 @@ __device__ bool grid_barrier(Ctrl* ctrl, uint32_t target, int64_t limit, int* fl
     }
     __syncthreads();
     return *flag != 0;
-}
-
-// Sums over the 64 lanes of a wave by row shifts and broadcasts in the vector
-// ALU (a cross-lane read through LDS has ten times the latency, and the small
-// phases of a pass are chains of them); every lane gets lane 63's total.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-    const uint64_t u = __double_as_longlong(v);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, true);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xF, true);
-    return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_add(int v) {
-    return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, true);
-}
-template <typename T>
-__device__ __forceinline__ T dpp_scan63(T v) {
-    v = dpp_add<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row
-    v = dpp_add<0x112, 0xF>(v);
-    v = dpp_add<0x114, 0xF>(v);
-    v = dpp_add<0x118, 0xF>(v);
-    v = dpp_add<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
-__device__ __forceinline__ double wave_sum_s(double v) {
-    const uint64_t u = __double_as_longlong(dpp_scan63(v));
-    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, 63);
-    const uint32_t hi = __builtin_amdgcn_readlane((int)(u >> 32), 63);
-    return __longlong_as_double(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ int wave_sum_s(int v) {
-    return __builtin_amdgcn_readlane(dpp_scan63(v), 63);
-}
-
-// W = M^{-1/2} of the m x m (m <= 8) symmetric positive definite M (LDS, leading
-// dim m) by one wave, lane (i, j) holding entry (i, j): the coupled
-// Newton-Schulz iteration Y <- Y T, Z <- T Z, T = (3 I - Z Y) / 2, from Y = M / c,
-// Z = I with c = ||M||_F / 2 (so the eigenvalues of Y lie in (0, 2]).  Z -> c^{1/2}
-// M^{-1/2} quadratically once Z Y is near I, with an error of about
-// cond(M) eps.  A well-conditioned M, which is what the polar factor of a pass
-// has, takes 6 to 10 iterations of two LDS round trips each, where the Jacobi
-// sweeps are chains of FP64 divisions and roots: 3 against 13 us per pass at
-// m = 5.  False when 12 iterations are not enough (cond(M) beyond about 10^3,
-// or not positive definite): the caller then runs the Jacobi eigensolve.
-__device__ bool newton_inv_sqrt(int m, const double* M, double* W, double* buf) {
-    const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
-    double* const Yb = buf;            // 8 x 8 each, leading dim 10
-    double* const Zb = buf + 80;
-    double* const Tb = buf + 160;
-    const bool in = i < m && j < m;
-    const double mij = in ? M[i * m + j] : 0.0;
-    const double f2 = wave_sum_s(mij * mij);
-    const double c = 0.5 * sqrt(f2);
-    if (!(c > 0.0) || !isfinite(c)) return false;
-    const double id = i == j ? 1.0 : 0.0;
-    double y = in ? mij / c : id, z = id;
-    auto row_dot = [&](const double* A, const double* B) {   // both symmetric
-        double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-        for (int k = 0; k < 8; k += 2) {
-            s0 = __builtin_fma(A[i * 10 + k], B[j * 10 + k], s0);
-            s1 = __builtin_fma(A[i * 10 + k + 1], B[j * 10 + k + 1], s1);
-        }
-        return s0 + s1;
-    };
-    bool last = false;
-    for (int it = 0; it < 12; ++it) {
-        Yb[i * 10 + j] = y;
-        Zb[i * 10 + j] = z;
-        group_sync<true>();
-        const double r = row_dot(Zb, Yb);
-        const double e = fabs(id - r);
-        if (__any(!(e < 1e100))) return false;
-        last = !__any(e > 1e-8);       // the update below squares it
-        Tb[i * 10 + j] = 1.5 * id - 0.5 * r;
-        group_sync<true>();
-        const double yn = row_dot(Yb, Tb);
-        z = row_dot(Tb, Zb);
-        y = yn;
-        group_sync<true>();
-        if (last) break;
-    }
-    if (!last) return false;
-    Zb[i * 10 + j] = z;
-    group_sync<true>();
-    if (in) W[i * m + j] = 0.5 * (z + Zb[j * 10 + i]) / sqrt(c);
-    group_sync<true>();
-    return true;
 }
 
 template <int ST, int MB, bool BLOCK>
@@ -803,14 +713,8 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
                     group_sync<true>();
                 }
                 const int mr = m + (m & 1);
-                if (MB == 8 && ss.ndead == 0 && newton_inv_sqrt(m, coef + 2 * mm, coef, jac)) {
-                    for (int e = lane; e < mm; e += 64) coef[mm + e] = 0.0;
-                    if (lane == 0) lc.ndead = 0;
-                    group_sync<true>();
-                } else {
-                    block_coefficients<true>(m, coef, coef + 5 * mm, ss, jac, jac + mr * LDM,
-                                             jac + 2 * mr * LDM, &lc);
-                }
+                block_coefficients<true>(m, coef, coef + 5 * mm, ss, jac, jac + mr * LDM,
+                                         jac + 2 * mr * LDM, &lc);
                 int bad = 0;
                 for (int e = lane; e < mm; e += 64) {
                     if (a.exact) coef[e] *= ss.dsc[e / m];
@@ -882,6 +786,7 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
             a.ctrl->ndead = lc.ndead;
             a.ctrl->degenerate_seen = lc.degenerate_seen;
             a.ctrl->warm = lc.warm;
+            a.ctrl->no_newton = lc.no_newton;
             a.ctrl->last_F = lc.last_F;
         }
     }

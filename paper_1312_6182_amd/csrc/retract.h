@@ -360,6 +360,226 @@ __device__ __forceinline__ double wave_sum_d(double v) {
     return v;
 }
 
+// Sums over the 64 lanes of a wave by row shifts and broadcasts in the vector
+// ALU (a cross-lane read through LDS has ten times the latency, and the small
+// phases of a pass are chains of them); every lane gets lane 63's total.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t u = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xF, true);
+    return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) {
+    return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, true);
+}
+template <typename T>
+__device__ __forceinline__ T dpp_scan63(T v) {
+    v = dpp_add<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ double wave_sum_s(double v) {
+    const uint64_t u = __double_as_longlong(dpp_scan63(v));
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, 63);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(u >> 32), 63);
+    return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ int wave_sum_s(int v) {
+    return __builtin_amdgcn_readlane(dpp_scan63(v), 63);
+}
+
+// W = M^{-1/2} of the m x m (m <= 8) symmetric positive definite M (LDS, leading
+// dim m) by one wave, lane (i, j) holding entry (i, j): the coupled
+// Newton-Schulz iteration Y <- Y T, Z <- T Z, T = (3 I - Z Y) / 2, from Y = M / c,
+// Z = I with c = ||M||_F / 2 (so the eigenvalues of Y lie in (0, 2]).  Z -> c^{1/2}
+// M^{-1/2} quadratically once Z Y is near I, with an error of about
+// cond(M) eps.  A well-conditioned M, which is what the polar factor of a pass
+// has, takes 6 to 10 iterations of two LDS round trips each, where the Jacobi
+// sweeps are chains of FP64 divisions and roots: 3 against 13 us per pass at
+// m = 5 in k_small.  False when 20 iterations are not enough (cond(M) beyond
+// about 10^5, or not positive definite): the caller then runs the Jacobi
+// eigensolve.
+__device__ inline bool newton_inv_sqrt(int m, const double* M, double* W, double* buf) {
+    const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+    double* const Yb = buf;            // 8 x 8 each, leading dim 10
+    double* const Zb = buf + 80;
+    double* const Tb = buf + 160;
+    const bool in = i < m && j < m;
+    const double mij = in ? M[i * m + j] : 0.0;
+    const double f2 = wave_sum_s(mij * mij);
+    const double c = 0.5 * sqrt(f2);
+    if (!(c > 0.0) || !isfinite(c)) return false;
+    const double id = i == j ? 1.0 : 0.0;
+    double y = in ? mij / c : id, z = id;
+    auto row_dot = [&](const double* A, const double* B) {   // both symmetric
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) {
+            s0 = __builtin_fma(A[i * 10 + k], B[j * 10 + k], s0);
+            s1 = __builtin_fma(A[i * 10 + k + 1], B[j * 10 + k + 1], s1);
+        }
+        return s0 + s1;
+    };
+    bool last = false;
+    for (int it = 0; it < 20; ++it) {
+        Yb[i * 10 + j] = y;
+        Zb[i * 10 + j] = z;
+        group_sync<true>();
+        const double r = row_dot(Zb, Yb);
+        const double e = fabs(id - r);
+        if (__any(!(e < 1e100))) return false;
+        last = !__any(e > 1e-8);       // the update below squares it
+        Tb[i * 10 + j] = 1.5 * id - 0.5 * r;
+        group_sync<true>();
+        const double yn = row_dot(Yb, Tb);
+        z = row_dot(Tb, Zb);
+        y = yn;
+        group_sync<true>();
+        if (last) break;
+    }
+    if (!last) return false;
+    Zb[i * 10 + j] = z;
+    group_sync<true>();
+    if (in) W[i * m + j] = 0.5 * (z + Zb[j * 10 + i]) / sqrt(c);
+    group_sync<true>();
+    return true;
+}
+
+// The same for 9 <= m <= 64 by the whole workgroup (at least one wave per 16 x 16
+// tile: 64 ceil(m / 16)^2 threads): a wave keeps its tile of Y, Z and T in the
+// accumulator layout of v_mfma_f64_16x16x4_f64 (lane l, entry v: row 4 v + l / 16,
+// column l % 16), and the products read rows of both operands from LDS (they are
+// symmetric; leading dim 66 keeps the reads free of bank conflicts).  buf: three
+// matrices of 16 ceil(m / 16) rows.  The Jacobi sweeps at m = 64 are 63 dependent
+// steps each: with this iteration the stop kernel of a BL1 pass at m = 64 takes 68
+// instead of 175 us and the projection of a start 60 instead of 577 (m = 16: 12 and
+// 10 instead of 17 and 60; m = 8, by the one-wave form: 8.5 and 5 instead of 19
+// and 24).
+constexpr int kNewtonLd = 66;
+constexpr int kNewtonIter = 24;   // cond(M) up to about 10^7
+__device__ inline bool newton_inv_sqrt_mfma(int m, const double* M, double* W, double* buf,
+                                            double* red) {
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    constexpr int LD = kNewtonLd;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int nt = (m + 15) / 16, mp = 16 * nt;
+    double* const Yb = buf;
+    double* const Zb = buf + mp * LD;
+    double* const Tb = buf + 2 * mp * LD;
+    const bool mine = wv < nt * nt;
+    const int ti = mine ? wv / nt : 0, tj = mine ? wv % nt : 0;
+    const int i0 = 16 * ti + (lane >> 4), j = 16 * tj + (lane & 15);   // rows i0 + 4 v
+    double y[4], z[4], id[4];
+    double f2 = 0.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int i = i0 + 4 * v;
+        const bool in = mine && i < m && j < m;
+        y[v] = in ? M[i * m + j] : 0.0;
+        id[v] = i == j ? 1.0 : 0.0;
+        z[v] = id[v];
+        f2 += y[v] * y[v];
+    }
+    f2 = wave_sum_s(f2);
+    if (lane == 0) red[wv] = mine ? f2 : 0.0;
+    __syncthreads();
+    double tot = 0.0;
+    for (int w = 0; w < nt * nt; ++w) tot += red[w];
+    const double c = 0.5 * sqrt(tot);
+    if (!(c > 0.0) || !isfinite(c)) return false;   // the same in every thread
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int i = i0 + 4 * v;
+        y[v] = i < m && j < m ? y[v] / c : id[v];
+    }
+    auto store = [&](double* B, const double (&x)[4]) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) B[(i0 + 4 * v) * LD + j] = x[v];
+    };
+    // tile (ti, tj) of A B for symmetric A and B
+    auto prod = [&](const double* A, const double* B) {
+        d4 s = d4{0.0, 0.0, 0.0, 0.0};
+        const double* ar = A + (16 * ti + (lane & 15)) * LD + (lane >> 4);
+        const double* br = B + (16 * tj + (lane & 15)) * LD + (lane >> 4);
+        for (int k = 0; k < mp; k += 4)
+            s = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[k], br[k], s, 0, 0, 0);
+        return s;
+    };
+    bool last = false;
+    for (int it = 0; it < kNewtonIter; ++it) {
+        if (mine) {
+            store(Yb, y);
+            store(Zb, z);
+        }
+        __syncthreads();
+        int bad = 0, more = 0;
+        if (mine) {
+            const d4 r = prod(Zb, Yb);
+            double tv[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double e = fabs(id[v] - r[v]);
+                bad |= !(e < 1e100);
+                more |= e > 1e-8;      // the update below squares it
+                tv[v] = 1.5 * id[v] - 0.5 * r[v];
+            }
+            store(Tb, tv);
+        }
+        if (__syncthreads_or(bad)) return false;
+        last = !__syncthreads_or(more);
+        if (mine) {
+            const d4 yn = prod(Yb, Tb), zn = prod(Tb, Zb);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                y[v] = yn[v];
+                z[v] = zn[v];
+            }
+        }
+        __syncthreads();
+        if (last) break;
+    }
+    if (!last) return false;
+    if (mine) store(Zb, z);
+    __syncthreads();
+    if (mine) {
+        const double sc = 0.5 / sqrt(c);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = i0 + 4 * v;
+            if (i < m && j < m) W[i * m + j] = sc * (z[v] + Zb[j * LD + i]);
+        }
+    }
+    __syncthreads();
+    return true;
+}
+
+// LDS of the retraction of m components (bytes): three matrices for the Jacobi
+// eigensolve (rows rounded up to even) or the Newton iteration.
+__host__ __device__ inline int retract_lds(int m) {
+    const int jac = 3 * (m + (m & 1)) * LDM * 8;
+    const int nwt = m > 8 ? 3 * 16 * ((m + 15) / 16) * kNewtonLd * 8 : 240 * 8;
+    return jac > nwt ? jac : nwt;
+}
+
+// M^{-1/2} of a well-conditioned M by the Newton iteration of its size.
+template <bool WAVE>
+__device__ __forceinline__ bool newton_root(int m, const double* M, double* W, double* buf,
+                                            double* red) {
+    if constexpr (WAVE) {
+        return m <= 8 && newton_inv_sqrt(m, M, W, buf);
+    } else {
+        if (m > 8) return newton_inv_sqrt_mfma(m, M, W, buf, red);
+        return blockDim.x == 64 && newton_inv_sqrt(m, M, W, buf);
+    }
+}
+
 struct StopShared {
     double rot[kMaxM];
     double lam[kMaxM];
@@ -383,6 +603,18 @@ __device__ void block_coefficients(int m, double* coef, double* vprev, StopShare
     double* Om = coef;
     double* Ps = coef + mm;
     const int nl = ss.nlive, nd = ss.ndead;
+    // every component live and G^T G well conditioned: Omega = (G^T G)^{-1/2}
+    // (a solve in which the iteration once did not converge stays with Jacobi)
+    if (nd == 0 && !ctrl->no_newton) {
+        if (newton_root<WAVE>(m, GtG, Om, A0, ss.lam)) {
+            for (int e = t; e < mm; e += nt) Ps[e] = 0.0;
+            if (t == 0) ctrl->ndead = 0;
+            group_sync<WAVE>();
+            return;
+        }
+        group_sync<WAVE>();
+        if (t == 0) ctrl->no_newton = 1;
+    }
     for (int e = t; e < 2 * mm; e += nt) coef[e] = 0.0;
     // W_L = (G_L^T G_L)^{-1/2}
     const bool warm = (nd == 0) && ctrl->warm;

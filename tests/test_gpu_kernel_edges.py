@@ -248,3 +248,51 @@ def test_small_solve_of_many_passes_and_threads(gpu):
     [t.join() for t in ts]
     for a, b in zip(solo, got):
         assert torch.equal(a.X, b.X) and torch.equal(a.Z, b.Z) and a.trace == b.trace
+
+
+@pytest.mark.parametrize("kappa", [1.0, 30.0, 3e3, 1e7, 1e12])
+@pytest.mark.parametrize("m", [1, 2, 5, 8, 9, 16, 17, 32, 33, 48, 49, 64])
+def test_start_projection_by_size_and_condition(gpu, m, kappa):
+    """The polar factor of a start whose Gram matrix has condition kappa^2, in
+    every size of the Newton iteration and beyond its reach (Jacobi).  The X_0 of a
+    one-pass solve against numpy's SVD; FP64 throughout, so up to the rounding of
+    the FP32 start and result and its amplification by kappa."""
+    p, n = 200, 400
+    rng = np.random.default_rng(m)
+    U = np.linalg.qr(rng.standard_normal((p, m)))[0]
+    V = np.linalg.qr(rng.standard_normal((m, m)))[0]
+    sv = np.geomspace(1.0, 1.0 / kappa, m) if m > 1 else np.ones(1)
+    X0 = fp32_round(3.0 * (U * sv) @ V.T)
+    u, _, vt = np.linalg.svd(X0, full_matrices=False)
+    A = W.gaussian(p, n, 11)
+    try:
+        res = gpu.solve(to_device(A), gpu.BL1, m, 0.5, X0=x_to_device(X0), tol=0.0, max_iter=1)
+    except gpu.GpspcaError as e:
+        # the Gram matrix's smallest eigenvalues are FP64 rounding here
+        assert kappa == 1e12 and e.code == gpu.EINVAL
+        return
+    # the FP64 Gram matrix resolves singular values down to 1e-8 of the largest
+    tol = 1e-6 if kappa <= 3e3 else 1e-2
+    if kappa <= 1e7:
+        assert rel(res.X.cpu().numpy(), u @ vt) <= tol
+    X = res.X.double().cpu().numpy()
+    if kappa <= 3e3:
+        assert np.abs(X.T @ X - np.eye(m)).max() <= 1e-6
+
+
+@pytest.mark.parametrize("m,mu", [(5, "graded"), (8, "one"), (12, "graded"), (24, "one"),
+                                  (33, "one"), (64, "one")])
+def test_block_retraction_sizes(gpu, m, mu):
+    """Block solves of every retraction size, plain and with graded weights
+    (whose Gram matrix has a condition number of m^4 or more)."""
+    p, n, iters = 300, 1500, 5
+    A32 = W.planted_block(p, n, min(m, 8), 60 + m, k=20)[0]
+    A64 = A32.astype(np.float64)
+    w = np.ones(m) if mu == "one" else 1.0 / np.sqrt(np.arange(1, m + 1))
+    X0 = fp32_round(O.init(A64, m)[0])
+    gamma = W.gamma_absolute(A64, False, 0.05)
+    ref = O.solve(A64, O.BL1, m, gamma, mu=w, X0=X0, tol=0.0, max_iter=iters)
+    res = gpu.solve(to_device(A32), gpu.BL1, m, gamma, mu=list(w), X0=x_to_device(X0), tol=0.0,
+                    max_iter=iters)
+    assert rel(res.X.cpu().numpy(), ref["X"]) <= 1e-5
+    np.testing.assert_allclose(res.trace, ref["trace"], rtol=1e-5)
