@@ -2,12 +2,14 @@
 //
 // Default start: the m columns of largest norm, ordered by (-||a_i||, i), so
 // ties go to the lower index; their polar factor (or normalization) is the
-// starting point.  Selection is two-level: each workgroup keeps the top m of
-// its column range, one workgroup merges the candidates.
+// starting point.  Selection is two-level: each workgroup keeps the sorted top m
+// of its column range, one workgroup merges the sorted lists.
 //
 // Outputs: Z = S with unit-norm columns (a column with empty support stays
 // zero), the support as packed bit words, and X copied out of the internal
 // padded buffer.
+#include <cfloat>
+
 #include "gpspca_internal.h"
 #include "storage.h"
 
@@ -19,11 +21,6 @@ __device__ __forceinline__ bool better(double va, int64_t ia, double vb, int64_t
     return va > vb || (va == vb && ia < ib);
 }
 
-// m rounds of a workgroup argmax over [b, e) of (val, idx) pairs.  The order
-// "larger value, then lower index" is strict and total, so round r's winner
-// is the best pair that comes after round r-1's winner in it: one comparison
-// per pair and round, and any reduction order finds the same (unique) pair.
-// Results in chosen_v / chosen_i (index -1 once the pairs run out).
 __device__ __forceinline__ void wave_best(double& v, int64_t& i) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -36,60 +33,26 @@ __device__ __forceinline__ void wave_best(double& v, int64_t& i) {
     }
 }
 
-// Ranges of at most CAP pairs per thread are read once into registers (all
-// loads issued together); longer ones are re-read every round.
-template <int CAP>
+// m rounds of a workgroup argmax over norms [b, e), read anew in each.  The order
+// "larger value, then lower index" is strict and total, so round r's winner
+// is the best pair that comes after round r-1's winner in it: one comparison
+// per pair and round, and any reduction order finds the same (unique) pair.
+// Results in chosen_v / chosen_i (index -1 once the pairs run out).
 __device__ void topm_block(int m, int64_t b, int64_t e, const double* __restrict__ val,
-                           const int64_t* __restrict__ idx, double* chosen_v, int64_t* chosen_i,
-                           double* rv, int64_t* ri) {
+                           double* chosen_v, int64_t* chosen_i, double* rv, int64_t* ri) {
     const int t = threadIdx.x, nt = blockDim.x, lane = t & 63, wv = t >> 6, nw = (nt + 63) >> 6;
-    const bool in_regs = (e - b) <= (int64_t)CAP * nt;
-    double pv[CAP];
-    int64_t pi[CAP];
-    if (in_regs) {
-#pragma unroll
-        for (int u = 0; u < CAP; ++u) {
-            pv[u] = -INFINITY;
-            pi[u] = -1;
-        }
-        if (e > b) {
-#pragma unroll
-            for (int u = 0; u < CAP; ++u) {
-                const int64_t i = b + t + (int64_t)u * nt;
-                const int64_t ic = i < e ? i : e - 1;   // in range; dropped below when i >= e
-                const int64_t ci = idx ? idx[ic] : ic;
-                const double cv = val[ic];
-                pv[u] = (i < e && ci >= 0) ? cv : -INFINITY;
-                pi[u] = (i < e) ? ci : -1;
-            }
-        }
-    }
     double lv = INFINITY;   // the previous round's winner (none yet: every pair qualifies)
     int64_t li = -1;
     for (int r = 0; r < m; ++r) {
         double bv = -INFINITY;
         int64_t bi = -1;
-        if (in_regs) {
-#pragma unroll
-            for (int u = 0; u < CAP; ++u) {
-                if (pi[u] < 0) continue;
-                const bool after = (r == 0) || better(lv, li, pv[u], pi[u]);
-                if (after && better(pv[u], pi[u], bv, bi)) {
-                    bv = pv[u];
-                    bi = pi[u];
-                }
-            }
-        } else {
-            for (int64_t i = b + t; i < e; i += nt) {
-                const int64_t ci = idx ? idx[i] : i;
-                if (ci < 0) continue;
-                const double cv = val[i];
-                // after the previous winner in the order, and better than the best so far
-                const bool after = (r == 0) || better(lv, li, cv, ci);
-                if (after && better(cv, ci, bv, bi)) {
-                    bv = cv;
-                    bi = ci;
-                }
+        for (int64_t i = b + t; i < e; i += nt) {
+            const double cv = fmax(val[i], -DBL_MAX);
+            // after the previous winner in the order, and better than the best so far
+            const bool after = (r == 0) || better(lv, li, cv, i);
+            if (after && better(cv, i, bv, bi)) {
+                bv = cv;
+                bi = i;
             }
         }
         wave_best(bv, bi);
@@ -124,37 +87,170 @@ __device__ void topm_block(int m, int64_t b, int64_t e, const double* __restrict
     }
 }
 
-__global__ __launch_bounds__(256) void k_topm_local(int64_t n, int m, const double* __restrict__ norms,
-                                                    double* __restrict__ cv, int64_t* __restrict__ ci) {
-    __shared__ double rv[256];
-    __shared__ int64_t ri[256];
-    __shared__ double chv[kMaxM];
-    __shared__ int64_t chi[kMaxM];
-    const int64_t b = n * blockIdx.x / gridDim.x, e = n * (blockIdx.x + 1) / gridDim.x;
-    topm_block<8>(m, b, e, norms, nullptr, chv, chi, rv, ri);
-    for (int r = threadIdx.x; r < m; r += blockDim.x) {
-        cv[(size_t)blockIdx.x * m + r] = chv[r];
-        ci[(size_t)blockIdx.x * m + r] = chi[r];
+// Largest value of the 64 lanes, by row shifts and broadcasts in the vector ALU.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_max(double v) {
+    const uint64_t u = __double_as_longlong(v);
+    const int ulo = (int)(uint32_t)u, uhi = (int)(u >> 32);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(ulo, ulo, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(uhi, uhi, CTRL, ROWS, 0xF, false);
+    return fmax(v, __longlong_as_double(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_max(double v) {
+    v = dpp_max<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row
+    v = dpp_max<0x112, 0xF>(v);
+    v = dpp_max<0x114, 0xF>(v);
+    v = dpp_max<0x118, 0xF>(v);
+    v = dpp_max<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_max<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    const uint64_t u = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, 63);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(u >> 32), 63);
+    return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// Top m of the m-entry lists lv[list * m + r], list < nl <= 64 LPL, each sorted
+// (-inf past its end) and of lower indices than the next list, by one wave: lane
+// l keeps the heads of lists l LPL .. l LPL + LPL - 1, and each round takes the
+// largest head, of the lowest list among equals.  pos[r] receives its place in
+// lv, -1 once the lists run out.  A round is one maximum over the lanes and one
+// LDS read, no barrier.
+template <int LPL>
+__device__ void merge_lists(int nl, int m, const double* lv, int* pos) {
+    const int lane = threadIdx.x & 63;
+    double h[LPL];
+    int q[LPL];
+#pragma unroll
+    for (int u = 0; u < LPL; ++u) {
+        const int l = lane * LPL + u;
+        q[u] = 0;
+        h[u] = l < nl ? lv[l * m] : -INFINITY;
+    }
+    for (int r = 0; r < m; ++r) {
+        double b = h[0];
+        int bu = 0;
+#pragma unroll
+        for (int u = 1; u < LPL; ++u)
+            if (h[u] > b) {
+                b = h[u];
+                bu = u;
+            }
+        const double top = wave_max(b);
+        if (top == -INFINITY) {
+            for (int k = r + lane; k < m; k += 64) pos[k] = -1;
+            return;
+        }
+        const uint64_t eq = __ballot(b == top);
+        if (lane == __ffsll((unsigned long long)eq) - 1) {
+            const int l = lane * LPL + bu;
+#pragma unroll
+            for (int u = 0; u < LPL; ++u)
+                if (u == bu) {
+                    pos[r] = l * m + q[u];
+                    ++q[u];
+                    h[u] = q[u] < m ? lv[l * m + q[u]] : -INFINITY;
+                }
+        }
     }
 }
 
-// 1024 threads: the candidates (at most 256 workgroups x 64) fit 16 per thread.
-__global__ __launch_bounds__(1024) void k_topm_final(int ncand, int m, const double* __restrict__ cv,
+constexpr int kTopLane = 8;                    // norms per lane
+constexpr int64_t kTopRange = 256 * kTopLane;  // norms per workgroup
+
+// Top m of norms[b, e), sorted; at most kTopRange of them: each wave takes a
+// quarter, each lane consecutive norms of it in registers, and a round takes
+// the largest of the lanes' largest (the lowest lane, the first norm among
+// equals, so the lowest index).  The four waves run without barriers and wave 0
+// merges their lists.  The rounds are a serial chain, here of about 200 cycles
+// each; as reductions over the workgroup of (norm, index) pairs by cross-lane
+// reads through LDS with two barriers a round, they took 33 us (both kernels 88)
+// at n = 20011, m = 16 and 128 (420) at n = 100000, m = 64.  A norm that is not a number
+// counts as the lowest.  Longer ranges (n > 524288) are re-read every round.
+__global__ __launch_bounds__(256) void k_topm_local(int64_t n, int m, const double* __restrict__ norms,
+                                                    double* __restrict__ cv, int64_t* __restrict__ ci) {
+    const int64_t b = n * blockIdx.x / gridDim.x, e = n * (blockIdx.x + 1) / gridDim.x;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    if (e - b > kTopRange) {
+        __shared__ double rv[256];
+        __shared__ int64_t ri[256];
+        __shared__ double chv[kMaxM];
+        __shared__ int64_t chi[kMaxM];
+        topm_block(m, b, e, norms, chv, chi, rv, ri);
+        for (int r = t; r < m; r += blockDim.x) {
+            cv[(size_t)blockIdx.x * m + r] = chv[r];
+            ci[(size_t)blockIdx.x * m + r] = chi[r];
+        }
+        return;
+    }
+    __shared__ double lv[4 * kMaxM];
+    __shared__ int64_t li[4 * kMaxM];
+    __shared__ int pos[kMaxM];
+    const int64_t len = e - b;
+    const int64_t wb = b + len * wv / 4, we = b + len * (wv + 1) / 4;
+    const int per = (int)((we - wb + 63) / 64);          // <= kTopLane
+    const int64_t lb = wb + (int64_t)lane * per;
+    double v[kTopLane];
+#pragma unroll
+    for (int u = 0; u < kTopLane; ++u)
+        v[u] = (u < per && lb + u < we) ? fmax(norms[lb + u], -DBL_MAX) : -INFINITY;
+    for (int r = 0; r < m; ++r) {
+        double best = v[0];
+        int bu = 0;
+#pragma unroll
+        for (int u = 1; u < kTopLane; ++u)
+            if (v[u] > best) {
+                best = v[u];
+                bu = u;
+            }
+        const double top = wave_max(best);
+        if (top == -INFINITY) {
+            for (int k = r + lane; k < m; k += 64) lv[wv * m + k] = -INFINITY;
+            break;
+        }
+        const uint64_t eq = __ballot(best == top);
+        if (lane == __ffsll((unsigned long long)eq) - 1) {
+            lv[wv * m + r] = best;
+            li[wv * m + r] = lb + bu;
+#pragma unroll
+            for (int u = 0; u < kTopLane; ++u)
+                if (u == bu) v[u] = -INFINITY;
+        }
+    }
+    __syncthreads();
+    if (wv == 0) merge_lists<1>(4, m, lv, pos);
+    __syncthreads();
+    for (int r = t; r < m; r += blockDim.x) {
+        const int k = pos[r];
+        cv[(size_t)blockIdx.x * m + r] = k < 0 ? -INFINITY : lv[k];
+        ci[(size_t)blockIdx.x * m + r] = k < 0 ? -1 : li[k];
+    }
+}
+
+// The lists of at most 256 workgroups, staged in LDS by 1024 threads.
+__global__ __launch_bounds__(1024) void k_topm_final(int nl, int m, const double* __restrict__ cv,
                                                      const int64_t* __restrict__ ci,
                                                      int64_t* __restrict__ idx) {
-    __shared__ double rv[16];
-    __shared__ int64_t ri[16];
-    __shared__ double chv[kMaxM];
-    __shared__ int64_t chi[kMaxM];
-    topm_block<16>(m, 0, ncand, cv, ci, chv, chi, rv, ri);
-    for (int r = threadIdx.x; r < m; r += blockDim.x) idx[r] = chi[r];
+    extern __shared__ double lists[];
+    __shared__ int pos[kMaxM];
+    for (int k = threadIdx.x; k < nl * m; k += blockDim.x) lists[k] = cv[k];
+    __syncthreads();
+    if (threadIdx.x < 64) merge_lists<4>(nl, m, lists, pos);
+    __syncthreads();
+    for (int r = threadIdx.x; r < m; r += blockDim.x) idx[r] = pos[r] < 0 ? -1 : ci[pos[r]];
 }
 
 hipError_t launch_topm(const Plan& pl, const double* norms, double* cand_v, int64_t* cand_i,
                        int64_t* idx, hipStream_t st) {
+    static const bool lds_once =
+        (hipFuncSetAttribute((const void*)k_topm_final, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             256 * kMaxM * (int)sizeof(double)),
+         (void)hipGetLastError(), true);   // advisory: no sticky error is left behind
+    (void)lds_once;
+    if (pl.topm_grid > 256 || pl.m > kMaxM) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_topm_local, dim3(pl.topm_grid), dim3(256), 0, st, pl.n, pl.m, norms,
                        cand_v, cand_i);
-    hipLaunchKernelGGL(k_topm_final, dim3(1), dim3(1024), 0, st, pl.topm_grid * pl.m, pl.m,
+    hipLaunchKernelGGL(k_topm_final, dim3(1), dim3(1024),
+                       sizeof(double) * (size_t)pl.topm_grid * pl.m, st, pl.topm_grid, pl.m,
                        cand_v, cand_i, idx);
     return hipGetLastError();
 }

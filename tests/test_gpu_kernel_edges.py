@@ -296,3 +296,21 @@ def test_block_retraction_sizes(gpu, m, mu):
                     max_iter=iters)
     assert rel(res.X.cpu().numpy(), ref["X"]) <= 1e-5
     np.testing.assert_allclose(res.trace, ref["trace"], rtol=1e-5)
+
+
+@pytest.mark.parametrize("order", ["ties", "falling", "rising", "equal"])
+@pytest.mark.parametrize("n,m", [(1, 1), (63, 63), (64, 64), (257, 5), (1024, 16), (1025, 64),
+                                 (20011, 16), (100003, 64), (524288, 3), (600001, 64)])
+def test_start_columns_selection(gpu, n, m, order):
+    """The m starts of a one-pass multistart are the columns of largest norm, ties to
+    the lower index, around the lanes, waves, workgroups and register range of the
+    selection.  Column i is its index in signs, times a level: norms are exact
+    whole numbers, and the signs of X_0 give the index back."""
+    bits = 20
+    i = np.arange(n)
+    level = {"ties": np.random.default_rng(n + m).integers(1, 40, n), "falling": n - i,
+             "rising": i + 1, "equal": np.full(n, 3)}[order].astype(np.float32)
+    A = (2.0 * ((i[None, :] >> np.arange(bits)[:, None]) & 1) - 1.0).astype(np.float32) * level
+    res = gpu.solve_multistart(to_device(A), gpu.SL1, m, 0.01, tol=0.0, max_iter=1)
+    got = ((res.X.cpu().numpy() > 0) * (1 << np.arange(bits))[:, None]).sum(axis=0)
+    np.testing.assert_array_equal(got, np.argsort(-level.astype(np.float64), kind="stable")[:m])
