@@ -163,9 +163,9 @@ constexpr int64_t kTopRange = 256 * kTopLane;  // norms per workgroup
 // equals, so the lowest index).  The four waves run without barriers and wave 0
 // merges their lists.  The rounds are a serial chain, here of about 200 cycles
 // each; as reductions over the workgroup of (norm, index) pairs by cross-lane
-// reads through LDS with two barriers a round, they took 33 us (both kernels 88)
-// at n = 20011, m = 16 and 128 (420) at n = 100000, m = 64.  A norm that is not a number
-// counts as the lowest.  Longer ranges (n > 524288) are re-read every round.
+// reads through LDS with two barriers a round, they took 33 instead of 12 us (both
+// kernels 88 and 20) at n = 20011, m = 16 and 128 and 41 (420 and 67) at n = 100000,
+// m = 64.  A norm that is not a number counts as the lowest.  Longer ranges (n > 524288) are re-read every round.
 __global__ __launch_bounds__(256) void k_topm_local(int64_t n, int m, const double* __restrict__ norms,
                                                     double* __restrict__ cv, int64_t* __restrict__ ci) {
     const int64_t b = n * blockIdx.x / gridDim.x, e = n * (blockIdx.x + 1) / gridDim.x;

@@ -179,60 +179,91 @@ hipError_t launch_reduce_partials(const Plan& pl, const float* gpart, const int*
 }
 
 // ---------------------------------------------------------------------------
-// Row block r0..r0+nr: g_r = sum_y l1[y][.][r] (fixed order) -> g64 (p x m,
-// leading dim p); partial Gram matrices over the block ->
-// gram[blk][0|1|2][m*m] = G^T G, G^T X, X^T X.
-// G^T G, G^T X and X^T X of one row block held in LDS (gt, xt: rows x (m+1)),
-// R x R entries per thread; rows are added in order, as in the untiled loop.
-template <int R>
-__device__ __forceinline__ void gram_tiles(const double* gt, const double* xt, int mp, int nr,
-                                           int m, int with_x, int t, double* out) {
-    const int ta = t >> 4, tb = t & 15, mm = m * m;
-    int ia[R], ib[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-        ia[i] = (ta + 16 * i < m) ? ta + 16 * i : m - 1;
-        ib[i] = (tb + 16 * i < m) ? tb + 16 * i : m - 1;
-    }
-    double sgg[R][R], sgx[R][R], sxx[R][R];
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int k = 0; k < R; ++k) sgg[i][k] = sgx[i][k] = sxx[i][k] = 0.0;
-    for (int rr = 0; rr < nr; ++rr) {
-        const double* gr = gt + rr * mp;
-        const double* xr = xt + rr * mp;
-        double ga[R], gb[R], xa[R], xb[R];
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            ga[i] = gr[ia[i]];
-            gb[i] = gr[ib[i]];
-            xa[i] = xr[ia[i]];
-            xb[i] = xr[ib[i]];
+// G^T G, G^T X and X^T X (with_x; else zeros) of one row block held in LDS (gt,
+// xt: leading dim ld >= m, rows up to the next multiple of 16 past nr zero) on the
+// FP64 matrix cores: a wave takes 16 x 16 tiles of the products in turn, the upper
+// ones of the two symmetric products, 4 rows per v_mfma_f64_16x16x4_f64 (lane l:
+// row l / 16, components l % 16 of both sides; entry v of the result is component
+// 4 v + l / 16 against l % 16) in two alternating sums.  Components past m repeat
+// the last one and are not stored.  One thread per entry, walking the rows,
+// spent its time on the LDS reads of that chain.
+__device__ __forceinline__ void gram_products(const double* gt, const double* xt, int ld, int nr,
+                                              int m, bool with_x, double* __restrict__ out) {
+    using d4 = __attribute__((ext_vector_type(4))) double;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nwv = blockDim.x >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const int nt = (m + 15) / 16, up = nt * (nt + 1) / 2, mm = m * m;
+    const int ntask = with_x ? 2 * up + nt * nt : up;
+    for (int q = wv; q < ntask; q += nwv) {
+        const int which = q < up ? 0 : q < 2 * up ? 2 : 1;
+        int ti, tj;
+        if (which == 1) {
+            ti = (q - 2 * up) / nt;
+            tj = (q - 2 * up) % nt;
+        } else {
+            int u = which == 0 ? q : q - up;
+            ti = 0;
+            while (u >= nt - ti) u -= nt - ti++;
+            tj = ti + u;
         }
+        const int ca = 16 * ti + li < m ? 16 * ti + li : m - 1;
+        const int cb = 16 * tj + li < m ? 16 * tj + li : m - 1;
+        const double* a = (which == 2 ? xt : gt) + lk * ld + ca;
+        const double* b = (which == 0 ? gt : xt) + lk * ld + cb;
+        d4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
+        for (int r = 0; r < nr; r += 16) {
+            double av[4], bv[4];
 #pragma unroll
-        for (int i = 0; i < R; ++i)
-#pragma unroll
-            for (int k = 0; k < R; ++k) {
-                sgg[i][k] += ga[i] * gb[k];
-                sgx[i][k] += ga[i] * xb[k];
-                sxx[i][k] += xa[i] * xb[k];
+            for (int k = 0; k < 4; ++k) {
+                av[k] = a[(r + 4 * k) * ld];
+                bv[k] = b[(r + 4 * k) * ld];
             }
-    }
+            s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(av[0], bv[0], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(av[1], bv[1], s1, 0, 0, 0);
+            s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(av[2], bv[2], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(av[3], bv[3], s1, 0, 0, 0);
+        }
+        s0 += s1;
 #pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const int a = ta + 16 * i, b = tb + 16 * k;
-            if (a < m && b < m) {
-                const int e = a * m + b;
-                out[e] = sgg[i][k];
-                out[mm + e] = with_x == 1 ? sgx[i][k] : 0.0;
-                out[2 * mm + e] = with_x == 1 ? sxx[i][k] : 0.0;
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * ti + 4 * v + lk, j = 16 * tj + li;
+            if (i < m && j < m) {
+                out[which * mm + i * m + j] = s0[v];
+                if (which != 1 && ti != tj) out[which * mm + j * m + i] = s0[v];
             }
         }
+    }
+    if (!with_x)
+        for (int e = threadIdx.x; e < 2 * mm; e += blockDim.x) out[mm + e] = 0.0;
 }
 
+// The diagonal of G^T G only (a gamma path): S row slices per component, added
+// by a fixed-order tree.  red: 256 doubles; every thread of the workgroup calls.
+__device__ __forceinline__ void gram_diagonal(const double* gt, int ld, int nr, int m, double* red,
+                                              double* __restrict__ out) {
+    const int t = threadIdx.x;
+    int S = 1;
+    while (2 * S * m <= 256 && S < 64) S *= 2;
+    if (t < m * S) {
+        const int j = t % m;
+        double acc = 0.0;
+        for (int r = t / m; r < nr; r += S) acc += gt[r * ld + j] * gt[r * ld + j];
+        red[t] = acc;
+    }
+    __syncthreads();
+    for (int h = S / 2; h >= 1; h /= 2) {
+        if (t < m * h) red[t] += red[t + m * h];
+        __syncthreads();
+    }
+    if (t < m) out[t * m + t] = red[t];
+}
+
+// Row block r0..r0+nr: g_r = sum_y l1[y][.][r] (fixed order) -> g64 (p x m,
+// leading dim p); partial Gram matrices over the block ->
+// gram[blk][0|1|2][m*m] = G^T G, G^T X, X^T X.  Bound by the latency of its
+// loads: four elements of a thread are in flight together.  With one element at
+// a time and a thread per Gram entry it took 13.6 instead of 6.6 us at p = 1999,
+// m = 16 (5 splits) and 36 instead of 28 at p = 10000, m = 64.
 __global__ __launch_bounds__(256) void k_gram(const double* __restrict__ l1, int nsplit, int m,
                                               int ldx, int p, int rows, const float* __restrict__ X,
                                               int with_x, double* __restrict__ g64,
@@ -240,6 +271,8 @@ __global__ __launch_bounds__(256) void k_gram(const double* __restrict__ l1, int
                                               const Ctrl* __restrict__ ctrl) {
     if (ctrl && ctrl->done) return;
     extern __shared__ double sh[];
+    __shared__ double red[256];
+    constexpr int U = 4;
     const int mp = m + 1;
     double* gt = sh;                         // rows x (m+1)
     double* xt = sh + (size_t)rows * mp;     // rows x (m+1)
@@ -247,96 +280,55 @@ __global__ __launch_bounds__(256) void k_gram(const double* __restrict__ l1, int
     const int nr = (p - r0 < rows) ? p - r0 : rows;
     const int t = threadIdx.x;
     const size_t ne = (size_t)m * ldx;
-    for (int e = t; e < nr * m; e += blockDim.x) {
-        const int rr = e % nr, j = e / nr;
-        double s;
-        if (l1) {
-            // in order of y; the loads of 8 splits are issued together
-            const double* src = l1 + (size_t)j * ldx + r0 + rr;
-            s = 0.0;
-            int y = 0;
-            for (; y + 8 <= nsplit; y += 8) {
-                double v[8];
+    for (int e0 = t; e0 < nr * m; e0 += U * 256) {
+        double s[U];
+        float x[U];
+        int rr[U], j[U];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(y + u) * ne];
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + 256 * u < nr * m ? e0 + 256 * u : nr * m - 1;
+            rr[u] = e % nr;
+            j[u] = e / nr;
+            x[u] = (with_x == 1) ? X[(size_t)j[u] * ldx + r0 + rr[u]] : 0.f;
+        }
+        if (!l1 || nsplit == 1) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) s += v[u];
-            }
-            for (; y < nsplit; ++y) s += src[(size_t)y * ne];
-            g64[(size_t)j * p + r0 + rr] = s;
+            for (int u = 0; u < U; ++u)
+                s[u] = l1 ? l1[(size_t)j[u] * ldx + r0 + rr[u]]
+                          : g64[(size_t)j[u] * p + r0 + rr[u]];
         } else {
-            s = g64[(size_t)j * p + r0 + rr];
+            // in order of y, four splits at a time (past the end the last one is
+            // re-read and not added)
+#pragma unroll
+            for (int u = 0; u < U; ++u) s[u] = 0.0;
+            for (int y = 0; y < nsplit; y += 4) {
+                double v[U][4];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        v[u][k] = l1[(size_t)(y + k < nsplit ? y + k : nsplit - 1) * ne +
+                                     (size_t)j[u] * ldx + r0 + rr[u]];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (y + k < nsplit) s[u] += v[u][k];
+            }
         }
-        gt[rr * mp + j] = s;
-        xt[rr * mp + j] = (with_x == 1) ? (double)X[(size_t)j * ldx + r0 + rr] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (e0 + 256 * u < nr * m) {
+                if (l1) g64[(size_t)j[u] * p + r0 + rr[u]] = s[u];
+                gt[rr[u] * mp + j[u]] = s[u];
+                xt[rr[u] * mp + j[u]] = (double)x[u];
+            }
     }
+    for (int e = nr * mp + t; e < ((nr + 15) & ~15) * mp; e += 256) gt[e] = xt[e] = 0.0;
     __syncthreads();
-    const int mm = m * m;
-    double* out = gram + (size_t)blockIdx.x * 3 * mm;
-    // Few entries (small m, or the diagonal only on a gamma path): every entry
-    // is summed by S row slices in parallel, then a fixed-order tree adds the
-    // slices, instead of one thread walking all rows.
-    const int nent = (with_x == 2) ? m : 3 * mm;
-    if (nent <= 128) {
-        __shared__ double red[256];
-        int S = 1;
-        while (2 * S * nent <= (int)blockDim.x && S < 64) S *= 2;
-        if (t < nent * S) {
-            const int e = t % nent, sl = t / nent;
-            double acc = 0.0;
-            if (with_x == 2) {
-                for (int rr = sl; rr < nr; rr += S) acc += gt[rr * mp + e] * gt[rr * mp + e];
-            } else {
-                const int which = e / mm, ab = e % mm, a = ab / m, b = ab % m;
-                const double* u = which == 2 ? xt : gt;
-                const double* w = which == 0 ? gt : xt;
-                if (which == 0 || with_x == 1)
-                    for (int rr = sl; rr < nr; rr += S) acc += u[rr * mp + a] * w[rr * mp + b];
-            }
-            red[sl * nent + e] = acc;
-        }
-        __syncthreads();
-        for (int h = S / 2; h >= 1; h /= 2) {
-            if (t < nent * h) red[t] += red[t + h * nent];
-            __syncthreads();
-        }
-        if (t < nent) {
-            if (with_x == 2) out[t * m + t] = red[t];
-            else out[t] = red[t];
-        }
-        return;
-    }
-    if (with_x == 2) {  // independent columns (gamma path): only ||g_j||^2 is needed
-        for (int a = t; a < m; a += blockDim.x) {
-            double sgg = 0.0;
-            for (int rr = 0; rr < nr; ++rr) sgg += gt[rr * mp + a] * gt[rr * mp + a];
-            out[a * m + a] = sgg;
-        }
-        return;
-    }
-    if (m > 16 && blockDim.x == 256) {
-        // register tiles: thread (ta, tb) of a 16 x 16 grid owns entries
-        // (ta + 16 i, tb + 16 k), i, k < R, of the three products, so a row
-        // costs 4R LDS reads for 3 R^2 multiply-adds
-        if (m <= 32) gram_tiles<2>(gt, xt, mp, nr, m, with_x, t, out);
-        else gram_tiles<4>(gt, xt, mp, nr, m, with_x, t, out);
-        return;
-    }
-    for (int e = t; e < mm; e += blockDim.x) {
-        const int a = e / m, b = e % m;
-        double sgg = 0.0, sgx = 0.0, sxx = 0.0;
-        for (int rr = 0; rr < nr; ++rr) {
-            const double ga = gt[rr * mp + a];
-            sgg += ga * gt[rr * mp + b];
-            if (with_x == 1) {
-                sgx += ga * xt[rr * mp + b];
-                sxx += xt[rr * mp + a] * xt[rr * mp + b];
-            }
-        }
-        out[e] = sgg;
-        out[mm + e] = sgx;
-        out[2 * mm + e] = sxx;
-    }
+    double* out = gram + (size_t)blockIdx.x * 3 * m * m;
+    if (with_x == 2) gram_diagonal(gt, mp, nr, m, red, out);
+    else gram_products(gt, xt, mp, nr, m, with_x == 1, out);
 }
 
 hipError_t launch_gram(const Plan& pl, const double* l1, int nsplit, const float* X, int with_x,
@@ -451,12 +443,16 @@ hipError_t launch_gram_sum(const Plan& pl, int nent, int ngram, const double* gr
 
 // ---------------------------------------------------------------------------
 // Fused partial reduction + Gram for m <= 16: one workgroup per 64 rows.
-// Thread (row rr, slice sl) sums the partials c = sl, sl+4, ... of its row for
-// every component, the four slices are added in order 0..3 (fixed order), the
-// row of G is written in FP64, and the block's contributions to G^T G, G^T X,
-// X^T X (or only the diagonal of G^T G, with_x == 2) go to gram[block].
-template <int MB>
-__global__ __launch_bounds__(256) void k_reduce_gram(const float* __restrict__ gpart,
+// Thread (row rr, slice sl) sums the partials c = sl, sl + NSL, ... of its row for
+// every component, the slices are added in order (fixed order), the row of G is
+// written in FP64, and the block's contributions to G^T G, G^T X, X^T X (or only
+// the diagonal of G^T G, with_x == 2) go to gram[block].  Bound by the latency of
+// the partials' loads, 4 partials per thread in flight: few row blocks take a
+// workgroup per CU with 16 slices (8 for m > 8, whose sums fill the LDS).  4 slices
+// and a thread per Gram entry took 8.0 instead of 5.5 us at p = 800, n = 8000, m = 5
+// and 9.9 instead of 6.5 at 10000 x 100000, m = 8.
+template <int MB, int NSL>
+__global__ __launch_bounds__(64 * NSL) void k_reduce_gram(const float* __restrict__ gpart,
                                                      const int* __restrict__ touched, int npart,
                                                      int m, int ldx, int p,
                                                      const float* __restrict__ X, int with_x,
@@ -464,12 +460,13 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const float* __restrict__ g
                                                      double* __restrict__ gram,
                                                      const Ctrl* __restrict__ ctrl) {
     if (ctrl->done) return;
-    constexpr int MP = MB + 1;
-    __shared__ double part[4][64][MP];
-    __shared__ double gt[64][MP];
-    __shared__ double xt[64][MP];
+    constexpr int MP = MB + 1, T = 64 * NSL;
+    extern __shared__ double sh[];
+    double* const part = sh;                    // NSL x 64 x MP
+    double* const gt = sh + NSL * 64 * MP;      // 64 x MP
+    double* const xt = gt + 64 * MP;
     __shared__ int plist[1024];
-    __shared__ int wcnt[4];
+    __shared__ int wcnt[NSL];
     const int t = threadIdx.x, rr = t & 63, sl = t >> 6;
     const int r0 = blockIdx.x * 64;
     const int r = r0 + rr;
@@ -478,17 +475,20 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const float* __restrict__ g
     // ascending list of the partials that hold data (all of them without flags),
     // built in parallel so that the sums below never wait on a flag
     int nlist = 0;
-    for (int c0 = 0; c0 < npart; c0 += 256) {
+    for (int c0 = 0; c0 < npart; c0 += T) {
         const int c = c0 + t;
         const bool on = c < npart && (!touched || touched[c] != 0);
         const uint64_t bal = __ballot(on);
-        if ((t & 63) == 0) wcnt[sl] = __popcll(bal);
+        if (rr == 0) wcnt[sl] = __popcll(bal);
         __syncthreads();
         int before = nlist;
-        for (int w = 0; w < sl; ++w) before += wcnt[w];
-        if (on && before + __popcll(bal & ((1ull << (t & 63)) - 1ull)) < 1024)
-            plist[before + __popcll(bal & ((1ull << (t & 63)) - 1ull))] = c;
-        nlist += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+#pragma unroll
+        for (int w = 0; w < NSL; ++w) {
+            before += w < sl ? wcnt[w] : 0;
+            nlist += wcnt[w];
+        }
+        const int at = before + __popcll(bal & ((1ull << rr) - 1ull));
+        if (on && at < 1024) plist[at] = c;
         __syncthreads();
     }
     double g[MB];
@@ -501,31 +501,25 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const float* __restrict__ g
 #pragma unroll
     for (int j = 0; j < MB; ++j) joff[j] = (size_t)(j < m ? j : m - 1) * ldx + r;
     if (r < p && nlist <= 1024) {
-        int e = sl;
-        for (; e + 12 < nlist; e += 16) {
+        for (int e = sl; e < nlist; e += 4 * NSL) {
             float v[4][MB];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float* src = gpart + (size_t)plist[e + 4 * u] * stride;
+                const int eu = e + u * NSL < nlist ? e + u * NSL : nlist - 1;
+                const float* src = gpart + (size_t)plist[eu] * stride;
 #pragma unroll
                 for (int j = 0; j < MB; ++j) v[u][j] = src[joff[j]];
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
+                if (e + u * NSL < nlist) {
 #pragma unroll
-                for (int j = 0; j < MB; ++j) g[j] += (j < m) ? (double)v[u][j] : 0.0;
-        }
-        for (; e < nlist; e += 4) {
-            float v[MB];
-            const float* src = gpart + (size_t)plist[e] * stride;
-#pragma unroll
-            for (int j = 0; j < MB; ++j) v[j] = src[joff[j]];
-#pragma unroll
-            for (int j = 0; j < MB; ++j) g[j] += (j < m) ? (double)v[j] : 0.0;
+                    for (int j = 0; j < MB; ++j) g[j] += (j < m) ? (double)v[u][j] : 0.0;
+                }
         }
     } else if (r < p) {
         // more than 1024 partials: walk the flags directly
-        for (int c = sl; c < npart; c += 4) {
+        for (int c = sl; c < npart; c += NSL) {
             if (touched && !touched[c]) continue;
             float v[MB];
             const float* src = gpart + (size_t)c * stride;
@@ -536,53 +530,44 @@ __global__ __launch_bounds__(256) void k_reduce_gram(const float* __restrict__ g
         }
     }
 #pragma unroll
-    for (int j = 0; j < MB; ++j) part[sl][rr][j] = g[j];
+    for (int j = 0; j < MB; ++j) part[(sl * 64 + rr) * MP + j] = g[j];
     __syncthreads();
-    if (sl == 0) {
+    for (int j = sl; j < MB; j += NSL) {
+        double v = 0.0;
 #pragma unroll
-        for (int j = 0; j < MB; ++j) {
-            const double v = ((part[0][rr][j] + part[1][rr][j]) + part[2][rr][j]) + part[3][rr][j];
-            gt[rr][j] = v;
-            if (r < p && j < m) g64[(size_t)j * p + r] = v;
-            xt[rr][j] = (with_x == 1 && r < p && j < m) ? (double)X[(size_t)j * ldx + r] : 0.0;
-        }
+        for (int w = 0; w < NSL; ++w) v += part[(w * 64 + rr) * MP + j];
+        gt[rr * MP + j] = v;
+        if (r < p && j < m) g64[(size_t)j * p + r] = v;
+        xt[rr * MP + j] = (with_x == 1 && r < p && j < m) ? (double)X[(size_t)j * ldx + r] : 0.0;
     }
     __syncthreads();
-    const int mm = m * m;
-    double* out = gram + (size_t)blockIdx.x * 3 * mm;
-    if (with_x == 2) {
-        for (int a = t; a < m; a += 256) {
-            double sgg = 0.0;
-            for (int k = 0; k < nr; ++k) sgg += gt[k][a] * gt[k][a];
-            out[a * m + a] = sgg;
-        }
-        return;
-    }
-    for (int e = t; e < 3 * mm; e += 256) {
-        const int which = e / mm, ab = e % mm, a = ab / m, b = ab % m;
-        double s2 = 0.0;
-        if (which == 0)
-            for (int k = 0; k < nr; ++k) s2 += gt[k][a] * gt[k][b];
-        else if (which == 1)
-            for (int k = 0; k < nr; ++k) s2 += gt[k][a] * xt[k][b];
-        else
-            for (int k = 0; k < nr; ++k) s2 += xt[k][a] * xt[k][b];
-        out[e] = s2;
-    }
+    double* out = gram + (size_t)blockIdx.x * 3 * m * m;
+    if (with_x == 2) gram_diagonal(gt, MP, nr, m, part, out);
+    else gram_products(gt, xt, MP, nr, m, with_x == 1, out);
+}
+
+template <int MB, int NSL>
+static void launch_reduce_gram_t(const Plan& pl, const float* gpart, const int* touched,
+                                 const float* X, int with_x, double* g64, double* gram,
+                                 const Ctrl* ctrl, hipStream_t st) {
+    static const bool lds_once = (set_lds_limit((const void*)k_reduce_gram<MB, NSL>), true);
+    (void)lds_once;
+    hipLaunchKernelGGL((k_reduce_gram<MB, NSL>), dim3((unsigned)((pl.p + 63) / 64)),
+                       dim3(64 * NSL), sizeof(double) * (NSL + 2) * 64 * (MB + 1), st, gpart,
+                       touched, pl.npart, pl.m, pl.ldx, (int)pl.p, X, with_x, g64, gram, ctrl);
 }
 
 hipError_t launch_reduce_gram(const Plan& pl, const float* gpart, const int* touched,
                               const float* X, int with_x, double* g64, double* gram,
                               const Ctrl* ctrl, hipStream_t st) {
-    const int grid = (int)((pl.p + 63) / 64);
-#define GPSPCA_RG(MB)                                                                        \
-    hipLaunchKernelGGL(k_reduce_gram<MB>, dim3(grid), dim3(256), 0, st, gpart, touched,     \
-                       pl.npart, pl.m, pl.ldx, (int)pl.p, X, with_x, g64, gram, ctrl)
-    if (pl.m <= 1) GPSPCA_RG(1);
-    else if (pl.m <= 2) GPSPCA_RG(2);
-    else if (pl.m <= 4) GPSPCA_RG(4);
-    else if (pl.m <= 8) GPSPCA_RG(8);
-    else GPSPCA_RG(16);
+    // up to 256 row blocks there is a CU for each
+    const bool wide = pl.p <= 64 * 256;
+#define GPSPCA_RG(MB, NSL)                                                                          (wide ? launch_reduce_gram_t<MB, NSL>(pl, gpart, touched, X, with_x, g64, gram, ctrl, st)            : launch_reduce_gram_t<MB, 4>(pl, gpart, touched, X, with_x, g64, gram, ctrl, st))
+    if (pl.m <= 1) GPSPCA_RG(1, 16);
+    else if (pl.m <= 2) GPSPCA_RG(2, 16);
+    else if (pl.m <= 4) GPSPCA_RG(4, 16);
+    else if (pl.m <= 8) GPSPCA_RG(8, 16);
+    else GPSPCA_RG(16, 8);
 #undef GPSPCA_RG
     return hipGetLastError();
 }

@@ -314,3 +314,30 @@ def test_start_columns_selection(gpu, n, m, order):
     res = gpu.solve_multistart(to_device(A), gpu.SL1, m, 0.01, tol=0.0, max_iter=1)
     got = ((res.X.cpu().numpy() > 0) * (1 << np.arange(bits))[:, None]).sum(axis=0)
     np.testing.assert_array_equal(got, np.argsort(-level.astype(np.float64), kind="stable")[:m])
+
+
+@pytest.mark.parametrize("p,n,m", [(17, 200, 2), (65, 1500, 4), (79, 600, 9), (129, 3000, 16),
+                                   (16384, 150, 5), (16385, 150, 5), (16400, 150, 12),
+                                   (200, 2000, 17), (113, 700, 64), (33000, 130, 20)])
+@pytest.mark.parametrize("path", [False, True], ids=["block", "path"])
+def test_gram_row_blocks(gpu, p, n, m, path, monkeypatch):
+    """The Gram products of a pass by row blocks: remainders of 64 rows and of 16,
+    both slicings of the partial sums, one to four component tiles; the diagonal
+    alone on a gamma path.  Rounding of FP32 operands, as in the block solves above."""
+    monkeypatch.setenv("GPSPCA_SMALL", "0")
+    A32 = W.planted_block(p, n, min(m, 8), 90 + m, k=20)[0]
+    A64 = A32.astype(np.float64)
+    X0 = fp32_round(O.init(A64, m)[0])
+    gamma = W.gamma_absolute(A64, False, 0.05)
+    if path:
+        g = [gamma * (1.0 + 0.01 * j) for j in range(m)]
+        res = gpu.solve_path(to_device(A32), gpu.SL1, g, X0=x_to_device(X0), tol=0.0, max_iter=3)
+        X = res.X.cpu().numpy()
+        for j in range(m):
+            ref = O.solve(A64, O.SL1, 1, g[j], X0=X0[:, [j]], tol=0.0, max_iter=3)
+            assert rel(X[:, [j]], ref["X"]) <= 1e-5
+    else:
+        ref = O.solve(A64, O.BL1, m, gamma, X0=X0, tol=0.0, max_iter=3)
+        res = gpu.solve(to_device(A32), gpu.BL1, m, gamma, X0=x_to_device(X0), tol=0.0, max_iter=3)
+        assert rel(res.X.cpu().numpy(), ref["X"]) <= 1e-5
+        np.testing.assert_allclose(res.trace, ref["trace"], rtol=1e-5)
