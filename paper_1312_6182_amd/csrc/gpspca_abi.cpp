@@ -166,14 +166,17 @@ static Tune env_tune() {
 }
 
 // Active fraction (in 1/1024) of the n columns from which a pass is
-// back-projected densely on the matrix cores.  The support-restricted kernel
-// reads each active column once per group of 16 components; the dense one
-// reads every column once for all components.  The thresholds are the measured
-// crossovers on a 10000 x 100000 matrix (gamma paths and block solves with
-// 16 to 64 components at 2% to 55% activity), per storage type and number of
-// component groups (1, 2, 3, 4); for FP32 they are near 0.40, 0.22, 0.19 and
-// 0.18.  Frozen-support passes visit only listed columns and leave S of the
-// others unwritten, so they stay sparse.
+// back-projected on the matrix cores.  Both forms read the active columns only,
+// the vector-ALU one once per group of 16 components; the matrix-core one reads
+// them once for all, but needs its list first and, with m > 16, a launch of its
+// own.  Measured as whole 6-pass solves of m starts (vector / matrix, in time;
+// 10000 x 100000, 2000 x 20000 and 600 x 6000, every storage type):
+//   m 8      0.92-1.02 up to 1.8% active, 1.00-1.12 at 7-12%, 1.05-1.5 at all
+//   m 16     0.95-1.03 up to 2%, 1.01-1.1 at 3%, 1.07-1.6 at 14-22%, 1.5-2.4 at all
+//   m 32     0.91-1.03 up to 1%, 0.96-1.3 at 4-7%, 1.1-2.4 at 27-40%, 1.3-3.2 at all
+//   m 64     0.90-1.08 up to 2%, 1.05-1.7 at 13%, 1.4-3.1 at 63%, 1.6-3.6 at all
+// Frozen-support passes visit only listed columns and leave S of the
+// others unwritten, so they take the vector-ALU form.
 static int backproj_threshold(const gpspca_matrix* A, int m, int vec4, int restricted) {
     const int never = 2 * 1024;
     if (restricted || m <= 4 || A->p < 64 || (A->dtype == GPSPCA_F32 && !vec4)) return never;
@@ -183,12 +186,7 @@ static int backproj_threshold(const gpspca_matrix* A, int m, int vec4, int restr
         if (v == "sparse") return never;
         if (!v.empty() && v != "auto") return std::max(0, std::min(never, std::atoi(e)));
     }
-    static const int thr[3][4] = {{410, 225, 195, 185},    // FP32
-                                  {185, 125, 110, 100},    // bfloat16
-                                  {195, 135, 125, 120}};   // e4m3
-    const int st = A->dtype == GPSPCA_BF16 ? 1 : A->dtype == GPSPCA_F8E4M3 ? 2 : 0;
-    const int groups = std::min(4, (m + 15) / 16);
-    return thr[st][groups - 1];
+    return m <= 8 ? 60 : m <= 16 ? 30 : 50;
 }
 
 // Whether k_corr_sh is the default correlation.  Its eight-wave workgroups pay

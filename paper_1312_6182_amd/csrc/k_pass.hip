@@ -20,11 +20,12 @@
 //  k_backproj  block forms: G partials = sum over ACTIVE columns only of
 //              a_i (mu * s_i)^T, so a sparse support costs a small fraction of a
 //              second pass; workgroups own a (row block, column range) tile.
-//              When enough of the pass's columns are active it instead runs
-//              the dense form: every column of each range with an active
-//              column, on the matrix cores (bpm_block), every component group
-//              in one read of A.
+//              When enough of the pass's columns are active it runs on the
+//              matrix cores (bpm_range), every component group in one read of
+//              the active columns.
 //  k_colnorm   ||a_i|| in FP64 (default start).
+#include <algorithm>
+
 #include "gpspca_internal.h"
 #include "storage.h"
 
@@ -511,59 +512,40 @@ __global__ __launch_bounds__(T) void k_corr_vx(PassParams pp, const float* __res
 }
 
 // ---------------------------------------------------------------------------
-// Dense or sparse back-projection.  The pass is back-projected densely iff at
-// least thr/1024 of all n columns are active (the correlation kernels count
-// them into *pp.nact): then every column range with an active column is taken
-// by the dense form of k_backproj, and the others (nothing to add) by its
-// sparse form.  One decision for the whole pass: a dense range costs a full
-// read of its columns by a few waves, so a pass with only some dense ranges
-// would wait on them.  thr > kBpThrMax: never.
+// Vector-ALU or matrix-core back-projection.  A pass takes the matrix cores iff
+// at least thr/1024 of all n columns are active (the correlation kernels count
+// them into *pp.nact), in every column range: one decision for the whole
+// pass, so that its ranges take about the same time.  thr > kBpThrMax: never.
 // ---------------------------------------------------------------------------
 constexpr int kBpThrMax = 1024;
 
-__device__ __forceinline__ bool pass_is_dense(const PassParams& pp, int thr) {
+__device__ __forceinline__ bool pass_on_mc(const PassParams& pp, int thr) {
     if (thr > kBpThrMax || !pp.nact) return false;
     const int64_t na = *pp.nact;
     return na > 0 && na * kBpThrMax >= (int64_t)thr * pp.n;
 }
 
-// This thread's share of the active columns of [cb, ce) (flags are 0 or 1),
-// read as aligned 32-bit words of the flag array, whose allocation is padded
-// to 256 bytes; bytes outside the range are masked off.
-__device__ __forceinline__ int count_active(const uint8_t* __restrict__ act, int64_t cb,
-                                            int64_t ce, int tid, int nthreads) {
-    const uint32_t* aw = reinterpret_cast<const uint32_t*>(act);
-    const int64_t w0 = cb >> 2, w1 = (ce + 3) >> 2;
-    int c = 0;
-#pragma unroll 4
-    for (int64_t w = w0 + tid; w < w1; w += nthreads) {
-        uint32_t v = aw[w];
-        const int64_t lo = cb - 4 * w, hi = 4 * w + 4 - ce;
-        if (lo > 0) v &= 0xFFFFFFFFu << (8 * lo);
-        if (hi > 0) v &= 0xFFFFFFFFu >> (8 * hi);
-        c += __popc(v);
-    }
-    return c;
-}
-
-
 // ---------------------------------------------------------------------------
-// bpm_block: dense G partial of column range cr = A[:, cb:ce] W[cb:ce, :],
-// W_ij = mu_j s_ij scale_i, over every column of the range, on the matrix
-// cores (v_mfma_f32_16x16x4_f32: 16 rows x 16 components, contraction over 4
-// columns).
-//   grid (row blocks of 64 RL rows, four per workgroup; column ranges); every
-//   component group (G of 16) in the same read of A.
+// Matrix-core form: G partial of a column range cb:ce, A[:, L] W[L, :] over the
+// list L of its active columns, W_ij = mu_j s_ij scale_i, with
+// v_mfma_f32_16x16x4_f32 (16 rows x 16 components, contraction over 4 columns).
+//   grid (row blocks of 64 RL rows, four per workgroup, one per wave; column
+//   ranges); every component group (G of 16) in the same read of A.
 //   Lane (li, lk) = (l % 16, l / 16) loads quad q0 + li + 16 r (r < RL) of
-//   column c + lk; that one load feeds the four tiles (r, e), whose operand row
-//   li is data row 4 (q0 + li + 16 r) + e, against the weight of column
-//   c + lk, component 16 g + li.  Accumulator register v of tile (r, e) then
+//   column L[4 step + lk]; that one load feeds the four tiles (r, e), whose operand
+//   row li is data row 4 (q0 + li + 16 r) + e, against the weight of that column,
+//   component 16 g + li.  Accumulator register v of tile (r, e) then
 //   holds data row 4 (q0 + 16 r + 4 lk + v) + e, so each lane stores whole
 //   quads.
 //   Steps of 4 columns are software-pipelined D deep with compile-time buffer
-//   indices.  Columns past the range are clamped and weighted 0; quads past
-//   the last full one are clamped and replaced by the ragged rows or zeros
-//   (TAIL, the last row block only), so no load is conditional.
+//   indices.  List entries past the end repeat the last one and are weighted 0;
+//   quads past the last full one are clamped and replaced by the ragged rows or
+//   zeros (TAIL, the last row block only), so no load is conditional.
+// The list is what the four waves of a workgroup share (LDS, kBpList columns of the
+// range at a time).  Reading every column of the range, with weight 0 for the
+// inactive ones, it took 850 instead of 296 us at 10000 x 100000, m = 32 with 35%
+// active (FP32), and with two row blocks per wave 40 instead of 21 us at 2003 x 20021, m = 16
+// with 27% active (bfloat16).
 // ---------------------------------------------------------------------------
 // Raw (undecoded) storage of one full quad, and its decoding; the tail quad
 // is kept as four raw elements.
@@ -621,14 +603,19 @@ __device__ __forceinline__ float decode_elem(uint32_t w) {
     else return e4m3_value(w);
 }
 
+constexpr int kBpList = 2048;   // columns of a list
+// pipeline depth, in steps of 4 columns: what the registers hold
+template <int G, int ST> constexpr int kBpDepth = (G == 1 || (G == 4 && ST == kStF32)) ? 4 : 3;
+
+// acc += A[:, L] W[L, :], L = base + list[0 .. total), total > 0.
 template <int RL, int G, int D, bool TAIL, int ST>
-__device__ __forceinline__ void bpm_block(const PassParams& pp, int64_t cb, int64_t ce, int q0,
-                                          const float* __restrict__ S,
-                                          float* __restrict__ gp) {
+__device__ __forceinline__ void bpm_chunk(const PassParams& pp, int64_t base,
+                                          const uint16_t* list, int total, int q0,
+                                          const float* __restrict__ S, f4 (&acc)[RL][4][G]) {
     using RawT = typename QuadRaw<ST>::T;
     const int lane = threadIdx.x & 63;
     const int li = lane & 15, lk = lane >> 4;
-    const int p = pp.p, m = pp.m, nqf = p >> 2, nq = (p + 3) >> 2;
+    const int p = pp.p, m = pp.m, nqf = p >> 2;
     float mul[G];
     int comp[G];
 #pragma unroll
@@ -658,9 +645,9 @@ __device__ __forceinline__ void bpm_block(const PassParams& pp, int64_t cb, int6
         float s[G];
         float sc;
     };
-    auto load = [&](int64_t step, Buf& b) {
-        const int64_t c = cb + 4 * step + lk;
-        const int64_t cc = (c < ce) ? c : ce - 1;
+    auto load = [&](int step, Buf& b) {
+        const int k = 4 * step + lk;
+        const int64_t cc = base + list[k < total ? k : total - 1];
         const void* colv = column_ptr<ST>(pp, cc);
 #pragma unroll
         for (int r = 0; r < RL; ++r) b.a[r] = load_quad_raw<ST>(colv, qa[r]);
@@ -672,31 +659,23 @@ __device__ __forceinline__ void bpm_block(const PassParams& pp, int64_t cb, int6
         for (int g = 0; g < G; ++g) b.s[g] = S[cc * m + comp[g]];
         if constexpr (ST != kStF32) b.sc = column_scale(pp, cc);
     };
-    f4 acc[RL][4][G];
-#pragma unroll
-    for (int r = 0; r < RL; ++r)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int g = 0; g < G; ++g) acc[r][e][g] = zero4();
-
-    const int64_t nstep = (ce - cb + 3) / 4;
+    const int nstep = (total + 3) / 4;
     Buf buf[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) load(d, buf[d]);
     __builtin_amdgcn_sched_barrier(0);
-    // steps past the last one are clamped loads with zero weights
-    for (int64_t s0 = 0; s0 < nstep; s0 += D) {
+    // steps past the last one are repeated loads with zero weights
+    for (int s0 = 0; s0 < nstep; s0 += D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const Buf& b = buf[d];
-            const float valid = (cb + 4 * (s0 + d) + lk < ce) ? 1.f : 0.f;
+            const bool valid = 4 * (s0 + d) + lk < total;
             float w[G];
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float wv = mul[g] * b.s[g];
                 if constexpr (ST != kStF32) wv *= b.sc;
-                w[g] = wv * valid;
+                w[g] = valid ? wv : 0.f;
             }
             f4 a[RL];
 #pragma unroll
@@ -723,7 +702,65 @@ __device__ __forceinline__ void bpm_block(const PassParams& pp, int64_t cb, int6
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+}
 
+// The matrix-core form by a workgroup of four waves, of which wave wv takes the row
+// block at quad q0 (none when that is past the last quad).  True when the range
+// has an active column; the partial is written only then.
+template <int RL, int G, int ST>
+__device__ __forceinline__ bool bpm_range(const PassParams& pp, int64_t cb, int64_t ce, int q0,
+                                          const float* __restrict__ S,
+                                          const uint8_t* __restrict__ act,
+                                          float* __restrict__ gp) {
+    constexpr int D = kBpDepth<G, ST>, NB = kBpList / 256;
+    __shared__ uint16_t list[kBpList];
+    __shared__ int cnt[NB * 4];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const int m = pp.m, nqf = pp.p >> 2, nq = (pp.p + 3) >> 2;
+    f4 acc[RL][4][G];
+#pragma unroll
+    for (int r = 0; r < RL; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[r][e][g] = zero4();
+    bool any = false;
+    for (int64_t base = cb; base < ce; base += kBpList) {
+        // ascending list: every flag of the chunk is loaded at once
+        bool on[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int64_t i = base + t + 256 * u;
+            on[u] = act[i < ce ? i : ce - 1] != 0 && i < ce;
+        }
+        uint64_t bal[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            bal[u] = __ballot(on[u]);
+            if (lane == 0) cnt[4 * u + wv] = __popcll(bal[u]);
+        }
+        __syncthreads();
+        int total = 0;
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if (w == wv && on[u])
+                    list[total + __popcll(bal[u] & ((1ull << lane) - 1ull))] = t + 256 * u;
+                total += cnt[4 * u + w];
+            }
+        __syncthreads();
+        any = any || total > 0;
+        if (total > 0 && q0 < nq) {
+            if (q0 + 16 * RL > nqf)
+                bpm_chunk<RL, G, D, true, ST>(pp, base, list, total, q0, S, acc);
+            else
+                bpm_chunk<RL, G, D, false, ST>(pp, base, list, total, q0, S, acc);
+        }
+        if (base + kBpList < ce) __syncthreads();   // before the list is rewritten
+    }
+    if (!any) return false;
 #pragma unroll
     for (int r = 0; r < RL; ++r)
 #pragma unroll
@@ -739,17 +776,17 @@ __device__ __forceinline__ void bpm_block(const PassParams& pp, int64_t cb, int6
                 }
             }
         }
+    return true;
 }
 
 // ---------------------------------------------------------------------------
 // k_backproj: G partial of column range cr.
 //   grid (row blocks, column ranges); 256 threads.
-//   Sparse pass: thread t owns quads qbase + t + 256 k (k < KQ2) of the row
+//   Vector-ALU form: thread t owns quads qbase + t + 256 k (k < KQ2) of the row
 //   block and adds the active columns, U per step, for components j0 .. j0+M-1.
-//   Dense pass, G = 1 (m <= 16): the workgroup's four waves take row blocks of
-//   256 rows in turn and run bpm_block over every column of a range that has
-//   an active column.  One launch serves both, so a sparse pass pays no launch
-//   for the dense code.  (m > 16: k_backproj_dense, below.)
+//   Matrix-core form, G = 1 (m <= 16): each of the workgroup's four waves takes
+//   one row block of 256 rows.  One launch serves both, so a pass pays no launch
+//   for the other form.  (m > 16: k_backproj_mc, below.)
 // ---------------------------------------------------------------------------
 template <int M, int KQ2, bool VEC, int ST, int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_backproj(
@@ -772,34 +809,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int qbase = blockIdx.x * 256 * KQ2;
     const int cr = blockIdx.y;
     const int64_t cb = pp.n * cr / ncr, ce = pp.n * (cr + 1) / ncr;
-    if (pass_is_dense(pp, thr)) {
-        // dense pass: ranges with an active column are read in full
-        int c = count_active(act, cb, ce, t, 256);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-        if (lane == 0) wcount[wv] = c;
-        __syncthreads();
-        const int64_t total = (int64_t)wcount[0] + wcount[1] + wcount[2] + wcount[3];
-        if (total > 0) {
-            if constexpr (G > 0) {
-                if (j0 == 0) {
-                    constexpr int RL = G <= 2 ? 4 : 2;
-                    const int nrb = (nq + 16 * RL - 1) / (16 * RL);
-                    float* gp = gpart + (size_t)cr * m * pp.ldx;
-                    for (int rb = blockIdx.x * 4 + wv; rb < nrb; rb += 4 * gridDim.x) {
-                        const int q0 = rb * 16 * RL;
-                        if (q0 + 16 * RL > nqf)
-                            bpm_block<RL, G, 3, true, ST>(pp, cb, ce, q0, S, gp);
-                        else
-                            bpm_block<RL, G, 3, false, ST>(pp, cb, ce, q0, S, gp);
-                    }
-                    if (blockIdx.x == 0 && t == 0) touched[cr] = 1;
-                }
-            }
-            return;
+    if (pass_on_mc(pp, thr)) {
+        // matrix-core form; with m > 16 it is a launch of its own
+        if constexpr (G > 0) {
+            constexpr int RL = 4;
+            const int q0 = (blockIdx.x * 4 + wv) * 16 * RL;
+            const bool on = bpm_range<RL, G, ST>(pp, cb, ce, q0, S, act,
+                                                 gpart + (size_t)cr * m * pp.ldx);
+            if (blockIdx.x == 0 && t == 0) touched[cr] = on ? 1 : 0;
         }
-        __syncthreads();
+        return;
     }
+    if (qbase >= nq) return;   // the grid also covers the row blocks of the other form
 
     f4 g[KQ2][M];
 #pragma unroll
@@ -1138,34 +1159,25 @@ hipError_t launch_corr_vx(const Plan& pl, const PassParams& pp, const float* X, 
     }
 }
 
-// Dense pass with more than one component group (m > 16): a launch of its
-// own (merged into k_backproj, the dense code would spill registers); four
+// Matrix-core form with more than one component group (m > 16): a launch of its
+// own (merged into k_backproj, the code would spill registers); four
 // waves per workgroup, each with its own row block.
 template <int RL, int G, int ST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_backproj_dense(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_backproj_mc(
     PassParams pp, const float* __restrict__ S, const uint8_t* __restrict__ act,
     float* __restrict__ gpart, int* __restrict__ touched, int ncr, int thr,
     const Ctrl* __restrict__ ctrl) {
-    if (ctrl->done || !pass_is_dense(pp, thr)) return;
-    const int lane = threadIdx.x & 63;
+    if (ctrl->done || !pass_on_mc(pp, thr)) return;
     const int q0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 16 * RL;
-    if (q0 >= ((pp.p + 3) >> 2)) return;   // past the last row block (whole wave)
     const int cr = blockIdx.y;
     const int64_t cb = pp.n * cr / ncr, ce = pp.n * (cr + 1) / ncr;
-    int c = count_active(act, cb, ce, lane, 64);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-    if (c == 0) return;
-    float* gp = gpart + (size_t)cr * pp.m * pp.ldx;
-    if (q0 + 16 * RL > (pp.p >> 2))
-        bpm_block<RL, G, 3, true, ST>(pp, cb, ce, q0, S, gp);
-    else
-        bpm_block<RL, G, 3, false, ST>(pp, cb, ce, q0, S, gp);
-    if (blockIdx.x == 0 && threadIdx.x == 0) touched[cr] = 1;
+    const bool on = bpm_range<RL, G, ST>(pp, cb, ce, q0, S, act,
+                                         gpart + (size_t)cr * pp.m * pp.ldx);
+    if (blockIdx.x == 0 && threadIdx.x == 0) touched[cr] = on ? 1 : 0;
 }
 
 template <int ST>
-static hipError_t launch_bp_dense(const Plan& pl, const PassParams& pp, const float* S,
+static hipError_t launch_bp_mc(const Plan& pl, const PassParams& pp, const float* S,
                                   const uint8_t* act, float* gpart, int* touched,
                                   const Ctrl* ctrl, hipStream_t st) {
     const int nq = (int)((pl.p + 3) / 4);
@@ -1173,10 +1185,10 @@ static hipError_t launch_bp_dense(const Plan& pl, const PassParams& pp, const fl
     const int nrb = (nq + qb - 1) / qb;
     const dim3 grid((unsigned)((nrb + 3) / 4), pl.bp_cr), block(256);
     if (pl.m <= 32)
-        hipLaunchKernelGGL((k_backproj_dense<4, 2, ST>), grid, block, 0, st, pp, S, act, gpart,
+        hipLaunchKernelGGL((k_backproj_mc<4, 2, ST>), grid, block, 0, st, pp, S, act, gpart,
                            touched, pl.bp_cr, pl.bp_thr, ctrl);
     else
-        hipLaunchKernelGGL((k_backproj_dense<2, 4, ST>), grid, block, 0, st, pp, S, act, gpart,
+        hipLaunchKernelGGL((k_backproj_mc<2, 4, ST>), grid, block, 0, st, pp, S, act, gpart,
                            touched, pl.bp_cr, pl.bp_thr, ctrl);
     return hipGetLastError();
 }
@@ -1186,13 +1198,16 @@ template <int M, bool VEC, int ST, int G>
 static hipError_t launch_bp_t(const Plan& pl, const PassParams& pp, int j0, const float* S,
                               const uint8_t* act, float* gpart, int* touched, const Ctrl* ctrl,
                               hipStream_t st, int ng = 1) {
-    hipLaunchKernelGGL((k_backproj<M, 2, VEC, ST, G>), dim3(pl.bp_rb, pl.bp_cr, ng), dim3(256), 0,
+    // the matrix-core form takes 1024 rows per workgroup
+    unsigned rb = pl.bp_rb;
+    if (G > 0) rb = std::max(rb, (unsigned)((pl.p + 1023) / 1024));
+    hipLaunchKernelGGL((k_backproj<M, 2, VEC, ST, G>), dim3(rb, pl.bp_cr, ng), dim3(256), 0,
                        st, pp, j0, S, act, gpart, touched, pl.bp_cr, pl.bp_thr, ctrl);
     return hipGetLastError();
 }
 
-// With m <= 16 the launch carries the dense code when the plan allows dense
-// passes (m > 4, 16-byte loads).
+// With m <= 16 the launch carries the matrix-core form when the plan allows it
+// (m > 4, 16-byte loads).
 template <bool VEC, int ST>
 static hipError_t launch_bp_v(const Plan& pl, const PassParams& pp, int j0, const float* S,
                               const uint8_t* act, float* gpart, int* touched, const Ctrl* ctrl,
@@ -1202,13 +1217,13 @@ static hipError_t launch_bp_v(const Plan& pl, const PassParams& pp, int j0, cons
     if (r > 16 || (r == 16 && pl.m > 16))
         return launch_bp_t<16, VEC, ST, 0>(pl, pp, j0, S, act, gpart, touched, ctrl, st, r / 16);
     const int mb = r <= 1 ? 1 : r <= 2 ? 2 : r <= 4 ? 4 : r <= 8 ? 8 : 16;
-    // m <= 16: the dense code rides in this launch; m > 16: k_backproj_dense
-    const bool dense_here = j0 == 0 && pl.bp_thr <= kBpThrMax && pl.m <= 16;
+    // m <= 16: the matrix-core form rides in this launch; m > 16: k_backproj_mc
+    const bool mc_here = j0 == 0 && pl.bp_thr <= kBpThrMax && pl.m <= 16;
     if constexpr (VEC) {
-        if (dense_here && mb == 8) return launch_bp_t<8, VEC, ST, 1>(pl, pp, j0, S, act, gpart, touched, ctrl, st);
-        if (dense_here && mb == 16) return launch_bp_t<16, VEC, ST, 1>(pl, pp, j0, S, act, gpart, touched, ctrl, st);
+        if (mc_here && mb == 8) return launch_bp_t<8, VEC, ST, 1>(pl, pp, j0, S, act, gpart, touched, ctrl, st);
+        if (mc_here && mb == 16) return launch_bp_t<16, VEC, ST, 1>(pl, pp, j0, S, act, gpart, touched, ctrl, st);
     }
-    if (dense_here) return hipErrorInvalidValue;   // the plan never allows this
+    if (mc_here) return hipErrorInvalidValue;   // the plan never allows this
     switch (mb) {
         case 1: return launch_bp_t<1, VEC, ST, 0>(pl, pp, j0, S, act, gpart, touched, ctrl, st);
         case 2: return launch_bp_t<2, VEC, ST, 0>(pl, pp, j0, S, act, gpart, touched, ctrl, st);
@@ -1225,11 +1240,11 @@ hipError_t launch_backproj(const Plan& pl, const PassParams& pp, const float* S,
     if (pl.bp_thr <= kBpThrMax && pl.m > 16) {
         hipError_t e;
         if (pl.dtype == GPSPCA_BF16)
-            e = launch_bp_dense<kStBF16>(pl, pp, S, act, gpart, touched, ctrl, st);
+            e = launch_bp_mc<kStBF16>(pl, pp, S, act, gpart, touched, ctrl, st);
         else if (pl.dtype == GPSPCA_F8E4M3)
-            e = launch_bp_dense<kStF8>(pl, pp, S, act, gpart, touched, ctrl, st);
+            e = launch_bp_mc<kStF8>(pl, pp, S, act, gpart, touched, ctrl, st);
         else
-            e = launch_bp_dense<kStF32>(pl, pp, S, act, gpart, touched, ctrl, st);
+            e = launch_bp_mc<kStF32>(pl, pp, S, act, gpart, touched, ctrl, st);
         if (e != hipSuccess) return e;
     }
     for (int j0 = 0; j0 < pl.m; j0 += (pl.m - j0 >= 16 && pl.m > 16) ? (pl.m - j0) / 16 * 16 : 16) {

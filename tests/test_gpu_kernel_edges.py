@@ -341,3 +341,34 @@ def test_gram_row_blocks(gpu, p, n, m, path, monkeypatch):
         res = gpu.solve(to_device(A32), gpu.BL1, m, gamma, X0=x_to_device(X0), tol=0.0, max_iter=3)
         assert rel(res.X.cpu().numpy(), ref["X"]) <= 1e-5
         np.testing.assert_allclose(res.trace, ref["trace"], rtol=1e-5)
+
+
+@pytest.mark.parametrize("store", ["f32", "bf16", "e4m3"])
+@pytest.mark.parametrize("active", ["one", "few", "clustered", "all"])
+@pytest.mark.parametrize("p,n,m", [(64, 2_200_000, 5), (1028, 4097, 9), (1023, 5000, 16),
+                                   (1000, 3000, 17), (2052, 700, 33), (67, 131, 64)])
+def test_matrix_core_back_projection(gpu, p, n, m, active, store, monkeypatch):
+    """G of one pass over lists of active columns: a single one, every 97th, the
+    last ranges only, all (2148 columns a range at n = 2.2e6, more than one list);
+    ragged rows; one to four component groups.  The same S in FP64 on the same
+    stored values, so only the FP32 sums over a range differ."""
+    monkeypatch.setenv("GPSPCA_BACKPROJ", "dense")
+    m = min(m, p)
+    gen = torch.Generator(device="cuda").manual_seed(p + n)
+    ld = (p + 3) // 4 * 4
+    buf = torch.randn((n, ld), device="cuda", generator=gen)
+    i = torch.arange(n, device="cuda")
+    on = {"one": i == n // 3, "few": i % 97 == 5, "clustered": i >= n - n // 9,
+          "all": i >= 0}[active]
+    buf *= on[:, None]
+    A = buf[:, :p].t()
+    scale, Av = None, A.double()
+    if store != "f32":
+        A, scale = gpu.quantize(A, TD[O.BF16 if store == "bf16" else O.E4M3])
+        Av = A[:p].double() * (1.0 if scale is None else scale.double()[None, :])
+    X = x_to_device(fp32_round(W.random_orthonormal(p, m, 7)))
+    mu = np.linspace(1.0, 0.7, m)
+    out = gpu.step(A, O.BL1, X, 0.05, mu=list(mu), col_scale=scale)
+    ref = Av @ (out.S.double() * torch.tensor(mu, device="cuda"))
+    assert (out.S != 0).any() and not (out.S[~on] != 0).any()
+    assert rel(out.G.cpu().numpy(), ref.cpu().numpy()) <= 1e-5
