@@ -342,9 +342,16 @@ def quantize(A: torch.Tensor, dtype: torch.dtype, stream: Optional[torch.cuda.St
     M = matrix(A)
     p, n = A.shape
     ldq = (p + 15) // 16 * 16
-    store = torch.empty((n, ldq), dtype=dtype, device=A.device)
-    if ldq > p:
-        store.view(torch.uint8).view(n, -1)[:, p * store.element_size():].zero_()
+    # The padding rows are zero.  Clearing all of a small store is one call, where
+    # the views of the padding cost the host 3 us more (216 x 1422 in 16 against
+    # 19 us, 1001 x 8000 in 17 against 19); at 2001 x 20000 clearing everything costs
+    # 11 us more in 16 bits, and at 10000 x 100000 it takes 240 us.
+    if ldq > p and n * ldq <= 1 << 24:
+        store = torch.zeros((n, ldq), dtype=dtype, device=A.device)
+    else:
+        store = torch.empty((n, ldq), dtype=dtype, device=A.device)
+        if ldq > p:
+            store.view(torch.uint8).view(n, -1)[:, p * store.element_size():].zero_()
     scale = torch.empty(n, dtype=torch.float32, device=A.device) \
         if dtype == torch.float8_e4m3fn else None
     to = L.BF16 if dtype == torch.bfloat16 else L.F8E4M3
