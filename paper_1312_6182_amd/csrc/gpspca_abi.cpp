@@ -778,7 +778,7 @@ static int enqueue_pass(const Plan& pl, const PassParams& pp, const Ptrs& P, int
     const bool x_in_stop = !pl.path && pl.m == 1 && pl.defl_k == 0 && !(pl.use_mfma || pl.use_q);
     if (pl.path) {
         GPSPCA_HIP(launch_stop_path(pl, P.fpart, P.nnzpart, P.gram, P.trace, P.coef, P.fcomp,
-                                    P.pstate, P.ctrl, st));
+                                    P.fsum, P.pstate, P.ctrl, st));
     } else {
         GPSPCA_HIP(launch_stop(pl, P.fpart, P.nnzpart, P.gram, P.trace, P.coef, P.fcomp,
                                P.coef + 5 * (size_t)pl.m * pl.m, P.g64, x_in_stop ? Xn : nullptr,

@@ -272,7 +272,7 @@ struct PathState {
 };
 hipError_t launch_stop_path(const Plan& pl, const double* fpart, const int* nnzpart,
                             const double* gram, double* trace, double* coef, double* fcomp,
-                            PathState* ps, Ctrl* ctrl, hipStream_t st);
+                            double* fsum, PathState* ps, Ctrl* ctrl, hipStream_t st);
 hipError_t launch_bcast_col0(const Plan& pl, float* X, hipStream_t st);
 hipError_t launch_project_diag(const Plan& pl, const double* gram, double* coef, Ctrl* ctrl,
                                hipStream_t st);

@@ -942,53 +942,26 @@ hipError_t launch_stop(const Plan& pl, const double* fpart, const int* nnzpart,
 // Per column: objective trace, stopping rule, and the sphere retraction
 // x_j <- g_j / ||g_j||; a column whose rule fired is frozen (Psi_jj = 1), so
 // its x, and with it S, F and Z, stay those of its stopping pass.
-__global__ __launch_bounds__(1024) void k_stop_path(int m, int nwp, const double* __restrict__ fpart,
-                            const int* __restrict__ nnzpart, double* __restrict__ trace,
+// fsum: objective and support size per column, summed by k_gram_sum in its own
+// workgroups (summed here, by one workgroup from 2048 partials a column, this
+// kernel took 11 us at m = 16 and 16 at m = 32 instead of 4.5 and 4.8).
+__global__ __launch_bounds__(256) void k_stop_path(int m, double* __restrict__ trace,
                             double* __restrict__ coef, double* __restrict__ fcomp,
+                            const double* __restrict__ fsum,
                             PathState* __restrict__ ps, Ctrl* __restrict__ ctrl) {
     if (ctrl->done) return;
-    __shared__ double red[1024];
-    __shared__ int redi[1024];
-    __shared__ double fj[kMaxM];
-    __shared__ int nj[kMaxM];
     __shared__ int nfrozen;
     const int t = threadIdx.x, nt = blockDim.x, mm = m * m;
     const int k = ctrl->k;
     const int max_iter = ctrl->max_iter;
     const double tol = ctrl->tol;
-    // per-column objective and support size: tpc threads per column, each
-    // summing a strided slice, the slices added in order (fixed order)
-    {
-        const int tpc = nt / m >= 1 ? nt / m : 1;
-        for (int j0 = 0; j0 < m; j0 += nt / tpc) {
-            const int j = j0 + t / tpc, sl = t % tpc;
-            double s = 0.0;
-            int c = 0;
-            if (j < m && t / tpc < nt / tpc)
-                slice_sum<16>(fpart + (size_t)j * nwp, nnzpart + (size_t)j * nwp, nwp, sl, tpc, &s, &c);
-            red[t] = s;
-            redi[t] = c;
-            __syncthreads();
-            if (sl == 0 && j < m && t / tpc < nt / tpc) {
-                double a = 0.0;
-                int b = 0;
-                for (int q = 0; q < tpc; ++q) {
-                    a += red[t + q];
-                    b += redi[t + q];
-                }
-                fj[j] = a;
-                nj[j] = b;
-            }
-            __syncthreads();
-        }
-    }
     if (t == 0) nfrozen = 0;
     for (int e = t; e < 2 * mm; e += nt) coef[e] = 0.0;  // Omega, Psi (the summed Gram is at 2mm)
     __syncthreads();
     for (int j = t; j < m; j += nt) {
-        const double F = fj[j];
+        const double F = fsum[j];
         fcomp[j] = F;
-        reinterpret_cast<int64_t*>(fcomp + m)[j] = nj[j];
+        reinterpret_cast<int64_t*>(fcomp + m)[j] = (int64_t)fsum[m + j];
         PathState st = ps[j];
         if (!st.frozen) {
             trace[(size_t)j * max_iter + k] = F;
@@ -1037,11 +1010,12 @@ __global__ __launch_bounds__(1024) void k_stop_path(int m, int nwp, const double
 
 hipError_t launch_stop_path(const Plan& pl, const double* fpart, const int* nnzpart,
                             const double* gram, double* trace, double* coef, double* fcomp,
-                            PathState* ps, Ctrl* ctrl, hipStream_t st) {
-    hipError_t e = launch_gram_sum(pl, pl.m * pl.m, pl.gram_blocks, gram, coef, ctrl, st);
+                            double* fsum, PathState* ps, Ctrl* ctrl, hipStream_t st) {
+    hipError_t e = launch_gram_sum(pl, pl.m * pl.m, pl.gram_blocks, gram, coef, ctrl, st, fpart,
+                                   nnzpart, fsum);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_stop_path, dim3(1), dim3(1024), 0, st, pl.m, pl.nwave_part, fpart,
-                       nnzpart, trace, coef, fcomp, ps, ctrl);
+    hipLaunchKernelGGL(k_stop_path, dim3(1), dim3(256), 0, st, pl.m, trace, coef, fcomp, fsum, ps,
+                       ctrl);
     return hipGetLastError();
 }
 
