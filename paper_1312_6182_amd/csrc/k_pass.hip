@@ -813,10 +813,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         // matrix-core form; with m > 16 it is a launch of its own
         if constexpr (G > 0) {
             constexpr int RL = 4;
-            const int q0 = (blockIdx.x * 4 + wv) * 16 * RL;
-            const bool on = bpm_range<RL, G, ST>(pp, cb, ce, q0, S, act,
-                                                 gpart + (size_t)cr * m * pp.ldx);
-            if (blockIdx.x == 0 && t == 0) touched[cr] = on ? 1 : 0;
+            for (int b = blockIdx.x; b * 64 * RL < nq; b += gridDim.x) {
+                const bool on = bpm_range<RL, G, ST>(pp, cb, ce, (b * 4 + wv) * 16 * RL, S, act,
+                                                     gpart + (size_t)cr * m * pp.ldx);
+                if (b == 0 && t == 0) touched[cr] = on ? 1 : 0;
+                __syncthreads();   // before the next block's list
+            }
         }
         return;
     }
@@ -1198,9 +1200,13 @@ template <int M, bool VEC, int ST, int G>
 static hipError_t launch_bp_t(const Plan& pl, const PassParams& pp, int j0, const float* S,
                               const uint8_t* act, float* gpart, int* touched, const Ctrl* ctrl,
                               hipStream_t st, int ng = 1) {
-    // the matrix-core form takes 1024 rows per workgroup
+    // the matrix-core form takes 1024 rows per workgroup and turn, the other one
+    // 2048: few workgroups get those of a second row block at once (2003 x 20021
+    // bfloat16, m = 16: 157 workgroups 40 us, 314 with a row block per wave 21); with
+    // 256 or more the second turn costs nothing, and the extra ones would cost
+    // passes of the vector-ALU form 1.7 us at 10000 x 100000, m = 8
     unsigned rb = pl.bp_rb;
-    if (G > 0) rb = std::max(rb, (unsigned)((pl.p + 1023) / 1024));
+    if (G > 0 && rb * (unsigned)pl.bp_cr < 256) rb = std::max(rb, (unsigned)((pl.p + 1023) / 1024));
     hipLaunchKernelGGL((k_backproj<M, 2, VEC, ST, G>), dim3(rb, pl.bp_cr, ng), dim3(256), 0,
                        st, pp, j0, S, act, gpart, touched, pl.bp_cr, pl.bp_thr, ctrl);
     return hipGetLastError();
