@@ -4,8 +4,10 @@
 // Per pass k (Section 2, Table 1):
 //   m = 1, p <= 20480   k_pass_m1 (one read of A; correlation, threshold and
 //                       back-projection fused)
-//   otherwise           k_corr (correlation + threshold, one read of A) and
-//                       k_backproj (reads only the columns in the support)
+//   small matrices      k_small (every pass of a solve in one persistent launch)
+//   otherwise           a correlation kernel (k_corr_sh, k_corr_mfma, k_corr, ...:
+//                       correlation + threshold, one read of A) and k_backproj
+//                       (reads only the columns in the support)
 //   then                k_reduce_partials -> k_gram -> k_stop -> k_apply
 //                       (after k_pass_m1: k_reduce_m1 -> k_stop_x1, which
 //                       writes x_{k+1} itself)

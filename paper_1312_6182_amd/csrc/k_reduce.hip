@@ -10,8 +10,9 @@
 //                      X_{k+1} = G Omega + X_k Psi:
 //                        m = 1   Omega = 1/||g||           (unit sphere)
 //                        block   Omega = (G^T G)^{-1/2}    (polar factor on the
-//                                Stiefel manifold), from a cyclic Jacobi
-//                                eigen-decomposition in FP64;
+//                                Stiefel manifold), in FP64 by a Newton-Schulz
+//                                iteration, by a cyclic Jacobi eigen-
+//                                decomposition where that does not converge;
 //                        dead components (empty support) are completed by the
 //                        polar factor of the previous columns projected off the
 //                        live part, expressed through the same Gram matrices,
