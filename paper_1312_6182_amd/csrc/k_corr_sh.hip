@@ -44,9 +44,10 @@
 //   2  bfloat16 codes, three products with the parts of X;
 //   3  e4m3 codes widened to bfloat16 (exact), as mode 2.
 // Rows past the last full 16-byte slot are added by FP32 FMAs at the end.  A
-// correlation that comes out non-finite in the modes that split values (the
-// parts of an infinity or of a value near the FP32 limit are NaN) is computed
-// again by plain FP32 FMAs.
+// correlation that comes out non-finite is computed again by plain FP32 FMAs:
+// the parts of an infinity or of a value near the FP32 limit are NaN, and in
+// every mode the slots of the last stage past a column's end repeat its last
+// full slot against zeros of X, where an infinity gives NaN.
 #include "gpspca_internal.h"
 #include "storage.h"
 
@@ -396,17 +397,15 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                     for (int jb = 0; jb < J; ++jb)
                         y[jb] = __builtin_fmaf(a, X[(size_t)(16 * jb + lj) * pp.ldx + r], y[jb]);
                 }
-                if constexpr (MODE != 0) {
 #pragma unroll
-                    for (int jb = 0; jb < J; ++jb)
-                        if (!(fabsf(y[jb]) < __builtin_inff())) {
-                            const float* xc = X + (size_t)(16 * jb + lj) * pp.ldx;
-                            float z = 0.f;
-                            for (int r = 0; r < p; ++r)
-                                z = __builtin_fmaf(sh_elem<MODE>(ac, r), xc[r], z);
-                            y[jb] = z;
-                        }
-                }
+                for (int jb = 0; jb < J; ++jb)
+                    if (!(fabsf(y[jb]) < __builtin_inff())) {
+                        const float* xc = X + (size_t)(16 * jb + lj) * pp.ldx;
+                        float z = 0.f;
+                        for (int r = 0; r < p; ++r)
+                            z = __builtin_fmaf(sh_elem<MODE>(ac, r), xc[r], z);
+                        y[jb] = z;
+                    }
                 const float sc = (MODE >= 2 && cvalid) ? column_scale(pp, col) : 1.0f;
                 bool any = false;
 #pragma unroll
