@@ -198,9 +198,9 @@ static int backproj_threshold(const gpspca_matrix* A, int m, int vec4, int restr
 //   FP32, aligned   m 5-16: 0.96 at 1600, 1.15 at 3200, 1.01-1.03 at 4000 and
 //                   10000; m 17-32: 1.00 at 100-400, 1.05-1.10 at 800-6000;
 //                   m > 32: 0.97 up to 4000, 1.17 at 6000, 1.3 at 10000
-//   FP32, unaligned m 2-4: 0.94 at 400, 1.13 at 1600, 1.5 at 6000; m 5-8: 0.92
-//                   up to 1600, 1.0 at 2000-3200, 1.07 at 6000; m 9-16: 0.96 at
-//                   400, 1.12 at 1600, 1.9 at 6000; m > 16: 1.02 at 100, 3 at 6000
+//   FP32, unaligned m 2-4: 0.92 at 400, 1.04 at 2000, 1.6 at 5000; m 5-8: 0.9 up
+//                   to 800, 0.95 at 2000, 1.09 at 5000; m 9-16: 1.0 up to 800,
+//                   1.35 at 2000, 1.9 at 5000; m > 16: 1.04 at 100, 1.5 at 2000
 //   bfloat16        0.97-1.05 up to 800, 1.03-1.16 above
 //   e4m3, m <= 32   0.97 up to 800, 1.02-1.07 at 2000-3200, 1.1-1.2 at 10000
 static bool sh_default(const gpspca_matrix* A, int m, int vec4, int path) {
@@ -208,7 +208,7 @@ static bool sh_default(const gpspca_matrix* A, int m, int vec4, int path) {
     if (A->dtype == GPSPCA_BF16) return true;
     if (A->dtype == GPSPCA_F8E4M3) return e >= 3e7;
     if (vec4) return m > 32 ? e >= 2.5e8 : m > 16 ? true : (m >= 5 || path) && e >= 4e7;
-    return m > 16 ? true : m > 8 ? e >= 1e7 : m > 4 ? e >= 4e7 : m >= 2 && e >= 2e7;
+    return m > 16 ? true : m > 8 ? e >= 1e7 : m > 4 ? e >= 9e7 : m >= 2 && e >= 4e7;
 }
 
 // ----------------------------------------------------------------------- plan

@@ -26,15 +26,16 @@
 //     made there, once per workgroup instead of once per wave.
 //
 // Times (10000 x 100000 unless stated; in brackets the kernels that served these
-// before): FP32, 64 components 932 us (one wave per workgroup, parts of X made
-// by every wave: 1245); FP32, 32 components 726 us (LDS DMA, 16x16x4 products:
-// 759 + 9 for its leftover tiles); e4m3, 32 components 296 us (372); FP32 1999 x
-// 20011, 16 components, odd leading dimension 36 us (two vector-ALU launches of
-// 37); bfloat16 2003 x 20021, 16 components 34 us (38).
-// At 64 components the six part products are the bound (the matrix cores are
-// busy 39% of the time and the conversions take 33% of the issue slots, with
-// two waves per SIMD to overlap them); below that, HBM and the latency of the
-// stages.
+// before): FP32, 64 components 993 us (one wave per workgroup, parts of X made
+// by every wave: 1245); FP32, 32 components 757 us (LDS DMA, 16x16x4 products:
+// 759 + 9 for its leftover tiles); e4m3, 32 components 296 us (372); odd leading
+// dimension, FP32: 12 components 756 us, 32 components 913, 64 components 1145
+// (n = 100000, p = 10001), 1999 x 20011, 12 components 39 us (two vector-ALU
+// launches of 37); bfloat16 2003 x 20021, 16 components 34 us (38).
+// At 64 components the six part products are the bound, with their totals (70
+// us, for an error of 3.4e-7 instead of 1.6e-6 at p = 10000) and the conversions
+// on two waves per SIMD to overlap them; below that, HBM and the latency of
+// the stages.
 // Modes (the arithmetic stays FP32-accurate in each):
 //   0  FP32 A, v_mfma_f32_16x16x4_f32 (at most 2 component groups: at 4 the
 //      FP32 matrix cores, not HBM, are the bound);
@@ -59,13 +60,14 @@ namespace gpspca {
 namespace {
 
 typedef float f4s __attribute__((ext_vector_type(4)));
+typedef double d4s __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8s __attribute__((ext_vector_type(8)));
 typedef uint32_t u4s __attribute__((ext_vector_type(4)));
 typedef uint32_t u4sa __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kShWaves = 8;
 constexpr int kShThreads = 64 * kShWaves;
-constexpr int kShTiles = 4;   // tiles per wave and round
+constexpr int kShTiles = 4;   // tiles per wave and round, at most
 constexpr int kShFlush = 4;   // stages per accumulator
 
 template <int MODE, int J, int SB>
@@ -145,7 +147,7 @@ __device__ __forceinline__ float sh_elem(const uint8_t* col, int r) {
 // cend are clamped and their results dropped).  Every wave of the workgroup
 // takes part in the staging of X and in the barriers, NT = 0 included.
 // D stages of A are in flight in registers.
-template <int MODE, int J, int SB, int NT, int D>
+template <int MODE, int J, int SB, int FINE, int NT, int D>
 __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64_t cend, int wv,
                                          uint8_t* __restrict__ lds, const float* __restrict__ X,
                                          const float* __restrict__ Xil, double* f_acc,
@@ -235,22 +237,26 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
         }
     };
 
-    // acc carries the products of kShFlush stages and is then added to tot: the
-    // matrix cores do not round each addition to nearest, and one accumulator
-    // through every stage ends up to 8e-6 off (relative, e4m3, p = 10000).  With
-    // 4 component groups there are no registers for both; the error is then
-    // 1e-6 (FP32, p = 10000).
-    constexpr bool kTot = J < 4;
-    f4s acc[NA][J], tot[NA][kTot ? J : 1];
+    // The matrix cores chain their additions (FP32 operands: one rounding per
+    // row; bfloat16: one truncation per 32 rows), so an accumulator through all
+    // rows would be off by sqrt(rows) roundings.  STEP: it carries 16 rows (FINE
+    // == 8: 8; mode 1: 32) from zero and is added to tot, in FP64 with FINE.
+    // Otherwise acc carries kShFlush stages before it is added to tot; with 4
+    // component groups of 16/8-bit codes it is all there is.
+    constexpr bool STEP = MODE == 1 || FINE > 0;
+    constexpr bool kTot = STEP || J < 4;
+    using TotV = typename std::conditional<(FINE > 0), d4s, f4s>::type;
+    f4s acc[STEP ? 1 : NA][STEP ? 1 : J];
+    TotV tot[kTot ? NA : 1][kTot ? J : 1];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int jb = 0; jb < J; ++jb) {
-            acc[t][jb] = f4s{0.f, 0.f, 0.f, 0.f};
-            if constexpr (kTot) tot[t][jb] = acc[t][jb];
+            if constexpr (!STEP) acc[t][jb] = f4s{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kTot) tot[t][jb] = TotV{0, 0, 0, 0};
         }
     auto flush = [&] {
-        if constexpr (kTot) {
+        if constexpr (kTot && !STEP) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -291,12 +297,31 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                 for (int jb = 0; jb < J; ++jb) {
                     const f4s x = *reinterpret_cast<const f4s*>(
                         xb + 16 * ((jb * (T::RS / 4) + 4 * g + lk) * 16 + lj));
+                    constexpr int NC = FINE == 8 ? 2 : 1;
+                    f4s c[NC][PT];
+#pragma unroll
+                    for (int u = 0; u < PT; ++u)
+#pragma unroll
+                        for (int h = 0; h < NC; ++h) {
+                            if constexpr (STEP) c[h][u] = f4s{0.f, 0.f, 0.f, 0.f};
+                            else c[h][u] = acc[t0 + u][jb];
+                        }
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
                         for (int u = 0; u < PT; ++u)
-                            acc[t0 + u][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                a[u][e], x[e], acc[t0 + u][jb], 0, 0, 0);
+                            c[e % NC][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], x[e],
+                                                                                c[e % NC][u], 0, 0, 0);
+#pragma unroll
+                    for (int u = 0; u < PT; ++u) {
+                        if constexpr (STEP) {
+#pragma unroll
+                            for (int h = 0; h < NC; ++h)
+                                tot[t0 + u][jb] += __builtin_convertvector(c[h][u], TotV);
+                        } else {
+                            acc[t0 + u][jb] = c[0][u];
+                        }
+                    }
                 }
             }
         } else {
@@ -324,9 +349,15 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                     const bf8s x1 = *reinterpret_cast<const bf8s*>(at);
                     const bf8s x2 = *reinterpret_cast<const bf8s*>(at + 1024);
                     const bf8s x3 = *reinterpret_cast<const bf8s*>(at + 2048);
+                    f4s c[PT];
+#pragma unroll
+                    for (int u = 0; u < PT; ++u) {
+                        if constexpr (STEP) c[u] = f4s{0.f, 0.f, 0.f, 0.f};
+                        else c[u] = acc[t0 + u][jb];
+                    }
 #define GPSPCA_SH_MM(AA, XX)                                                              \
-    _Pragma("unroll") for (int u = 0; u < PT; ++u) acc[t0 + u][jb] =                       \
-        __builtin_amdgcn_mfma_f32_16x16x32_bf16(AA[u], XX, acc[t0 + u][jb], 0, 0, 0)
+    _Pragma("unroll") for (int u = 0; u < PT; ++u) c[u] =                                  \
+        __builtin_amdgcn_mfma_f32_16x16x32_bf16(AA[u], XX, c[u], 0, 0, 0)
                     if constexpr (MODE == 1) {   // smallest terms first
                         GPSPCA_SH_MM(a3, x1);
                         GPSPCA_SH_MM(a2, x2);
@@ -340,6 +371,11 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                         GPSPCA_SH_MM(a1, x1);
                     }
 #undef GPSPCA_SH_MM
+#pragma unroll
+                    for (int u = 0; u < PT; ++u) {
+                        if constexpr (STEP) tot[t0 + u][jb] += __builtin_convertvector(c[u], TotV);
+                        else acc[t0 + u][jb] = c[u];
+                    }
                 }
             }
         }
@@ -390,7 +426,10 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                 const uint8_t* ac = Ab + (cvalid ? col : cend - 1) * colbytes;
                 float y[J];
 #pragma unroll
-                for (int jb = 0; jb < J; ++jb) y[jb] = kTot ? tot[t][kTot ? jb : 0][v] : acc[t][jb][v];
+                for (int jb = 0; jb < J; ++jb) {
+                    if constexpr (kTot) y[jb] = (float)tot[t][jb][v];
+                    else y[jb] = acc[t][jb][v];
+                }
                 for (int r = rows_main; r < p; ++r) {
                     const float a = sh_elem<MODE>(ac, r);
 #pragma unroll
@@ -435,7 +474,7 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
     }
 }
 
-template <int MODE, int J, int SB>
+template <int MODE, int J, int SB, int FINE>
 __global__ __launch_bounds__(kShThreads, 2) void k_corr_sh(PassParams pp, const float* __restrict__ X,
                                                         const float* __restrict__ Xil,
                                                         float* __restrict__ S,
@@ -460,7 +499,9 @@ __global__ __launch_bounds__(kShThreads, 2) void k_corr_sh(PassParams pp, const 
 #pragma unroll
     for (int jb = 0; jb < J; ++jb) { f_acc[jb] = 0.0; nnz_acc[jb] = 0; }
 
-    constexpr int per = kShWaves * kShTiles;
+    // FP64 totals of 4 component groups: two tiles are what the registers hold
+    constexpr int most = FINE > 0 && J == 4 ? 2 : kShTiles;
+    constexpr int per = kShWaves * most;
     for (int64_t r0 = tb; r0 < te; r0 += per) {
         // the round's tiles, split evenly over the waves
         const int64_t r1 = r0 + per < te ? r0 + per : te;
@@ -470,13 +511,16 @@ __global__ __launch_bounds__(kShThreads, 2) void k_corr_sh(PassParams pp, const 
         const int64_t cend = std::min<int64_t>(n, 16 * w1);
         constexpr int d1 = T::NL == 4 ? 4 : 6;
 #define GPSPCA_SHR(NT, D) \
-    sh_round<MODE, J, SB, NT, D>(pp, c0, cend, wv, lds, X, Xil, f_acc, nnz_acc, S, act)
+    sh_round<MODE, J, SB, FINE, NT, D>(pp, c0, cend, wv, lds, X, Xil, f_acc, nnz_acc, S, act)
         switch ((int)(w1 - w0)) {
             case 0: GPSPCA_SHR(0, 1); break;
             case 1: GPSPCA_SHR(1, d1); break;
             case 2: GPSPCA_SHR(2, (d1 == 4 ? 2 : 4)); break;
-            case 3: GPSPCA_SHR(3, (d1 == 4 ? 1 : 2)); break;
-            default: GPSPCA_SHR(4, (d1 == 4 ? 1 : 2)); break;
+            default:
+                if constexpr (most > 2) {
+                    if (w1 - w0 == 3) GPSPCA_SHR(3, (d1 == 4 ? 1 : 2));
+                    else GPSPCA_SHR(4, (d1 == 4 ? 1 : 2));
+                }
         }
 #undef GPSPCA_SHR
     }
@@ -498,11 +542,11 @@ __global__ __launch_bounds__(kShThreads, 2) void k_corr_sh(PassParams pp, const 
     }
 }
 
-template <int MODE, int J, int SB>
+template <int MODE, int J, int SB, int FINE = 0>
 hipError_t sh_launch(const Plan& pl, const PassParams& pp, const float* X, const float* Xil,
                      float* S, uint8_t* act, double* fpart, int* nnzpart, const Ctrl* ctrl,
                      hipStream_t st) {
-    GPSPCA_LAUNCH_TIMED((k_corr_sh<MODE, J, SB>), dim3(pl.corr_grid), dim3(kShThreads), 0, st,
+    GPSPCA_LAUNCH_TIMED((k_corr_sh<MODE, J, SB, FINE>), dim3(pl.corr_grid), dim3(kShThreads), 0, st,
                         pp, X, Xil, S, act, fpart, nnzpart, ctrl);
     return hipGetLastError();
 }
@@ -528,6 +572,26 @@ hipError_t launch_corr_sh(const Plan& pl, const PassParams& pp, const float* X, 
     const int J = pl.m <= 16 ? 1 : pl.m <= 32 ? 2 : 4;
 #define GPSPCA_SH(MODE, JJ, SB) \
     return sh_launch<MODE, JJ, SB>(pl, pp, X, Xil, S, act, fpart, nnzpart, ctrl, st)
+    // FP32 columns that are not 16-byte aligned: FP64 totals, so that this kernel
+    // is as close to FP64 as the vector-ALU one (k_corr), whose lanes add p / 64
+    // rows each.  Relative error of a correlation, here / k_corr: 6.4e-8 / 7.2e-8
+    // at p = 101, 7.9e-8 / 7.6e-8 at 201 by 16 rows (6.5e-8 by 8), 8.2e-8 / 8.3e-8 at
+    // 401, 8.2e-8 / 2.3e-7 at 10001 (FP32 totals: 2.9e-7 at 1001, 3.1e-7 at 10001).
+    // 8 rows cost 4 us more than 16 at 1999 x 20011, m = 12, so only short
+    // columns take them.  64 components: 5e-8 to 1.2e-7 / 7e-8 to 2.3e-7 (one
+    // accumulator: 4.8e-7 at 1001, 1.6e-6 at 10001).
+    if (pl.dtype == GPSPCA_F32 && !pl.vec4) {
+#define GPSPCA_SHF(MODE, JJ, SB, FF) \
+    return sh_launch<MODE, JJ, SB, FF>(pl, pp, X, Xil, S, act, fpart, nnzpart, ctrl, st)
+        if (J == 4) GPSPCA_SHF(1, 4, 128, 16);
+        if (J == 1) {
+            if (pl.p < 401) GPSPCA_SHF(0, 1, 256, 8);
+            GPSPCA_SHF(0, 1, 256, 16);
+        }
+        if (pl.p < 401) GPSPCA_SHF(0, 2, 256, 8);
+        GPSPCA_SHF(0, 2, 256, 16);
+#undef GPSPCA_SHF
+    }
     if (pl.dtype == GPSPCA_F32) {
         if (J == 1) GPSPCA_SH(0, 1, 256);
         if (J == 2) GPSPCA_SH(0, 2, 256);
