@@ -19,8 +19,14 @@
 //      into LDS.  Equal inputs in equal order give every workgroup the same X
 //      and the same decision, so neither has to be communicated.
 //
+// Sums are FP32 over 8 to 16 rows (4 to 16 columns) and FP64 above that, so that
+// the results are as close to FP64 as those of the separate launches, whose
+// chains are shorter than a workgroup's here: with FP32 alone the X and Z of a
+// pass were 1.1 to 2 times further off.  It costs 1.3 us per pass at 200 x 2000,
+// m = 5, and 0.2 at m = 1.
+//
 // Per pass, as separate launches -> here: 100 x 1000, m = 1: 20 -> 8 us; 200 x 2000,
-// m = 5: 56 -> 21; 400 x 4000, m = 1, deflated: 27 -> 13.  What is left is the
+// m = 5: 56 -> 22; 400 x 4000, m = 1, deflated: 27 -> 13.  What is left is the
 // latency of the barrier (1.5-3 us), of reading the partials (2-4) and of the
 // dependent steps in between.
 //
@@ -49,6 +55,7 @@ namespace {
 
 typedef float f4c __attribute__((ext_vector_type(4)));
 typedef float f4cu __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d4c __attribute__((ext_vector_type(4)));
 
 constexpr int kSmT = 512, kSmW = 8;
 constexpr int kSmallLds = 146 * 1024;       // dynamic LDS of a workgroup
@@ -257,23 +264,41 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
                 const int tl = i % tw, part = i / tw;
                 const f4c* ac = Al + (tl * 16 + lj) * sq + lk;
                 const int sa = nsteps * part / parts, sz = nsteps * (part + 1) / parts;
-                f4c acc = f4c{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-                for (int s = sa; s < sz; ++s) {
-                    const f4c x = *reinterpret_cast<const f4c*>(Xl + 4 * (4 * s + lk));
-                    const f4c av = ac[4 * s];
+                double yd = 0.0;
+#pragma unroll 2
+                for (int s0 = sa; s0 < sz; s0 += 4) {   // 4 quads per FP32 sum
+                    f4c acc = f4c{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(av[e], x[e], acc[e]);
+                    for (int u = 0; u < 4; ++u) {
+                        const bool in = s0 + u < sz;
+                        const int s = in ? s0 + u : sz - 1;
+                        const f4c x = *reinterpret_cast<const f4c*>(Xl + 4 * (4 * s + lk));
+                        const f4c av = ac[4 * s];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[e] = __builtin_fmaf(in ? av[e] : 0.f, x[e], acc[e]);
+                    }
+                    yd += (double)((acc[0] + acc[1]) + (acc[2] + acc[3]));
                 }
-                float y = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-                y += __shfl_xor(y, 16, 64);
-                y += __shfl_xor(y, 32, 64);
-                if (lk == 0) gp[(tl * 16 + lj) * parts + part] = y;
+                yd += __shfl_xor(yd, 16, 64);
+                yd += __shfl_xor(yd, 32, 64);
+                // at most 128 partial sums, or one per column
+                if (lk == 0 && parts > 1)
+                    reinterpret_cast<double*>(gp)[(tl * 16 + lj) * parts + part] = yd;
+                else if (lk == 0)
+                    gp[tl * 16 + lj] = (float)yd;
             }
             __syncthreads();
             for (int c = t; c < tw * 16; c += kSmT) {
-                float y = gp[c * parts];
-                for (int i = 1; i < parts; ++i) y += gp[c * parts + i];
+                float y;
+                if (parts > 1) {
+                    const double* yp = reinterpret_cast<const double*>(gp) + c * parts;
+                    double yd = yp[0];
+                    for (int i = 1; i < parts; ++i) yd += yp[i];
+                    y = (float)yd;
+                } else {
+                    y = gp[c];
+                }
                 float s = 0.f;
                 const int64_t col = 16 * tb + c;
                 if (col < n) {
@@ -292,18 +317,19 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
         for (int tl = wv; tl < tw; tl += kSmW) {
             const int64_t c0 = 16 * (tb + tl);
             const f4c* ac = Al + (tl * 16 + lj) * sq + lk;
-            f4c acc[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] = f4c{0.f, 0.f, 0.f, 0.f};
+            d4c tot = d4c{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
-            for (int s = 0; s < nsteps; ++s) {
+            for (int s = 0; s < nsteps; ++s) {   // 8 rows per FP32 sum
                 const f4c x = *reinterpret_cast<const f4c*>(Xl + 4 * ((4 * s + lk) * m + cj));
                 const f4c av = ac[4 * s];
+                f4c c[2];
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], x[e], acc[e], 0, 0, 0);
+                    c[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        av[e], x[e], e < 2 ? f4c{0.f, 0.f, 0.f, 0.f} : c[e & 1], 0, 0, 0);
+                tot += __builtin_convertvector(c[0] + c[1], d4c);
             }
-            const f4c y = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+            const f4c y = __builtin_convertvector(tot, f4c);
             uint32_t mask = 0;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -363,35 +389,44 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
             for (int q0 = 0; q0 < nq; q0 += kSmT) {
                 const int q = nsp > 1 ? t % nq : q0 + t, sp = nsp > 1 ? t / nq : 0;
                 if (q < nq && sp < nsp) {
-                    f4c g = f4c{0.f, 0.f, 0.f, 0.f};
+                    d4c tot = d4c{0.0, 0.0, 0.0, 0.0};
                     const int ca = tw * 16 * sp / nsp, cz = tw * 16 * (sp + 1) / nsp;
-                    for (int c = ca; c < cz; ++c) {
-                        const float sw = Sw[c];
-                        float w = muj * sw;
-                        if constexpr (ST != kStF32) {
-                            const int64_t col = 16 * tb + c;
-                            w *= column_scale(pp, col < n ? col : n - 1);
-                        }
-                        // an inactive column has weight 0 and may hold anything
-                        const f4c av = Al[c * sq + q];
+                    for (int c0 = ca; c0 < cz; c0 += 8) {   // 4 columns per FP32 sum
+                        f4c g[2];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            g[e] = __builtin_fmaf(w, sw != 0.f ? av[e] : 0.f, g[e]);
+                        for (int u = 0; u < 8; ++u) {
+                            if (u % 4 == 0) g[u / 4] = f4c{0.f, 0.f, 0.f, 0.f};
+                            const int c = c0 + u < cz ? c0 + u : cz - 1;
+                            const float sw = c0 + u < cz ? Sw[c] : 0.f;
+                            float w = muj * sw;
+                            if constexpr (ST != kStF32) {
+                                const int64_t col = 16 * tb + c;
+                                w *= column_scale(pp, col < n ? col : n - 1);
+                            }
+                            // an inactive column has weight 0 and may hold anything
+                            const f4c av = Al[c * sq + q];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                g[u / 4][e] = __builtin_fmaf(w, sw != 0.f ? av[e] : 0.f, g[u / 4][e]);
+                        }
+                        tot += __builtin_convertvector(g[0], d4c) + __builtin_convertvector(g[1], d4c);
                     }
-                    *reinterpret_cast<f4c*>(gp + 4 * (nsp > 1 ? sp * nq + q : t)) = g;
+                    *reinterpret_cast<f4c*>(gp + 4 * (nsp > 1 ? sp * nq + q : t)) =
+                        __builtin_convertvector(tot, f4c);
                 }
                 __syncthreads();
                 const int len = nsp > 1 ? 4 * nq : 4 * (nq - q0 < kSmT ? nq - q0 : kSmT);
                 for (int e = t; e < len; e += kSmT) {
                     const int r = 4 * q0 + e;
-                    float v[8], g = 0.f;
+                    float v[8];
+                    double g = 0.0;
 #pragma unroll
                     for (int i = 0; i < 8; ++i) v[i] = gp[(i < nsp ? i : 0) * 4 * nq + e];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) g += i < nsp ? v[i] : 0.f;
+                    for (int i = 0; i < 8; ++i) g += i < nsp ? (double)v[i] : 0.0;
                     if (r < p) {
-                        if (nb > 1) put(gpart + (size_t)wg * ldx + r, g);
-                        else Gd[r] = (double)g;
+                        if (nb > 1) put(gpart + (size_t)wg * ldx + r, (float)g);
+                        else Gd[r] = g;
                     }
                 }
                 __syncthreads();
@@ -407,35 +442,46 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
             if (rb < nrb && cs < csp) {
                 const int ta = tw * cs / csp, tz = tw * (cs + 1) / csp;
                 const int q = 16 * rb + lj < sq ? 16 * rb + lj : sq - 1;   // rows past p are dropped
-                f4c acc[4];
+                d4c tot[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = f4c{0.f, 0.f, 0.f, 0.f};
-                for (int tl = ta; tl < tz; ++tl) {
-                    const uint32_t mask = __builtin_amdgcn_readfirstlane(actm[tl]);
-                    if (mask == 0) continue;
+                for (int e = 0; e < 4; ++e) tot[e] = d4c{0.0, 0.0, 0.0, 0.0};
+                for (int t0 = ta; t0 < tz; t0 += 2) {   // 16 columns per FP32 sum
+                    f4c acc[2][4];
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int c = tl * 16 + 4 * g + lk;
-                        // an inactive column has weight 0 and may hold anything
-                        const bool in = (mask >> (4 * g + lk)) & 1u;
-                        const f4c av = Al[c * sq + q];
-                        float w = muj * Sw[c * m + cj];
-                        if constexpr (ST != kStF32) {
-                            const int64_t col = 16 * tb + c;
-                            w *= column_scale(pp, col < n ? col : n - 1);
+                    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[h][e] = f4c{0.f, 0.f, 0.f, 0.f};
+                        const int tl = t0 + h;
+                        if (tl >= tz) continue;
+                        const uint32_t mask = __builtin_amdgcn_readfirstlane(actm[tl]);
+                        if (mask == 0) continue;
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const int c = tl * 16 + 4 * g + lk;
+                            // an inactive column has weight 0 and may hold anything
+                            const bool in = (mask >> (4 * g + lk)) & 1u;
+                            const f4c av = Al[c * sq + q];
+                            float w = muj * Sw[c * m + cj];
+                            if constexpr (ST != kStF32) {
+                                const int64_t col = 16 * tb + c;
+                                w *= column_scale(pp, col < n ? col : n - 1);
+                            }
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                acc[h][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                    in ? av[e] : 0.f, w, acc[h][e], 0, 0, 0);
                         }
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? av[e] : 0.f, w, acc[e],
-                                                                          0, 0, 0);
                     }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        tot[e] += __builtin_convertvector(acc[0][e] + acc[1][e], d4c);
                 }
                 if (lj < m) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            gp[(wv * m + lj) * 64 + 16 * lk + 4 * v + e] = acc[e][v];
+                            gp[(wv * m + lj) * 64 + 16 * lk + 4 * v + e] = (float)tot[e][v];
                 }
             }
             __syncthreads();
@@ -444,14 +490,15 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
                 const int row = e & 63, j = (e >> 6) % m, b = (e >> 6) / m;
                 const int r = 64 * (rb0 + b) + row;
                 if (r >= p) continue;
-                float v[kSmW], g = 0.f;
+                float v[kSmW];
+                double g = 0.0;
 #pragma unroll
                 for (int c = 0; c < kSmW; ++c)
                     v[c] = gp[(((c < csp ? c : 0) * nrb + b) * m + j) * 64 + row];
 #pragma unroll
-                for (int c = 0; c < kSmW; ++c) g += c < csp ? v[c] : 0.f;
-                if (nb > 1) put(gpart + ((size_t)wg * m + j) * ldx + r, g);
-                else Gd[j * p + r] = (double)g;
+                for (int c = 0; c < kSmW; ++c) g += c < csp ? (double)v[c] : 0.0;
+                if (nb > 1) put(gpart + ((size_t)wg * m + j) * ldx + r, (float)g);
+                else Gd[j * p + r] = g;
             }
             __syncthreads();
         }

@@ -66,3 +66,54 @@ def test_64_components_keep_the_accuracy_of_short_chains(gpu, monkeypatch):
     X = x_to_device(fp32_round(W.random_orthonormal(p, m, 9)))
     monkeypatch.setenv("GPSPCA_CORR_KERNEL", "sh")
     assert _correlation_error(gpu, A, X, A.t().double() @ X.double()) <= 5e-7
+
+
+def _two_passes64(A, X0, gamma, polar):
+    """X_1 and the unit-norm Z of the second pass of an L1 solve, in FP64."""
+    def soft(X):
+        Y = A.t() @ X
+        return torch.sign(Y) * (Y.abs() - gamma).clamp_min(0.0)
+
+    G = A @ soft(X0)
+    if polar:
+        w, V = torch.linalg.eigh(G.t() @ G)
+        X = G @ (V / w.sqrt()) @ V.t()
+    else:
+        X = G / G.norm(dim=0)
+    S = soft(X)
+    return X, S / S.norm(dim=0)
+
+
+@pytest.mark.parametrize("pad", [0, 1], ids=["aligned", "odd"])
+@pytest.mark.parametrize("kind,m", [("SL1", 1), ("BL1", 2), ("BL1", 5), ("BL1", 8), ("multi", 4),
+                                    ("multi", 16)])
+@pytest.mark.parametrize("p,n", [(100, 1000), (200, 2000), (400, 4000), (400, 100), (1200, 600)])
+def test_persistent_solves_keep_the_launches_accuracy(gpu, p, n, kind, m, pad, monkeypatch):
+    """Two passes of k_small are no further from FP64 than the launches of the
+    same solve; errors over 24 matrices (at least 2400 entries of X, so their
+    2-norm is known to 1.5%), 7% for the two samples."""
+    p += pad
+    err = {"1": [0.0, 0.0], "0": [0.0, 0.0]}
+    for seed in range(24):
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        A = torch.randn((n, p), device="cuda", generator=gen).t()
+        A64 = A.double()
+        gamma = 0.03 * float(A64.norm(dim=0).max())
+        top = torch.sort(A64.norm(dim=0), descending=True, stable=True)[1][:m]
+        X0 = A64[:, top]
+        if kind == "BL1":
+            u, _, vt = torch.linalg.svd(X0, full_matrices=False)
+            X, Z = _two_passes64(A64, u @ vt, gamma, True)
+        else:
+            X, Z = _two_passes64(A64, X0 / X0.norm(dim=0), gamma, False)
+        for small in err:
+            monkeypatch.setenv("GPSPCA_SMALL", small)
+            if kind == "multi":
+                r = gpu.solve_multistart(A, gpu.SL1, m, gamma, tol=0.0, max_iter=2)
+            else:
+                r = gpu.solve(A, gpu.SL1 if m == 1 else gpu.BL1, m, gamma, tol=0.0, max_iter=2)
+            err[small][0] += float((r.X.double() - X).square().sum())
+            err[small][1] += float((r.Z.double() - Z).square().sum())
+    ratio = [(a / b) ** 0.5 for a, b in zip(err["1"], err["0"])]
+    print(f"\n[accuracy] {kind}{m} p={p} n={n} X {ratio[0]:.3f} Z {ratio[1]:.3f}", flush=True)
+    assert max(ratio) <= 1.07
