@@ -843,9 +843,12 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
 
 // Workgroups of the solve (0: it is not taken) and whether each sums all of G.
 int small_workgroups(const Plan& pl, int* whole) {
-    if (pl.m > (pl.path ? 16 : 8) || pl.restricted || pl.p > 8192) return 0;
+    if (pl.m > (pl.path ? 16 : 8) || pl.restricted) return 0;
     const int64_t ntile = (pl.n + 15) / 16;
     static_assert(kSmallWgs <= 64, "one lane per workgroup's objective term");
+    // the columns alone in 64 bits first (64 bytes of LDS per row and tile at least):
+    // small_lds counts in 32
+    if ((ntile + kSmallWgs - 1) / kSmallWgs * 64 * pl.p > kSmallLds) return 0;
     const int most = std::min(kSmallWgs, std::min(pl.npart, pl.nwave_part) / 2);   // two sets
     // tiles per workgroup that give its waves work, then what its LDS holds
     int nb = (int)std::min<int64_t>(most, (ntile + kSmallTiles - 1) / kSmallTiles);

@@ -1,0 +1,130 @@
+"""What the library launches, without a GPU: the host code of libgpspca.so runs
+against a stub of the HIP runtime (hip_stub.cpp) that records every launch.
+Each scenario is a function of this file run in a child process of its own,
+which loads the stub before the library and never imports torch."""
+import ctypes
+import importlib.util
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+def _module(name, *path):
+    spec = importlib.util.spec_from_file_location(name, os.path.join(ROOT, *path))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    hipcc = _module("gpspca_build", "paper_1312_6182_amd", "build.py").hipcc()
+    so = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-shared",
+                    "-fPIC", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(HERE, "hip_stub.cpp"), "-o", so], check=True, capture_output=True)
+    return so
+
+
+def _child(stub, scenario, **env):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, stub],
+                       capture_output=True, text=True, timeout=120, env={**os.environ, **env})
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+class Lib:
+    """The library on the stub; pointers to device memory are made up."""
+
+    DATA, WS, OUT = 1 << 40, 1 << 44, 1 << 46
+
+    def __init__(self, stub):
+        self.stub = ctypes.CDLL(stub, mode=ctypes.RTLD_GLOBAL)
+        self.stub.stub_log.restype = ctypes.c_size_t
+        self.L = _module("gpspca_lib", "paper_1312_6182_amd", "_lib.py")
+        self.lib = self.L.load()
+        self.result(1)
+
+    def result(self, n_iter, status=1, abort=0):
+        self.stub.stub_result(n_iter, status, abort)
+
+    def launches(self):
+        """(kernel name, (gx, gy, gz), threads, LDS bytes, stream, quantized columns)"""
+        n = self.stub.stub_log(None, ctypes.c_size_t(0))
+        buf = ctypes.create_string_buffer(n + 1)
+        self.stub.stub_log(buf, ctypes.c_size_t(n + 1))
+        out = []
+        for line in buf.value.decode().splitlines():
+            f = line.split()
+            out.append((f[0], tuple(int(v) for v in f[1:4]), int(f[4]), int(f[5]), f[6], int(f[7])))
+        return out
+
+    def names(self):
+        return [k[0] for k in self.launches()]
+
+    def matrix(self, p, n, dtype=0, odd=False):
+        M = self.L.Matrix()
+        pad = (4, 8, 16)[dtype]
+        M.data, M.p, M.n, M.dtype = self.DATA, p, n, dtype
+        M.lda = p | 1 if odd else (p + pad - 1) // pad * pad
+        M.col_scale = 1 << 45 if dtype == self.L.F8E4M3 else None
+        return M
+
+    def solve(self, M, m=1, form=None, max_iter=1, tol=0.0, stream=None):
+        form = (self.L.SL1 if m == 1 else self.L.BL1) if form is None else form
+        nb = self.lib.gpspca_workspace_bytes(ctypes.byref(M), form, m, max_iter)
+        assert nb > 0, self.lib.gpspca_last_error()
+        nit = ctypes.c_int(0)
+        trace = (ctypes.c_double * max_iter)()
+        return self.lib.gpspca_solve(ctypes.byref(M), form, m, 0.1, None, None, tol, max_iter,
+                                     self.WS, nb, stream, self.OUT, self.OUT, self.OUT, trace,
+                                     ctypes.byref(nit))
+
+    def multistart(self, M, m, max_iter=1):
+        nb = self.lib.gpspca_path_workspace_bytes(ctypes.byref(M), m, max_iter)
+        nit, st = (ctypes.c_int * m)(), (ctypes.c_int * m)()
+        return self.lib.gpspca_solve_multistart(ctypes.byref(M), self.L.SL1, m, 0.1, 0.0, max_iter,
+                                                self.WS, nb, None, self.OUT, self.OUT, self.OUT,
+                                                None, nit, st)
+
+
+def _check_limits(case, launches):
+    assert launches, case
+    for name, grid, threads, lds, _, _ in launches:
+        assert all(1 <= g and g * threads < 1 << 32 for g in grid[:1]), (case, name, grid, threads)
+        assert grid[1] < 1 << 16 and grid[2] < 1 << 16, (case, name, grid)
+        assert 1 <= threads <= 1024 and 0 <= lds <= 160 * 1024, (case, name, threads, lds)
+
+
+def child_launch_limits(lib):
+    """Every launch of a solve within the limits of the hardware, from one row and
+    column to matrices that fill the memory of a GPU."""
+    shapes = [(1, 1), (1, 1000), (4, 100000), (100, 1000), (1000, 10000), (1900, 64), (9000, 50),
+              (10000, 100000), (100000, 1000), (1 << 20, 64),
+              (1000, 34_000_000), (1000, 60_000_000), (16, (1 << 30) - 64), (40, 900_000_000)]
+    for p, n in shapes:
+        for dtype in (0, 1, 2):
+            if p * n * (4, 2, 1)[dtype] > 280 << 30:
+                continue
+            M = lib.matrix(p, n, dtype)
+            for m in (1, 2, 5, 8, 16, 64):
+                if m > min(p, n) or 4 * m * n > 200 << 30:
+                    continue
+                case = (p, n, dtype, m)
+                assert lib.solve(M, m) >= 0, (case, lib.lib.gpspca_last_error())
+                _check_limits(case, lib.launches())
+                if m <= 16:
+                    assert lib.multistart(M, m) >= 0, (case, "multistart")
+                    _check_limits((case, "multistart"), lib.launches())
+
+
+def test_launch_limits(stub):
+    _child(stub, "launch_limits")
+
+
+if __name__ == "__main__":
+    globals()["child_" + sys.argv[1]](Lib(sys.argv[2]))
