@@ -855,8 +855,19 @@ static void launch_quantize_to(const float* A, int64_t lda, int p, int64_t n, vo
 
 hipError_t launch_quantize(const float* A, int64_t lda, int p, int64_t n, int to, void* out,
                            int64_t ldq, float* scale, hipStream_t st) {
-    if (to == GPSPCA_BF16) launch_quantize_to<kStBF16>(A, lda, p, n, out, ldq, scale, st);
-    else launch_quantize_to<kStF8>(A, lda, p, n, out, ldq, scale, st);
+    // a dimension of a grid has fewer than 2^32 threads, 256 per column in the
+    // largest shapes
+    constexpr int64_t step = (int64_t)1 << 23;
+    for (int64_t c = 0; c < n; c += step) {
+        const int64_t cols = n - c < step ? n - c : step;
+        float* sc = scale ? scale + c : nullptr;
+        if (to == GPSPCA_BF16)
+            launch_quantize_to<kStBF16>(A + c * lda, lda, p, cols,
+                                        static_cast<uint16_t*>(out) + c * ldq, ldq, sc, st);
+        else
+            launch_quantize_to<kStF8>(A + c * lda, lda, p, cols,
+                                      static_cast<uint8_t*>(out) + c * ldq, ldq, sc, st);
+    }
     return hipGetLastError();
 }
 

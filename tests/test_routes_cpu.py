@@ -126,5 +126,22 @@ def test_launch_limits(stub):
     _child(stub, "launch_limits")
 
 
+def child_quantize_limits(lib):
+    """The quantizer's launches cover every column, each within the 2^32 work
+    items of a dimension (a grid of 2^24 workgroups of 256 threads is too large)."""
+    for p, n in ((3, 50_000_000), (2560, 100), (2561, 20_000_000), (10240, (1 << 24) - 1),
+                 (10240, 1 << 24), (10241, 5_000_000), (40961, 1_000_000)):
+        M = lib.matrix(p, n)
+        for to, ld in ((1, (p + 7) // 8 * 8), (2, (p + 15) // 16 * 16)):
+            assert lib.lib.gpspca_quantize(ctypes.byref(M), to, lib.WS, ld, lib.OUT, None) == 0
+            launches = lib.launches()
+            _check_limits((p, n, to), launches)
+            assert sum(k[5] for k in launches) == n, (p, n, launches)
+
+
+def test_quantize_limits(stub):
+    _child(stub, "quantize_limits")
+
+
 if __name__ == "__main__":
     globals()["child_" + sys.argv[1]](Lib(sys.argv[2]))
