@@ -888,20 +888,43 @@ static int capture_pair(const Plan& pl, const PassParams& pp, const Ptrs& P, Pas
     return GPSPCA_OK;
 }
 
+// CUs of an XCD, also of the partitions of a GPU into several devices.
+constexpr int kXcdCus = 32;
+
+// CUs of each XCD that a persistent solve of nb workgroups holds at most:
+// workgroup i of a launch goes to XCD i mod their number, and one takes a CU's LDS.
+static int small_cus(int nb, int ncu) {
+    const int xcds = std::max(1, ncu / kXcdCus);
+    return nb > 1 ? (nb + xcds - 1) / xcds : 0;
+}
+static int small_room(int ncu) { return std::min(ncu, kXcdCus); }
+
+// Whether every CU is open to the stream's kernels.
+static bool all_cus(hipStream_t st, int ncu) {
+    uint32_t mask[32] = {0};
+    const int words = std::min(32, (ncu + 31) / 32);
+    if (hipExtStreamGetCUMask(st, (uint32_t)words, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    int on = 0;
+    for (int w = 0; w < words; ++w) on += __builtin_popcount(mask[w]);
+    return on >= ncu;
+}
+
 // Admission of the persistent solves (k_small.hip) of this process: their
 // workgroups wait for each other, so all of a solve's must be resident at once.
-// Workgroup i of a launch goes to XCD i mod 8, and one takes a CU's LDS, so a
-// solve with nb workgroups holds ceil(nb / 8) CUs of an XCD at most; the solves
-// in flight on a device never hold more than its XCDs have.  A thread that
+// The solves in flight on a device never hold more CUs than its XCDs have (a
+// solve that could not be resident alone is not taken).  A thread that
 // finds no room waits for another's solve to end.  Other kernels end by
 // themselves; should workgroups wait in vain all the same (another process's
 // persistent kernels), the kernel's bounded wait ends it.
 class SmallRoom {
   public:
-    SmallRoom(int nb, int ncu, int dev) : need_(nb > 1 ? (nb + 7) / 8 : 0), dev_(dev & 63) {
+    SmallRoom(int nb, int ncu, int dev) : need_(small_cus(nb, ncu)), dev_(dev & 63) {
         if (!need_) return;
         std::unique_lock<std::mutex> lk(mu());
-        const int cap = std::max(need_, ncu / 8);
+        const int cap = small_room(ncu);
         cv().wait(lk, [&] { return used()[dev_] + need_ <= cap; });
         used()[dev_] += need_;
     }
@@ -1059,7 +1082,12 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     pl.defl_q = defl_q;
     pl.defl_k = defl_q ? defl_k : 0;
     pl.exact = (exact && !path) ? 1 : 0;
-    if (!no_small && small_enabled(A, m, path)) pl.small_nb = small_workgroups(pl, &pl.small_whole);
+    if (!no_small && small_enabled(A, m, path)) {
+        pl.small_nb = small_workgroups(pl, &pl.small_whole);
+        if (small_cus(pl.small_nb, ncu) > small_room(ncu) ||
+            (pl.small_nb > 1 && !all_cus(st, ncu)))
+            pl.small_nb = 0;
+    }
     const Ptrs P = carve(pl, workspace);
     PassParams pp = make_params(A, pl, gamma, mu, gammas);
     pp.nact = &P.ctrl->nact;

@@ -38,7 +38,7 @@
 //
 // The barriers need every workgroup resident.  The host admits no more
 // workgroups of such solves at once than the CUs of each XCD can hold, one per
-// CU (gpspca_abi.cpp), and a wait that lasts 2 s ends the kernel with
+// CU, and none on a stream that is kept off some CUs (gpspca_abi.cpp), and a wait that lasts 2 s ends the kernel with
 // Ctrl::abort set: the host then runs the passes as separate launches.
 #include "gpspca_internal.h"
 #include "retract.h"

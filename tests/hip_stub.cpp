@@ -20,7 +20,7 @@ struct State {
     std::mutex mu;
     std::map<const void*, std::string> names;
     std::string log;
-    int cus = 256;
+    int cus = 256, masked = 0;   // CUs of the device; of them closed to every stream
     gpspca::Ctrl ctrl;
     dim3 grid, block;
     size_t shm = 0;
@@ -51,7 +51,10 @@ hipError_t record(const void* f, dim3 g, dim3 b, void** args, size_t shm, hipStr
 extern "C" {
 
 // ---- what the test sets and reads
-void stub_device(int cus) { S().cus = cus; }
+void stub_device(int cus, int masked) {
+    S().cus = cus;
+    S().masked = masked;
+}
 void stub_result(int n_iter, int status, int abort) {
     std::lock_guard<std::mutex> lk(S().mu);
     std::memset(&S().ctrl, 0, sizeof(gpspca::Ctrl));
@@ -130,6 +133,11 @@ hipError_t hipStreamSynchronize(hipStream_t st) {
     return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)(uintptr_t)64; return hipSuccess; }
+hipError_t hipExtStreamGetCUMask(hipStream_t, uint32_t words, uint32_t* mask) {
+    std::memset(mask, 0, 4 * words);
+    for (int c = S().masked; c < S().cus && c < 32 * (int)words; ++c) mask[c / 32] |= 1u << (c % 32);
+    return hipSuccess;
+}
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 
 // ---- events and graphs

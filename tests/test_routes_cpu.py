@@ -49,6 +49,11 @@ class Lib:
         self.lib = self.L.load()
         self.result(1)
 
+    def device(self, cus, masked=0):
+        """CUs of the device (the library reads them once), and how many of them are
+        closed to streams."""
+        self.stub.stub_device(cus, masked)
+
     def result(self, n_iter, status=1, abort=0):
         self.stub.stub_result(n_iter, status, abort)
 
@@ -141,6 +146,43 @@ def child_quantize_limits(lib):
 
 def test_quantize_limits(stub):
     _child(stub, "quantize_limits")
+
+
+def _small(lib):
+    """Workgroups of the persistent kernel in the launches so far (none: [])."""
+    return [k[1][0] for k in lib.launches() if "k_small" in k[0]]
+
+
+# persistent solves that take 8, 13, 50 and 64 workgroups on a whole GPU
+SMALL = [(100, 1000, 8), (150, 1600, 13), (400, 4000, 50), (16, 60000, 64)]
+
+
+def child_few_cus(lib):
+    """A device of 32 CUs (one XCD of a partitioned GPU) holds 32 workgroups."""
+    lib.device(32)
+    for p, n, nb in SMALL:
+        assert lib.solve(lib.matrix(p, n), 1, max_iter=4) >= 0
+        assert _small(lib) == ([nb] if nb <= 32 else []), (p, n)
+
+
+def child_masked_stream(lib):
+    """On a stream that is kept off some CUs the XCDs may hold fewer workgroups than
+    the admission counts on: the passes are separate launches there."""
+    lib.device(256)
+    for p, n, nb in SMALL:
+        M = lib.matrix(p, n)
+        assert lib.solve(M, 1, max_iter=4) >= 0 and _small(lib) == [nb]
+        lib.device(256, masked=200)
+        assert lib.solve(M, 1, max_iter=4) >= 0 and _small(lib) == []
+        lib.device(256)
+    M = lib.matrix(20, 100)          # one workgroup waits for nobody
+    lib.device(256, masked=200)
+    assert lib.solve(M, 1, max_iter=4) >= 0 and _small(lib) == [1]
+
+
+@pytest.mark.parametrize("scenario", ["few_cus", "masked_stream"])
+def test_persistent_solves_need_their_cus(stub, scenario):
+    _child(stub, scenario)
 
 
 if __name__ == "__main__":
