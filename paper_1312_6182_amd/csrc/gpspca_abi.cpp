@@ -63,13 +63,14 @@ static bool mfma_balance_enabled() {
 }
 
 // ---------------------------------------------------------------- device info
-static int device_cus(int* out) {
+static int device_cus(int* out, int* device = nullptr) {
     static std::mutex mu;
     static int cached[64] = {0};
     int dev = 0;
     GPSPCA_HIP(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(mu);
     if (dev < 0 || dev >= 64) return fail(GPSPCA_EDEVICE, "device index out of range");
+    if (device) *device = dev;
     if (cached[dev] == 0) {
         int cus = 0;
         GPSPCA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -921,7 +922,7 @@ static bool all_cus(hipStream_t st, int ncu) {
 // persistent kernels), the kernel's bounded wait ends it.
 class SmallRoom {
   public:
-    SmallRoom(int nb, int ncu, int dev) : need_(small_cus(nb, ncu)), dev_(dev & 63) {
+    SmallRoom(int nb, int ncu, int dev) : need_(small_cus(nb, ncu)), dev_(dev) {
         if (!need_) return;
         std::unique_lock<std::mutex> lk(mu());
         const int cap = small_room(ncu);
@@ -946,21 +947,46 @@ class SmallRoom {
     int need_, dev_;
 };
 
+// Limit of a barrier's wait in ticks of the 100 MHz clock: 100 ms, a hundred times
+// the longest kernels of this library, whose workgroups the waiting ones may have
+// to follow.  GPSPCA_SMALL_WAIT sets it (tests).
+static int64_t small_wait() {
+    const char* e = std::getenv("GPSPCA_SMALL_WAIT");
+    return e ? std::atoll(e) : 10000000;
+}
+
+// A wait that ran out is likely to run out again while whatever holds the CUs (another
+// process's persistent kernels) does, so the thread's next 64 solves on that
+// device take the launches at once, twice as many after each further run-out in a
+// row, at most 4096.  A longer limit than the one that ran out is tried all the same.
+struct SmallRetreat {
+    int64_t limit = 0;
+    int left = 0, last = 0;
+    bool holds(int64_t wait) {
+        if (left == 0 || wait > limit) return false;
+        --left;
+        return true;
+    }
+    void ended(bool ran_out, int64_t wait) {
+        last = ran_out ? std::min(4096, std::max(64, 2 * last)) : 0;
+        left = last;
+        limit = wait;
+    }
+};
+static thread_local SmallRetreat t_retreat[64];
+
 // Passes of one k_small launch: a long solve is cut so that the host sees it end.
 constexpr int kSmallChunk = 256;
 constexpr int kSmallAborted = 1000;   // internal: run the passes as separate launches
 
 static int run_small(const Plan& pl, const PassParams& pp, const Ptrs& P, int max_iter, int ncu,
-                     hipStream_t st, Ctrl* fin, bool noalloc, const std::function<int()>& tail) {
-    int dev = 0;
-    GPSPCA_HIP(hipGetDevice(&dev));
+                     int dev, hipStream_t st, Ctrl* fin, bool noalloc,
+                     const std::function<int()>& tail) {
     Ctrl stack_snap;
     Ctrl* snap = &stack_snap;
     int rc = noalloc ? GPSPCA_OK : pinned_ctrl(&snap);
     if (rc) return rc;
-    // GPSPCA_SMALL_WAIT: the barriers' limit in ticks of the 100 MHz clock (tests)
-    const char* we = std::getenv("GPSPCA_SMALL_WAIT");
-    const int64_t wait = we ? std::atoll(we) : 200000000;
+    const int64_t wait = small_wait();
     SmallRoom room(pl.small_nb, ncu, dev);
     uint32_t bar0 = 0;
     for (int kk = 0; kk < max_iter; kk += kSmallChunk) {
@@ -979,6 +1005,7 @@ static int run_small(const Plan& pl, const PassParams& pp, const Ptrs& P, int ma
     GPSPCA_HIP(hipMemcpyAsync(snap, P.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
     GPSPCA_HIP(hipStreamSynchronize(st));
     *fin = *snap;
+    if (pl.small_nb > 1) t_retreat[dev].ended(snap->abort != 0, wait);
     return snap->abort ? kSmallAborted : GPSPCA_OK;
 }
 
@@ -1072,8 +1099,8 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
                float* X, float* Z, uint32_t* support, double* obj_trace, int* n_iter,
                int* status_out, const double* norms_in, int multistart, const double* defl_q,
                int defl_k, int exact, int noalloc, int no_small) {
-    int ncu = 0;
-    int rc = device_cus(&ncu);
+    int ncu = 0, dev = 0;
+    int rc = device_cus(&ncu, &dev);
     if (rc) return rc;
     const int pform = path ? (form == GPSPCA_SL0 ? GPSPCA_BL0 : GPSPCA_BL1) : form;
     Plan pl;
@@ -1084,8 +1111,9 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     pl.exact = (exact && !path) ? 1 : 0;
     if (!no_small && small_enabled(A, m, path)) {
         pl.small_nb = small_workgroups(pl, &pl.small_whole);
-        if (small_cus(pl.small_nb, ncu) > small_room(ncu) ||
-            (pl.small_nb > 1 && !all_cus(st, ncu)))
+        if (pl.small_nb > 1 &&
+            (small_cus(pl.small_nb, ncu) > small_room(ncu) || !all_cus(st, ncu) ||
+             t_retreat[dev].holds(small_wait())))
             pl.small_nb = 0;
     }
     const Ptrs P = carve(pl, workspace);
@@ -1202,7 +1230,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     };
     Ctrl fin;
     if (pl.small_nb) {
-        rc = run_small(pl, pp, P, max_iter, ncu, st, &fin, noalloc != 0, outputs);
+        rc = run_small(pl, pp, P, max_iter, ncu, dev, st, &fin, noalloc != 0, outputs);
         if (rc == kSmallAborted)
             return solve_core(A, form, m, gamma, mu, gammas, path, mask, X0, tol, max_iter,
                               workspace, ws_bytes, st, X, Z, support, obj_trace, n_iter, status_out,

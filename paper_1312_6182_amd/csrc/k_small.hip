@@ -38,8 +38,9 @@
 //
 // The barriers need every workgroup resident.  The host admits no more
 // workgroups of such solves at once than the CUs of each XCD can hold, one per
-// CU, and none on a stream that is kept off some CUs (gpspca_abi.cpp), and a wait that lasts 2 s ends the kernel with
-// Ctrl::abort set: the host then runs the passes as separate launches.
+// CU, and none on a stream that is kept off some CUs (gpspca_abi.cpp), and a wait that lasts 100 ms ends the kernel
+// with Ctrl::abort set: the host then runs the passes as separate launches, and
+// the thread's next solves as well.
 #include "gpspca_internal.h"
 #include "retract.h"
 #include "storage.h"

@@ -180,7 +180,32 @@ def child_masked_stream(lib):
     assert lib.solve(M, 1, max_iter=4) >= 0 and _small(lib) == [1]
 
 
-@pytest.mark.parametrize("scenario", ["few_cus", "masked_stream"])
+def child_run_out(lib):
+    """A wait that ran out is not waited for again at once: the passes run as
+    launches, and so do the next 64 solves of that size or another; a second
+    run-out in a row doubles that, a solve that ends well ends it.  A limit longer
+    than the one that ran out is tried."""
+    M, other = lib.matrix(100, 1000), lib.matrix(150, 1600)
+
+    def solve(A=M, abort=0):
+        lib.result(1, abort=abort)
+        assert lib.solve(A, 1, max_iter=4) >= 0
+        names = lib.names()
+        return sum("k_small" in k for k in names), sum("k_pass_m1" in k for k in names)
+
+    assert solve() == (1, 0)
+    for quiet in (64, 128, 256):
+        assert solve(abort=1) == (1, 4)
+        for i in range(quiet):
+            assert solve(other if i % 2 else M) == (0, 4), (quiet, i)
+    assert solve() == (1, 0) and solve() == (1, 0)
+    assert solve(abort=1) == (1, 4)
+    assert solve() == (0, 4)
+    os.environ["GPSPCA_SMALL_WAIT"] = str(1 << 40)
+    assert solve() == (1, 0)
+
+
+@pytest.mark.parametrize("scenario", ["few_cus", "masked_stream", "run_out"])
 def test_persistent_solves_need_their_cus(stub, scenario):
     _child(stub, scenario)
 
