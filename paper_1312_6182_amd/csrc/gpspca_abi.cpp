@@ -913,6 +913,12 @@ static bool all_cus(hipStream_t st, int ncu) {
     return on >= ncu;
 }
 
+static bool stream_busy(hipStream_t st) {
+    const hipError_t e = hipStreamQuery(st);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e != hipSuccess;
+}
+
 // Admission of the persistent solves (k_small.hip) of this process: their
 // workgroups wait for each other, so all of a solve's must be resident at once.
 // The solves in flight on a device never hold more CUs than its XCDs have (a
@@ -979,14 +985,18 @@ static thread_local SmallRetreat t_retreat[64];
 constexpr int kSmallChunk = 256;
 constexpr int kSmallAborted = 1000;   // internal: run the passes as separate launches
 
+// queued: earlier work of others was in the stream when the solve began.
 static int run_small(const Plan& pl, const PassParams& pp, const Ptrs& P, int max_iter, int ncu,
-                     int dev, hipStream_t st, Ctrl* fin, bool noalloc,
+                     int dev, hipStream_t st, bool queued, Ctrl* fin, bool noalloc,
                      const std::function<int()>& tail) {
     Ctrl stack_snap;
     Ctrl* snap = &stack_snap;
     int rc = noalloc ? GPSPCA_OK : pinned_ctrl(&snap);
     if (rc) return rc;
     const int64_t wait = small_wait();
+    // the room is not held while the solve waits behind that work, which may take
+    // long or depend on a solve of another thread
+    if (queued && pl.small_nb > 1) GPSPCA_HIP(hipStreamSynchronize(st));
     SmallRoom room(pl.small_nb, ncu, dev);
     uint32_t bar0 = 0;
     for (int kk = 0; kk < max_iter; kk += kSmallChunk) {
@@ -1093,12 +1103,13 @@ static const char* status_text(int s) {
 //  server caches them with a resident matrix).
 //  multistart (path, no X0): problem j starts at the normalized column of the
 //  j-th largest norm instead of all at the largest.
+//  route: kRouteIdle, kRouteLaunches.
 int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const double* mu,
                const double* gammas, int path, const uint32_t* mask, const float* X0,
                double tol, int max_iter, void* workspace, size_t ws_bytes, hipStream_t st,
                float* X, float* Z, uint32_t* support, double* obj_trace, int* n_iter,
                int* status_out, const double* norms_in, int multistart, const double* defl_q,
-               int defl_k, int exact, int noalloc, int no_small) {
+               int defl_k, int exact, int noalloc, int route) {
     int ncu = 0, dev = 0;
     int rc = device_cus(&ncu, &dev);
     if (rc) return rc;
@@ -1109,12 +1120,14 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     pl.defl_q = defl_q;
     pl.defl_k = defl_q ? defl_k : 0;
     pl.exact = (exact && !path) ? 1 : 0;
-    if (!no_small && small_enabled(A, m, path)) {
+    bool queued = false;
+    if (!(route & kRouteLaunches) && small_enabled(A, m, path)) {
         pl.small_nb = small_workgroups(pl, &pl.small_whole);
         if (pl.small_nb > 1 &&
             (small_cus(pl.small_nb, ncu) > small_room(ncu) || !all_cus(st, ncu) ||
              t_retreat[dev].holds(small_wait())))
             pl.small_nb = 0;
+        if (pl.small_nb > 1 && !(route & kRouteIdle)) queued = stream_busy(st);
     }
     const Ptrs P = carve(pl, workspace);
     PassParams pp = make_params(A, pl, gamma, mu, gammas);
@@ -1230,11 +1243,11 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     };
     Ctrl fin;
     if (pl.small_nb) {
-        rc = run_small(pl, pp, P, max_iter, ncu, dev, st, &fin, noalloc != 0, outputs);
+        rc = run_small(pl, pp, P, max_iter, ncu, dev, st, queued, &fin, noalloc != 0, outputs);
         if (rc == kSmallAborted)
             return solve_core(A, form, m, gamma, mu, gammas, path, mask, X0, tol, max_iter,
                               workspace, ws_bytes, st, X, Z, support, obj_trace, n_iter, status_out,
-                              norms_in, multistart, defl_q, defl_k, exact, noalloc, 1);
+                              norms_in, multistart, defl_q, defl_k, exact, noalloc, kRouteLaunches);
     } else {
         rc = run_passes(pl, pp, P, max_iter, tol, st, &fin, noalloc != 0, &outputs);
     }
@@ -1554,6 +1567,9 @@ int gpspca_solve_deflated(const gpspca_matrix* A, int form, int m, double gamma,
     make_plan(A, form, 1, max_iter, ncu, &p1);
     int worst = GPSPCA_OK;
     for (int k = 0; k < m; ++k) {
+        // after the first component's solve, which waits for the stream, only the
+        // launches below are in it
+        const int route = k > 0 ? kRouteIdle : 0;
         const float* start = nullptr;
         if (k > 0) {
             // default start of the deflated matrix: its column of largest norm,
@@ -1571,7 +1587,7 @@ int gpspca_solve_deflated(const gpspca_matrix* A, int form, int m, double gamma,
         rc = solve_core(A, form, 1, gamma, nullptr, nullptr, 0, nullptr, start, tol, max_iter,
                         workspace, core, st, X + (size_t)k * P, Z + (size_t)k * A->n,
                         support + (size_t)k * words, obj_trace + (size_t)k * max_iter,
-                        &n_iter[k], nullptr, nullptr, 0, k > 0 ? Q : nullptr, k);
+                        &n_iter[k], nullptr, nullptr, 0, k > 0 ? Q : nullptr, k, 0, 0, route);
         if (rc < 0) return rc;
         status[k] = rc;
         if (rc > worst) worst = rc;

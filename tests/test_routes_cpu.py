@@ -205,7 +205,40 @@ def child_run_out(lib):
     assert solve() == (1, 0)
 
 
-@pytest.mark.parametrize("scenario", ["few_cus", "masked_stream", "run_out"])
+def child_queued(lib):
+    """Solves that wait behind long work of their own streams keep nobody from
+    starting: four of 64 workgroups, whose streams move on only when a fifth one on
+    an idle stream has ended."""
+    import threading
+    ended = threading.Event()
+    streams = [0x10000 * (i + 1) for i in range(4)]
+    wait = ctypes.CFUNCTYPE(None, ctypes.c_void_p)(
+        lambda st: st in streams and (ended.wait(60) or os._exit(3)))
+    lib.stub.stub_on_sync(wait)
+    for st in streams:
+        lib.stub.stub_busy(ctypes.c_void_p(st))
+    M = lib.matrix(16, 60000)
+    rc = [None] * 5
+
+    def run(i, stream):
+        rc[i] = lib.solve(M, 1, max_iter=4, stream=stream)
+
+    ts = [threading.Thread(target=run, args=(i, st)) for i, st in enumerate(streams)]
+    for t in ts:
+        t.start()
+        t.join(0.3)          # it launches its passes, or waits
+        assert t.is_alive()
+    last = threading.Thread(target=run, args=(4, None), daemon=True)
+    last.start()
+    last.join(20)
+    assert not last.is_alive(), "an idle stream's solve waits for queued ones"
+    ended.set()
+    for t in ts:
+        t.join()
+    assert min(rc) >= 0 and _small(lib) == [64] * 5
+
+
+@pytest.mark.parametrize("scenario", ["few_cus", "masked_stream", "run_out", "queued"])
 def test_persistent_solves_need_their_cus(stub, scenario):
     _child(stub, scenario)
 
