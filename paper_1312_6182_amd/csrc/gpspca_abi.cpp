@@ -1232,7 +1232,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     char* const stage_ps = static_cast<char*>(stage) + sizeof(double) * trace_n;
     const std::function<int()> outputs = [&]() -> int {
         GPSPCA_HIP(launch_copy_x_last(pl, P.x[0], P.x[1], P.ctrl, X, st));
-        GPSPCA_HIP(launch_finalize(pl, P.S, P.fin, P.invn, Z, support, st));
+        GPSPCA_HIP(launch_finalize(pl, P.S, P.fin, P.invn, Z, support, P.ctrl, st));
         if (stage && trace_n)
             GPSPCA_HIP(hipMemcpyAsync(stage, P.trace, sizeof(double) * trace_n,
                                       hipMemcpyDeviceToHost, st));
@@ -1446,7 +1446,7 @@ int gpspca_step(const gpspca_matrix* A, int form, int m, double gamma, const dou
     TimedLaunches tl;
     rc = enqueue_pass(pl, pp, P, 0, st, tl);
     if (rc) return rc;
-    if (S) GPSPCA_HIP(launch_finalize(pl, P.S, P.fin, nullptr, S, nullptr, st));
+    if (S) GPSPCA_HIP(launch_finalize(pl, P.S, P.fin, nullptr, S, nullptr, nullptr, st));
     if (G)
         GPSPCA_HIP(hipMemcpyAsync(G, P.g64, sizeof(double) * m * A->p, hipMemcpyDeviceToDevice, st));
     std::vector<double> host(2 * (size_t)m);

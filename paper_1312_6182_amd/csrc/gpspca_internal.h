@@ -295,7 +295,7 @@ hipError_t launch_topm(const Plan& pl, const double* norms, double* cand_v, int6
 hipError_t launch_gather(const Plan& pl, const PassParams& pp, const int64_t* idx, double* g64,
                          hipStream_t st);
 hipError_t launch_finalize(const Plan& pl, const float* S, double* fin, double* invn, float* Z,
-                           uint32_t* support, hipStream_t st);
+                           uint32_t* support, const Ctrl* ctrl, hipStream_t st);
 hipError_t launch_copy_x(const Plan& pl, const float* Xint, float* Xout, hipStream_t st);
 // X_{n_iter - 1} (Xa when n_iter is odd, Xb when even, read from ctrl on the
 // device) -> Xout (leading dim p)

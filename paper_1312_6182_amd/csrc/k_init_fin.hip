@@ -287,7 +287,9 @@ hipError_t launch_gather(const Plan& pl, const PassParams& pp, const int64_t* id
 // m = 16.
 __global__ __launch_bounds__(256) void k_fin_support(int64_t n, int m, const float* __restrict__ S,
                                                      uint32_t* __restrict__ support,
-                                                     double* __restrict__ fin) {
+                                                     double* __restrict__ fin,
+                                                     const Ctrl* __restrict__ ctrl) {
+    if (ctrl && ctrl->abort) return;
     __shared__ double red[256];
     const int t = threadIdx.x;
     const int wpb = 256 / m, j = t % m, k = t / m;
@@ -344,7 +346,9 @@ __global__ __launch_bounds__(256) void k_fin_norm(int m, int nblk, const double*
 // values.
 __global__ __launch_bounds__(256) void k_fin_z(int64_t n, int m, const float* __restrict__ S,
                                                const double* __restrict__ invn,
-                                               float* __restrict__ Z) {
+                                               float* __restrict__ Z,
+                                               const Ctrl* __restrict__ ctrl) {
+    if (ctrl && ctrl->abort) return;
     __shared__ float tile[64 * (kMaxM + 1)];
     const int t = threadIdx.x;
     const int64_t i0 = (int64_t)blockIdx.x * 64;
@@ -361,16 +365,18 @@ __global__ __launch_bounds__(256) void k_fin_z(int64_t n, int m, const float* __
     }
 }
 
+// ctrl (may be NULL): of a solve whose persistent kernel may have given up.  It runs
+// again then, and its start X0 may lie in an output: nothing is written.
 hipError_t launch_finalize(const Plan& pl, const float* S, double* fin, double* invn, float* Z,
-                           uint32_t* support, hipStream_t st) {
+                           uint32_t* support, const Ctrl* ctrl, hipStream_t st) {
     if (invn) {
         hipLaunchKernelGGL(k_fin_support, dim3(pl.fin_grid), dim3(256), 0, st, pl.n, pl.m, S,
-                           support, fin);
+                           support, fin, ctrl);
         hipLaunchKernelGGL(k_fin_norm, dim3(pl.m), dim3(256), 0, st, pl.m, pl.fin_grid, fin, invn);
     }
     if (Z)
         hipLaunchKernelGGL(k_fin_z, dim3((unsigned)((pl.n + 63) / 64)), dim3(256), 0, st, pl.n,
-                           pl.m, S, invn, Z);
+                           pl.m, S, invn, Z, ctrl);
     return hipGetLastError();
 }
 
@@ -383,12 +389,13 @@ __global__ void k_copy_x(int m, int p, int ldx, const float* __restrict__ Xi, fl
 }
 
 // The same from the iterate of the last pass, X_{n_iter - 1}, which sits in
-// Xa (n_iter odd) or Xb (n_iter even); nothing when no pass was made.
+// Xa (n_iter odd) or Xb (n_iter even); nothing when no pass was made or the
+// persistent kernel gave up.
 __global__ void k_copy_x_last(int m, int p, int ldx, const float* __restrict__ Xa,
                               const float* __restrict__ Xb, const Ctrl* __restrict__ ctrl,
                               float* __restrict__ Xo) {
     const int ni = ctrl->n_iter;
-    if (ni < 1) return;
+    if (ni < 1 || ctrl->abort) return;
     const float* Xi = ((ni - 1) & 1) ? Xb : Xa;
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (int64_t)m * p) return;

@@ -1,4 +1,6 @@
 """Faults that were found in the kernels and their dispatch, one test each."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -117,3 +119,38 @@ def test_persistent_solves_keep_the_launches_accuracy(gpu, p, n, kind, m, pad, m
     ratio = [(a / b) ** 0.5 for a, b in zip(err["1"], err["0"])]
     print(f"\n[accuracy] {kind}{m} p={p} n={n} X {ratio[0]:.3f} Z {ratio[1]:.3f}", flush=True)
     assert max(ratio) <= 1.07
+
+
+@pytest.mark.parametrize("p,n,m", [(100, 1000, 1), (200, 2000, 5)])
+def test_start_inside_an_output_survives_a_given_up_solve(gpu, p, n, m, monkeypatch):
+    """X0 is read before anything is written, so it may lie in the buffer of an
+    output.  A persistent solve that gives up (its barriers may not wait here) runs
+    again from X0 and must not have written its outputs."""
+    A = to_device(W.planted_block(p, n, 2, 3, k=30)[0])
+    M = gpu.matrix(A)
+    form, gamma, iters = (O.SL1 if m == 1 else O.BL1), 0.08 * float(A.norm(dim=0).max()), 6
+    X0 = x_to_device(fp32_round(W.random_orthonormal(p, m, 4)))
+    want = gpu.solve(A, form, m, gamma, X0=X0, tol=0.0, max_iter=iters)
+    ws = torch.empty(gpu.workspace_bytes(A, form, m, iters) + 256, dtype=torch.uint8, device="cuda")
+    ws = ws[(-ws.data_ptr()) % 256:]
+    words = (n + 31) // 32
+    for wait in ("0", None):
+        monkeypatch.delenv("GPSPCA_SMALL_WAIT", raising=False)
+        if wait is not None:
+            monkeypatch.setenv("GPSPCA_SMALL_WAIT", wait)
+        for place in range(2):
+            X = torch.empty((m, p), device="cuda")
+            Z = torch.empty((m, n), device="cuda")
+            sup = torch.empty((m, words), dtype=torch.int32, device="cuda")
+            at = (X, Z)[place].view(-1)[:m * p]
+            at.copy_(X0.t().reshape(-1))
+            nit = ctypes.c_int(0)
+            trace = (ctypes.c_double * iters)()
+            rc = gpu.load().gpspca_solve(ctypes.byref(M), form, m, gamma, None, at.data_ptr(), 0.0,
+                                         iters, ws.data_ptr(), ws.numel(),
+                                         torch.cuda.current_stream().cuda_stream, X.data_ptr(),
+                                         Z.data_ptr(), sup.data_ptr(), trace, ctypes.byref(nit))
+            assert rc == gpu.MAXITER and nit.value == iters
+            np.testing.assert_allclose(list(trace), want.trace, rtol=1e-5)
+            assert float((X.t() - want.X).norm() / want.X.norm()) <= 1e-5
+            assert float((Z.t() - want.Z).norm() / want.Z.norm()) <= 1e-5
