@@ -392,7 +392,8 @@ const char* gpspca_version(void);
  * times launches of its dominant (A-streaming) correlation kernel with a pair
  * of HIP events that the launch itself records at the kernel's start and end
  * (hipExtLaunchKernelGGL): the first launch of each solve and every on-th one
- * after it (on = 1: every launch).  on <= 0 disables timing.
+ * after it (on = 1: every launch).  on <= 0 disables timing.  A small solve
+ * whose passes are one persistent launch reports that launch (k_small).
  * gpspca_profile_read returns the summed duration (ms) of the timed launches,
  * their count, and the name of the kernel, then resets the counters.  Solves
  * whose correlation runs as several launches (the vector-ALU fallback for

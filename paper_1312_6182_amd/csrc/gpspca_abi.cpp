@@ -460,9 +460,9 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
     pl->total = o;
 }
 
-// Whether a solve may run as one persistent kernel: not while launches are timed
-// or when a kernel, a tuned configuration or the graph setting was asked for
-// (those name the launches of a pass).  GPSPCA_SMALL=0 turns it off.
+// Whether a solve may run as one persistent kernel: not when a kernel, a tuned
+// configuration or the graph setting was asked for (those name the launches of a
+// pass).  GPSPCA_SMALL=0 turns it off.
 static bool small_enabled(const gpspca_matrix* A, int m, int path);
 
 // The plan of a solve in ws_bytes of workspace: the default configuration, or,
@@ -651,8 +651,7 @@ static bool small_enabled(const gpspca_matrix* A, int m, int path) {
     Tune tt;
     if (tn.kernel != kTuneDefault || tn.stages || tn.waves || tune_lookup(tune_key(A, m, path), &tt))
         return false;
-    std::lock_guard<std::mutex> lk(g_prof.mu);
-    return !g_prof.on;
+    return true;
 }
 
 thread_local KernelEvents g_kev;
@@ -997,13 +996,21 @@ static int run_small(const Plan& pl, const PassParams& pp, const Ptrs& P, int ma
     // the room is not held while the solve waits behind that work, which may take
     // long or depend on a solve of another thread
     if (queued && pl.small_nb > 1) GPSPCA_HIP(hipStreamSynchronize(st));
+    TimedLaunches tl;
+    if (!noalloc) {
+        std::lock_guard<std::mutex> lk(g_prof.mu);
+        tl.on = g_prof.on;
+        tl.every = g_prof.every;
+    }
     SmallRoom room(pl.small_nb, ncu, dev);
     uint32_t bar0 = 0;
     for (int kk = 0; kk < max_iter; kk += kSmallChunk) {
         const int c = std::min(kSmallChunk, max_iter - kk);
+        GPSPCA_HIP(tl.begin(st));
         GPSPCA_HIP(launch_small(pl, pp, P.x[0], P.x[1], P.S, P.gpart, P.fpart, P.nnzpart, P.g64,
                                 P.trace, P.coef + 5 * (size_t)pl.m * pl.m, P.pstate, P.ctrl, c,
                                 bar0, wait, st));
+        GPSPCA_HIP(tl.end(st));
         bar0 += (uint32_t)c * (uint32_t)pl.small_nb * (pl.small_whole ? 1u : 2u);
         if (kk + c >= max_iter) break;
         GPSPCA_HIP(hipMemcpyAsync(snap, P.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
@@ -1014,6 +1021,7 @@ static int run_small(const Plan& pl, const PassParams& pp, const Ptrs& P, int ma
     if (rc) return rc;
     GPSPCA_HIP(hipMemcpyAsync(snap, P.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
     GPSPCA_HIP(hipStreamSynchronize(st));
+    tl.collect("k_small");
     *fin = *snap;
     if (pl.small_nb > 1) t_retreat[dev].ended(snap->abort != 0, wait);
     return snap->abort ? kSmallAborted : GPSPCA_OK;

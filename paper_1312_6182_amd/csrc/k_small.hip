@@ -874,7 +874,7 @@ hipError_t launch_small(const Plan& pl, const PassParams& pp, float* x0, float* 
             (const void*)k_small<ST, MB, BLOCK>, hipFuncAttributeMaxDynamicSharedMemorySize,   \
             kSmallLds);                                                                        \
         if (limit != hipSuccess) (void)hipGetLastError();                                      \
-        hipLaunchKernelGGL((k_small<ST, MB, BLOCK>), grid, block, lds, st, pp, a);             \
+        GPSPCA_LAUNCH_TIMED((k_small<ST, MB, BLOCK>), grid, block, lds, st, pp, a);            \
     } while (0)
 #define GPSPCA_SM(ST)                                              \
     do {                                                           \

@@ -154,3 +154,50 @@ def test_start_inside_an_output_survives_a_given_up_solve(gpu, p, n, m, monkeypa
             np.testing.assert_allclose(list(trace), want.trace, rtol=1e-5)
             assert float((X.t() - want.X).norm() / want.X.norm()) <= 1e-5
             assert float((Z.t() - want.Z).norm() / want.Z.norm()) <= 1e-5
+
+
+def _kernels(gpu, fn):
+    """(result of fn, dominant kernel, its timed launches) by the library's timing."""
+    gpu.profile_read()
+    gpu.profile_enable(True)
+    try:
+        r = fn()
+    finally:
+        gpu.profile_enable(False)
+    _, launches, name = gpu.profile_read()
+    return r, name, launches
+
+
+# (form, m, p, n, name as launches): solves of several workgroups, with one and with
+# two barriers a pass
+SMALL = [("SL1", 1, 100, 1000, "k_pass_m1"), ("SL1", 1, 400, 4000, "k_pass_m1"),
+         ("BL1", 5, 200, 2000, "k_corr_mfma"), ("multi", 4, 100, 1000, "k_corr_mfma")]
+
+
+@pytest.mark.parametrize("form,m,p,n,other", SMALL)
+def test_small_solves_take_the_persistent_kernel(gpu, form, m, p, n, other, monkeypatch):
+    """What ran, by the timing of launches, and with the timing on the same bits as
+    without: one k_small; after a barrier's wait that ran out the passes as
+    launches; k_small again with a longer limit; the launches alone when told so."""
+    A = to_device(W.planted_block(p, n, 2, 3, k=30)[0])
+    gamma, iters = 0.1 * float(A.norm(dim=0).max()), 7
+
+    def solve():
+        if form == "multi":
+            return gpu.solve_multistart(A, gpu.SL1, m, gamma, tol=0.0, max_iter=iters)
+        return gpu.solve(A, gpu.SL1 if m == 1 else gpu.BL1, m, gamma, tol=0.0, max_iter=iters)
+
+    plain = solve()
+    r, name, launches = _kernels(gpu, solve)
+    assert (name, launches) == ("k_small", 1) and torch.equal(r.X, plain.X)
+    monkeypatch.setenv("GPSPCA_SMALL_WAIT", "0")
+    r, name, launches = _kernels(gpu, solve)
+    assert (name, launches) == (other, 1 + iters)
+    assert float((r.X - plain.X).norm() / plain.X.norm()) <= 1e-5
+    r, name, launches = _kernels(gpu, solve)      # not tried again at once
+    assert (name, launches) == (other, iters)
+    monkeypatch.delenv("GPSPCA_SMALL_WAIT")
+    r, name, launches = _kernels(gpu, solve)
+    assert (name, launches) == ("k_small", 1) and torch.equal(r.X, plain.X)
+    monkeypatch.setenv("GPSPCA_SMALL", "0")
+    assert _kernels(gpu, solve)[1:] == (other, iters)
