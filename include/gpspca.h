@@ -287,7 +287,8 @@ int gpspca_quantize(const gpspca_matrix* A, int to, void* out, int64_t ldq, floa
 /*
  * Autotuner of the correlation kernel.  Times every candidate configuration
  * for this problem (kernel variant: LDS-staged or register-direct matrix-core
- * kernel, or X-in-registers VALU kernel; LDS stages; workgroups per CU) over
+ * kernel, or X-in-registers VALU kernel; LDS stages; workgroups per CU; for a
+ * small matrix the persistent kernel that runs every pass in one launch) over
  * `passes` passes of the iteration from the feasible start X0 (device p x m,
  * leading dim p), and records the fastest in a process-wide table (thread-safe)
  * that every later plan with the same storage type, m, p, n, alignment and kind

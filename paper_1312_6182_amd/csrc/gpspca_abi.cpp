@@ -23,6 +23,7 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <tuple>
 #include <string>
@@ -263,6 +264,7 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
                 tune_lookup(tune_key(A, m, path), &tt))
                 tn = tt;
         }
+        if (tn.kernel == kTuneLaunches) tn = Tune{kTuneDefault, 0, 0};
         const bool vx_ok = f32 && pl->vec4 && m >= 2 && m <= 8 && A->p <= 10240 && A->p >= 4 && !path;
         const bool mv_ok = f32 && pl->vec4 && m <= 16 && A->p >= 4;
         if (restricted) {}
@@ -460,10 +462,11 @@ static void make_plan(const gpspca_matrix* A, int form, int m, int max_iter, int
     pl->total = o;
 }
 
-// Whether a solve may run as one persistent kernel: not when a kernel, a tuned
-// configuration or the graph setting was asked for (those name the launches of a
-// pass).  GPSPCA_SMALL=0 turns it off.
-static bool small_enabled(const gpspca_matrix* A, int m, int path);
+// Whether a solve may run as one persistent kernel: not when a kernel or the graph
+// setting was asked for, or the autotuner chose launches (those name the launches
+// of a pass).  GPSPCA_SMALL=0 turns it off.
+// tuned: the autotuner's table is looked at.
+static bool small_enabled(const gpspca_matrix* A, int m, int path, bool tuned = true);
 
 // The plan of a solve in ws_bytes of workspace: the default configuration, or,
 // where only that one's buffers are too large, the leaner correlation kernel of
@@ -481,9 +484,12 @@ static void make_plan_fit(const gpspca_matrix* A, int form, int m, int max_iter,
 }
 
 // Configurations the autotuner tries for this problem (the default first).
-static std::vector<Tune> tune_candidates(const gpspca_matrix* A, int m, int path) {
+// small: the default is the persistent kernel.
+static std::vector<Tune> tune_candidates(const gpspca_matrix* A, int m, int path,
+                                         bool small = false) {
     std::vector<Tune> c;
     c.push_back(Tune{kTuneDefault, 0, 0});
+    if (small) c.push_back(Tune{kTuneLaunches, 0, 0});
     const bool vec = ((A->lda & 3) == 0) && ((reinterpret_cast<uintptr_t>(A->data) & 15) == 0);
     if (A->dtype != GPSPCA_F32) {
         c.push_back(Tune{kTuneQw, 8, 0});
@@ -644,14 +650,14 @@ struct Prof {
 };
 static Prof g_prof;
 
-static bool small_enabled(const gpspca_matrix* A, int m, int path) {
+static bool small_enabled(const gpspca_matrix* A, int m, int path, bool tuned) {
     const char* e = std::getenv("GPSPCA_SMALL");
     if ((e && e[0] == '0') || std::getenv("GPSPCA_GRAPH") || std::getenv("GPSPCA_BACKPROJ")) return false;
     const Tune tn = env_tune();
     Tune tt;
-    if (tn.kernel != kTuneDefault || tn.stages || tn.waves || tune_lookup(tune_key(A, m, path), &tt))
-        return false;
-    return true;
+    if (tn.kernel != kTuneDefault || tn.stages || tn.waves) return false;
+    return !tuned || !tune_lookup(tune_key(A, m, path), &tt) ||
+           (tt.kernel == kTuneDefault && tt.stages == 0 && tt.waves == 0);
 }
 
 thread_local KernelEvents g_kev;
@@ -980,6 +986,16 @@ struct SmallRetreat {
 };
 static thread_local SmallRetreat t_retreat[64];
 
+// The workgroups of the persistent kernel for the plan's solve on the stream (0: it
+// takes launches).
+static void small_route(Plan* pl, int ncu, int dev, hipStream_t st) {
+    pl->small_nb = small_workgroups(*pl, &pl->small_whole);
+    if (pl->small_nb > 1 &&
+        (small_cus(pl->small_nb, ncu) > small_room(ncu) || !all_cus(st, ncu) ||
+         t_retreat[dev].holds(small_wait())))
+        pl->small_nb = 0;
+}
+
 // Passes of one k_small launch: a long solve is cut so that the host sees it end.
 constexpr int kSmallChunk = 256;
 constexpr int kSmallAborted = 1000;   // internal: run the passes as separate launches
@@ -1130,11 +1146,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     pl.exact = (exact && !path) ? 1 : 0;
     bool queued = false;
     if (!(route & kRouteLaunches) && small_enabled(A, m, path)) {
-        pl.small_nb = small_workgroups(pl, &pl.small_whole);
-        if (pl.small_nb > 1 &&
-            (small_cus(pl.small_nb, ncu) > small_room(ncu) || !all_cus(st, ncu) ||
-             t_retreat[dev].holds(small_wait())))
-            pl.small_nb = 0;
+        small_route(&pl, ncu, dev, st);
         if (pl.small_nb > 1 && !(route & kRouteIdle)) queued = stream_busy(st);
     }
     const Ptrs P = carve(pl, workspace);
@@ -1643,12 +1655,15 @@ int gpspca_quantize(const gpspca_matrix* A, int to, void* out, int64_t ldq, floa
 namespace gpspca {
 
 // Time `passes` passes of configuration `tn` (after one untimed pass) from the
-// feasible start X0.  Returns GPSPCA_ENOMEM when the workspace is too small.
+// feasible start X0; small_nb > 0: as one launch of the persistent kernel.  Returns
+// GPSPCA_ENOMEM when the workspace is too small or the kernel gave up.
 static int time_config(const gpspca_matrix* A, int pform, int m, double gamma, int path,
                        const Tune& tn, const float* X0, int passes, void* ws, size_t ws_bytes,
-                       hipStream_t st, int ncu, float* ms) {
+                       hipStream_t st, int ncu, int dev, int small_nb, int small_whole, float* ms) {
     Plan pl;
     make_plan(A, pform, m, passes + 1, ncu, &pl, path, 0, &tn);
+    pl.small_nb = small_nb;
+    pl.small_whole = small_whole;
     if (ws_bytes < pl.total) return GPSPCA_ENOMEM;
     const Ptrs P = carve(pl, ws);
     std::vector<double> gam(m, gamma);
@@ -1672,7 +1687,20 @@ static int time_config(const gpspca_matrix* A, int pform, int m, double gamma, i
         GPSPCA_HIP(launch_x_interleave(pl, P.x[0], P.xil[0], st));
     }
     TimedLaunches tl;
-    int rc = enqueue_pass(pl, pp, P, 0, st, tl);
+    std::unique_ptr<SmallRoom> room;
+    uint32_t arrived = 0;
+    auto small = [&](int count) -> int {
+        GPSPCA_HIP(launch_small(pl, pp, P.x[0], P.x[1], P.S, P.gpart, P.fpart, P.nnzpart, P.g64,
+                                P.trace, P.coef + 5 * (size_t)m * m, P.pstate, P.ctrl, count,
+                                arrived, small_wait(), st));
+        arrived += (uint32_t)count * (uint32_t)pl.small_nb * (pl.small_whole ? 1u : 2u);
+        return GPSPCA_OK;
+    };
+    if (small_nb) {
+        GPSPCA_HIP(hipStreamSynchronize(st));   // nothing else is waited for in the room
+        room = std::make_unique<SmallRoom>(small_nb, ncu, dev);
+    }
+    int rc = small_nb ? small(1) : enqueue_pass(pl, pp, P, 0, st, tl);
     if (rc) return rc;
     hipEvent_t a = nullptr, b = nullptr;
     GPSPCA_HIP(hipEventCreate(&a));
@@ -1682,7 +1710,8 @@ static int time_config(const gpspca_matrix* A, int pform, int m, double gamma, i
         return fail(GPSPCA_EDEVICE, hipGetErrorString(e));
     }
     e = hipEventRecord(a, st);
-    for (int k = 1; k <= passes && e == hipSuccess && rc == GPSPCA_OK; ++k)
+    if (small_nb && e == hipSuccess) rc = small(passes);
+    for (int k = 1; k <= passes && !small_nb && e == hipSuccess && rc == GPSPCA_OK; ++k)
         rc = enqueue_pass(pl, pp, P, k, st, tl);
     if (e == hipSuccess) e = hipEventRecord(b, st);
     if (e == hipSuccess) e = hipEventSynchronize(b);
@@ -1692,11 +1721,21 @@ static int time_config(const gpspca_matrix* A, int pform, int m, double gamma, i
     if (rc) return rc;
     if (e != hipSuccess) return fail(GPSPCA_EDEVICE, hipGetErrorString(e));
     *ms /= (float)passes;
+    if (small_nb) {
+        Ctrl end;
+        GPSPCA_HIP(hipMemcpyAsync(&end, P.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+        GPSPCA_HIP(hipStreamSynchronize(st));
+        if (end.abort) return GPSPCA_ENOMEM;
+    }
     return GPSPCA_OK;
 }
 
 static std::string tune_text(const Plan& pl) {
     char b[96];
+    if (pl.small_nb) {
+        std::snprintf(b, sizeof(b), "k_small workgroups=%d", pl.small_nb);
+        return b;
+    }
     const char* k = pl.fused_m1 ? "k_pass_m1" : pl.use_vx ? "k_corr_vx"
                   : pl.use_sh ? "k_corr_sh"
                   : pl.use_x3 ? "k_corr_x3"
@@ -1727,30 +1766,41 @@ int gpspca_autotune(const gpspca_matrix* A, int form, int m, double gamma, const
     if (passes < 1 || passes > 1000) return fail(GPSPCA_EINVAL, "need 1 <= passes <= 1000");
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return fail(GPSPCA_EINVAL, "workspace must be non-NULL and 256-byte aligned");
-    int ncu = 0;
-    rc = device_cus(&ncu);
+    int ncu = 0, dev = 0;
+    rc = device_cus(&ncu, &dev);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int pform = path ? (form == GPSPCA_SL0 ? GPSPCA_BL0 : GPSPCA_BL1) : form;
-    const std::vector<Tune> cand = tune_candidates(A, m, path);
+    // whether an untuned solve takes the persistent kernel
+    const TuneKey key = tune_key(A, m, path);
+    Plan def;
+    const Tune deft{kTuneDefault, 0, 0};
+    make_plan(A, pform, m, passes + 1, ncu, &def, path, 0, &deft);
+    if (small_enabled(A, m, path, false)) small_route(&def, ncu, dev, st);
+    const std::vector<Tune> cand = tune_candidates(A, m, path, def.small_nb > 0);
     int timed = 0, best = -1;
     float best_t = 0.f;
     for (size_t i = 0; i < cand.size(); ++i) {
         float t = 0.f;
         rc = time_config(A, pform, m, gamma, path, cand[i], X0, passes, workspace, ws_bytes, st,
-                         ncu, &t);
+                         ncu, dev, i == 0 ? def.small_nb : 0, def.small_whole, &t);
         if (rc == GPSPCA_ENOMEM) continue;
         if (rc) return rc;
         ++timed;
-        if (best < 0 || t < best_t) { best = (int)i; best_t = t; }
+        // a solve by launches also pays for their capture and enqueuing, which is not in
+        // the time of its passes: at 400 x 4000, m = 1, both take 14.6 us a pass and
+        // solves of 10 to 60 passes 1.1 times as long by launches
+        const float worth = best == 0 && def.small_nb ? 1.1f * t : t;
+        if (best < 0 || worth < best_t) { best = (int)i; best_t = t; }
     }
     if (best < 0) return fail(GPSPCA_ENOMEM, "workspace too small for every configuration");
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tune[tune_key(A, m, path)] = cand[best];
+        g_tune[key] = cand[best];
     }
     Plan pl;
     make_plan(A, pform, m, passes + 1, ncu, &pl, path, 0, &cand[best]);
+    if (best == 0) pl.small_nb = def.small_nb;
     if (n_timed) *n_timed = timed;
     if (best_ms) *best_ms = best_t;
     if (best_desc && desc_len) std::snprintf(best_desc, desc_len, "%s", tune_text(pl).c_str());

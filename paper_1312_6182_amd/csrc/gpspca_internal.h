@@ -74,7 +74,8 @@ struct BalArgs {
 
 // A configuration of the correlation kernel: the autotuner's unit of choice.
 enum TuneKernel { kTuneDefault = 0, kTuneMfma = 1, kTuneVx = 2, kTuneValu = 3, kTuneRd = 4,
-                  kTuneWg = 5, kTuneRd128 = 6, kTuneX3 = 7, kTuneQw = 8, kTuneSh = 9 };
+                  kTuneWg = 5, kTuneRd128 = 6, kTuneX3 = 7, kTuneQw = 8, kTuneSh = 9,
+                  kTuneLaunches = 10 };   // the default as launches of its own (not k_small)
 struct Tune {
     int kernel;            // TuneKernel
     int stages;            // LDS stages (matrix-core kernels), 0 = default

@@ -23,12 +23,16 @@ struct State {
     std::string log;
     int cus = 256, masked = 0;   // CUs of the device; of them closed to every stream
     gpspca::Ctrl ctrl;
-    dim3 grid, block;
-    size_t shm = 0;
-    hipStream_t stream = nullptr;
+    float first_ms = 1.f, later_ms = 1.f;     // measured times: the first one, the others
     void (*on_sync)(hipStream_t) = nullptr;   // called by hipStreamSynchronize
     std::set<hipStream_t> busy;               // streams with unfinished work
 };
+struct Pushed {   // the thread's configuration between push and pop
+    dim3 grid, block;
+    size_t shm;
+    hipStream_t stream;
+};
+thread_local Pushed t_pushed;
 State& S() {
     static State* s = new State;
     return *s;
@@ -65,6 +69,10 @@ void stub_result(int n_iter, int status, int abort) {
     S().ctrl.status = status;
     S().ctrl.abort = abort;
 }
+void stub_times(float first, float later) {
+    S().first_ms = first;
+    S().later_ms = later;
+}
 void stub_on_sync(void (*f)(hipStream_t)) { S().on_sync = f; }
 void stub_busy(hipStream_t st) { S().busy.insert(st); }
 size_t stub_log(char* out, size_t len) {
@@ -85,19 +93,14 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
 }
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t shm, hipStream_t st) {
-    std::lock_guard<std::mutex> lk(S().mu);   // one launching thread at a time in the tests
-    S().grid = g;
-    S().block = b;
-    S().shm = shm;
-    S().stream = st;
+    t_pushed = Pushed{g, b, shm, st};
     return hipSuccess;
 }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* shm, hipStream_t* st) {
-    std::lock_guard<std::mutex> lk(S().mu);
-    *g = S().grid;
-    *b = S().block;
-    *shm = S().shm;
-    *st = S().stream;
+    *g = t_pushed.grid;
+    *b = t_pushed.block;
+    *shm = t_pushed.shm;
+    *st = t_pushed.stream;
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t shm, hipStream_t st) {
@@ -153,7 +156,11 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCre
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+    *ms = S().first_ms;
+    S().first_ms = S().later_ms;
+    return hipSuccess;
+}
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { *g = nullptr; return hipSuccess; }
 hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {

@@ -201,3 +201,27 @@ def test_small_solves_take_the_persistent_kernel(gpu, form, m, p, n, other, monk
     assert (name, launches) == ("k_small", 1) and torch.equal(r.X, plain.X)
     monkeypatch.setenv("GPSPCA_SMALL", "0")
     assert _kernels(gpu, solve)[1:] == (other, iters)
+
+
+@pytest.mark.parametrize("form,m,p,n,other", SMALL)
+def test_autotuning_a_small_matrix_does_not_slow_it(gpu, form, m, p, n, other):
+    """Whole solves of these sizes are faster by the persistent kernel (1.1 to 2.4
+    times), so it is what the autotuner has to choose, and later solves give the bits
+    of untuned ones."""
+    A = to_device(W.planted_block(p, n, 2, 3, k=30)[0])
+    gamma = 0.1 * float(A.norm(dim=0).max())
+
+    def solve():
+        if form == "multi":
+            return gpu.solve_multistart(A, gpu.SL1, m, gamma, tol=0.0, max_iter=7)
+        return gpu.solve(A, gpu.SL1 if m == 1 else gpu.BL1, m, gamma, tol=0.0, max_iter=7)
+
+    plain = solve()
+    try:
+        rep = gpu.autotune(A, gpu.BL1 if form == "BL1" else gpu.SL1, m, gamma, passes=20)
+        print(f"\n[autotune] {form} m={m} {rep}", flush=True)
+        assert rep["choice"].startswith("k_small")
+        r, name, launches = _kernels(gpu, solve)
+        assert (name, launches) == ("k_small", 1) and torch.equal(r.X, plain.X)
+    finally:
+        gpu.autotune_clear()

@@ -89,6 +89,19 @@ class Lib:
                                      self.WS, nb, stream, self.OUT, self.OUT, self.OUT, trace,
                                      ctypes.byref(nit))
 
+    def autotune(self, M, m=1, form=None, times=(1.0, 1.0)):
+        """(configurations timed, description of the chosen one)"""
+        form = (self.L.SL1 if m == 1 else self.L.BL1) if form is None else form
+        self.stub.stub_times(ctypes.c_float(times[0]), ctypes.c_float(times[1]))
+        size = (self.lib.gpspca_path_workspace_bytes(ctypes.byref(M), m, 4)
+                if form == self.L.SL1 and m > 1 else
+                self.lib.gpspca_workspace_bytes(ctypes.byref(M), form, m, 4))
+        timed, desc = ctypes.c_int(0), ctypes.create_string_buffer(128)
+        rc = self.lib.gpspca_autotune(ctypes.byref(M), form, m, 0.1, self.OUT, 3, self.WS, size,
+                                      None, ctypes.byref(timed), None, desc, 128)
+        assert rc == 0, self.lib.gpspca_last_error()
+        return timed.value, desc.value.decode()
+
     def multistart(self, M, m, max_iter=1):
         nb = self.lib.gpspca_path_workspace_bytes(ctypes.byref(M), m, max_iter)
         nit, st = (ctypes.c_int * m)(), (ctypes.c_int * m)()
@@ -241,6 +254,42 @@ def child_queued(lib):
 @pytest.mark.parametrize("scenario", ["few_cus", "masked_stream", "run_out", "queued"])
 def test_persistent_solves_need_their_cus(stub, scenario):
     _child(stub, scenario)
+
+
+def child_autotune(lib):
+    """The autotuner times the persistent kernel of a small matrix beside the
+    launches and later solves take what won; a tuned default is no reason to
+    leave the kernel."""
+    for m, form, p, n in ((1, None, 100, 1000), (1, None, 400, 4000), (5, None, 200, 2000),
+                          (4, lib.L.SL1, 100, 1000)):
+        M = lib.matrix(p, n)
+
+        def kernels():
+            lib.launches()
+            rc = lib.multistart(M, m, 4) if form is not None else lib.solve(M, m, max_iter=4)
+            assert rc >= 0
+            return sum("k_small" in k for k in lib.names())
+
+        assert kernels() == 1
+        timed, desc = lib.autotune(M, m, form, times=(1.0, 2.0))
+        assert timed >= 2 and desc.startswith("k_small workgroups="), (timed, desc)
+        assert sum("k_small" in k for k in lib.names()) == 2     # untimed, timed
+        assert kernels() == 1
+        timed, desc = lib.autotune(M, m, form, times=(1.05, 1.0))
+        assert desc.startswith("k_small")    # launches have their own cost per solve
+        timed, desc = lib.autotune(M, m, form, times=(2.0, 1.0))
+        lib.launches()
+        assert "k_small" not in desc and kernels() == 0, (m, form, desc)
+        lib.lib.gpspca_autotune_clear()
+        assert kernels() == 1
+    # no persistent kernel: as many configurations as there are correlation kernels
+    assert lib.autotune(lib.matrix(5000, 50000))[0] == 1
+    lib.result(1, abort=1)       # it gave up: it is not chosen
+    assert "k_small" not in lib.autotune(lib.matrix(100, 1000), times=(1.0, 2.0))[1]
+
+
+def test_autotune_of_small_matrices(stub):
+    _child(stub, "autotune")
 
 
 if __name__ == "__main__":
