@@ -202,15 +202,26 @@ static int backproj_threshold(const gpspca_matrix* A, int m, int vec4, int restr
 //                   m > 32: 0.97 up to 4000, 1.17 at 6000, 1.3 at 10000
 //   FP32, unaligned m 2-4: 0.92 at 400, 1.04 at 2000, 1.6 at 5000; m 5-8: 0.9 up
 //                   to 800, 0.95 at 2000, 1.09 at 5000; m 9-16: 1.0 up to 800,
-//                   1.35 at 2000, 1.9 at 5000; m > 16: 1.04 at 100, 1.5 at 2000
+//                   1.35 at 2000, 1.9 at 5000; m > 16: 1.04 at 100, 1.5 at 2000;
+//                   off that shape m 2: 0.94 at 128 x 400000, m 5: 0.95 at 12000 x
+//                   12000, m 12 and 32: 0.93-0.95 at 40000 x 500
 //   bfloat16        0.97-1.05 up to 800, 1.03-1.16 above
 //   e4m3, m <= 32   0.97 up to 800, 1.02-1.07 at 2000-3200, 1.1-1.2 at 10000
+// Columns of up to 512 rows are a few stages of 16/8-bit codes, and X is staged for
+// them anew in every round of tiles: 0.85-0.93 at 64 x 200000, 0.88-0.94 at 256 x
+// 40000, 0.90-1.01 at 384 x 200000, 0.89-0.95 with more than 16 components at 400 x
+// 4000 and 8000; with up to 16, 1.0-1.08 at 200 x 3000 and 400 x 8000.  (Above 512
+// rows k_corr_sh is also the more accurate one.)
 static bool sh_default(const gpspca_matrix* A, int m, int vec4, int path) {
     const double e = (double)A->p * (double)A->n;
+    if (A->dtype != GPSPCA_F32 && A->p <= 512 && (m > 16 || A->p < 200 || A->n > 50 * A->p))
+        return false;
     if (A->dtype == GPSPCA_BF16) return true;
     if (A->dtype == GPSPCA_F8E4M3) return e >= 3e7;
     if (vec4) return m > 32 ? e >= 2.5e8 : m > 16 ? true : (m >= 5 || path) && e >= 4e7;
-    return m > 16 ? true : m > 8 ? e >= 1e7 : m > 4 ? e >= 9e7 : m >= 2 && e >= 4e7;
+    if (A->n < 1000) return false;
+    return m > 16 ? true : m > 8 ? e >= 1e7 : m > 4 ? e >= 9e7 && A->n >= 20000
+                                                    : m >= 2 && e >= 4e7 && A->p >= 400;
 }
 
 // ----------------------------------------------------------------------- plan

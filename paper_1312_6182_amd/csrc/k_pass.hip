@@ -972,6 +972,46 @@ __device__ __forceinline__ double sumsq16(const u4n& w) {
     }
 }
 
+// Short columns: a lane takes one quad of rows at a time, four columns in flight.
+template <bool VEC, int ST>
+__global__ __launch_bounds__(256) void k_colnorm_short(PassParams pp, double* __restrict__ norms) {
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t nw = (int64_t)gridDim.x * 4;
+    const int64_t cb = pp.n * wave / nw, ce = pp.n * (wave + 1) / nw;
+    const int p = pp.p, nqf = p >> 2, nq = (p + 3) >> 2;
+    constexpr int C = 4;
+    for (int64_t c0 = cb; c0 < ce; c0 += C) {
+        double s[C];
+        const void* colp[C];
+#pragma unroll
+        for (int b = 0; b < C; ++b) {
+            s[b] = 0.0;
+            colp[b] = column_ptr<ST>(pp, (c0 + b < ce) ? c0 + b : ce - 1);
+        }
+        for (int q = lane; q < nq; q += 64) {
+#pragma unroll
+            for (int b = 0; b < C; ++b) {
+                f4 a;
+                if constexpr (ST == kStF32)
+                    a = load_quad<VEC>(static_cast<const float*>(colp[b]), q, nqf, p);
+                else
+                    a = load_quad_st<ST>(colp[b], q, nqf, p);
+                s[b] += (double)a.x * a.x + (double)a.y * a.y + (double)a.z * a.z +
+                        (double)a.w * a.w;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < C; ++b) {
+            const double tot = wave_allreduce_sum(s[b]);
+            if (lane == 0 && c0 + b < ce) {
+                const double sc = (ST == kStF32) ? 1.0 : (double)column_scale(pp, c0 + b);
+                norms[c0 + b] = sc * sqrt(tot);
+            }
+        }
+    }
+}
+
 template <bool VEC, int ST>
 __global__ __launch_bounds__(256) void k_colnorm(PassParams pp, double* __restrict__ norms) {
     const int lane = threadIdx.x & 63;
@@ -1268,18 +1308,30 @@ hipError_t launch_backproj(const Plan& pl, const PassParams& pp, const float* S,
     return hipSuccess;
 }
 
+// k_colnorm needs columns that give every lane of a wave a 16-byte segment; below
+// that k_colnorm_short.  Whole calls, short / wide: 8-bit storage 57 / 131 us at 64 x
+// 200000, 54 / 79 at 512 x 100000, 73 / 81 at 1024 x 100000, 67 / 51 at 2048 x 50000;
+// 16 bits 60 / 98, 50 / 59, 70 / 63 and 68 / 51; FP32 65 / 72 at 64 x 200000, 30 / 32 at
+// 256 x 40000, 102 / 79 at 384 x 200000.
+template <bool VEC, int ST>
+static void launch_colnorm_t(const PassParams& pp, double* norms, int grid, hipStream_t st) {
+    constexpr int kShort = 64 * (ST == kStF32 ? 4 : ST == kStBF16 ? 8 : 16);
+    if (pp.p <= kShort)
+        hipLaunchKernelGGL((k_colnorm_short<VEC, ST>), dim3(grid), dim3(256), 0, st, pp, norms);
+    else
+        hipLaunchKernelGGL((k_colnorm<VEC, ST>), dim3(grid), dim3(256), 0, st, pp, norms);
+}
+
 hipError_t launch_colnorm(const PassParams& pp, int dtype, double* norms, int grid,
                           hipStream_t st) {
     if (dtype == GPSPCA_BF16) {
-        hipLaunchKernelGGL((k_colnorm<true, kStBF16>), dim3(grid), dim3(256), 0, st, pp, norms);
+        launch_colnorm_t<true, kStBF16>(pp, norms, grid, st);
     } else if (dtype == GPSPCA_F8E4M3) {
-        hipLaunchKernelGGL((k_colnorm<true, kStF8>), dim3(grid), dim3(256), 0, st, pp, norms);
+        launch_colnorm_t<true, kStF8>(pp, norms, grid, st);
     } else {
         const bool vec = ((pp.lda & 3) == 0) && ((reinterpret_cast<uintptr_t>(pp.A) & 15) == 0);
-        if (vec)
-            hipLaunchKernelGGL((k_colnorm<true, kStF32>), dim3(grid), dim3(256), 0, st, pp, norms);
-        else
-            hipLaunchKernelGGL((k_colnorm<false, kStF32>), dim3(grid), dim3(256), 0, st, pp, norms);
+        if (vec) launch_colnorm_t<true, kStF32>(pp, norms, grid, st);
+        else launch_colnorm_t<false, kStF32>(pp, norms, grid, st);
     }
     return hipGetLastError();
 }

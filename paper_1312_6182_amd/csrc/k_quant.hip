@@ -106,7 +106,7 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 // the first is used, 10 KB per wave in flight.  The loads are 16 bytes at any
 // 4-byte alignment; the codes of a quad are one store when the output allows
 // it (PK), bytes otherwise.  One wave holds a column of up to 2560 rows without
-// a barrier; longer ones take four.  The whole call at 10000 x 100000 to e4m3:
+// a barrier (four columns of up to 64 rows); longer ones take four.  The whole call at 10000 x 100000 to e4m3:
 // 0.96 ms, 5.2 TB/s of its 5 GB (2.65 ms with two passes of 4-byte loads and a
 // cleared output).
 template <int TO, int T, int KQ, bool PK>
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ A, i
                 for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fabsf(v[k][e]));
         }
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        for (int o = T < 64 ? T / 2 : 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
         if constexpr (T == 256) {
             if ((t & 63) == 0) red[t >> 6] = mx;
             __syncthreads();
@@ -842,7 +842,9 @@ static void launch_quantize_to(const float* A, int64_t lda, int p, int64_t n, vo
             hipLaunchKernelGGL((k_quantize<TO, TT, KK, false>), grid, block, 0, st, A, lda, p, \
                                n, out, ldq, scale);                                            \
     } while (0)
-    if (p <= 1024) GPSPCA_QZ(64, 4);
+    if (p <= 64) GPSPCA_QZ(16, 1);
+    else if (p <= 256) GPSPCA_QZ(64, 1);
+    else if (p <= 1024) GPSPCA_QZ(64, 4);
     else if (p <= 2560) GPSPCA_QZ(64, 10);
     else if (p <= 10240) GPSPCA_QZ(256, 10);
     else if (p <= 20480) GPSPCA_QZ(256, 20);

@@ -225,3 +225,46 @@ def test_autotuning_a_small_matrix_does_not_slow_it(gpu, form, m, p, n, other):
         assert (name, launches) == ("k_small", 1) and torch.equal(r.X, plain.X)
     finally:
         gpu.autotune_clear()
+
+
+@pytest.mark.parametrize("pad", [0, 3], ids=["packed", "bytes"])
+@pytest.mark.parametrize("to", [O.BF16, O.E4M3], ids=["bf16", "e4m3"])
+@pytest.mark.parametrize("p", [1, 3, 5, 60, 63, 64, 65, 252, 255, 256, 257])
+def test_quantize_short_columns(gpu, p, to, pad):
+    """Codes and scales bit for bit around the shapes of the shortest columns, with
+    columns past the last full workgroup and rows past p untouched."""
+    n = 37
+    A = W.gaussian(p, n, p)
+    A[:, 1] = 0.0
+    A[:, 2] *= 1e-39
+    ldq = (p + 15) // 16 * 16 + pad
+    es = 2 if to == O.BF16 else 1
+    out = torch.full((n, ldq * es), 0x5A, dtype=torch.uint8, device="cuda")
+    sc = torch.full((n,), -1.0, dtype=torch.float32, device="cuda")
+    M = gpu.matrix(to_device(A, lda=p + pad))
+    assert gpu.load().gpspca_quantize(ctypes.byref(M), int(to), out.data_ptr(), ldq, sc.data_ptr(),
+                                      torch.cuda.current_stream().cuda_stream) == 0
+    got = out.cpu().numpy()
+    got = got.view(np.uint16) if es == 2 else got
+    assert (got.view(np.uint8)[:, p * es:] == 0x5A).all()
+    ref, ref_sc = O.quantize(A, to, ldq=ldq)
+    np.testing.assert_array_equal(got[:, :p].T, ref[:p])
+    np.testing.assert_array_equal(sc.cpu().numpy(), ref_sc if to == O.E4M3 else np.ones(n))
+
+
+@pytest.mark.parametrize("p", [1, 4, 63, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025])
+def test_column_norms_of_short_columns(gpu, p):
+    """FP64 norms of every storage type around the lengths where the kernel changes."""
+    n = 133
+    A = W.gaussian(p, n, 70 + p)
+    ref = np.sqrt((A.astype(np.float64) ** 2).sum(axis=0))
+    for lda in (p | 1, (p + 3) // 4 * 4 + 4):
+        got = gpu.column_norms(to_device(A, lda=lda)).cpu().numpy()
+        np.testing.assert_allclose(got, ref, rtol=1e-14, atol=0)
+    for to in (O.BF16, O.E4M3):
+        Aq, sc = gpu.quantize(to_device(A), torch.bfloat16 if to == O.BF16
+                              else torch.float8_e4m3fn)
+        codes, scale = O.quantize(A, to)
+        deq = O.dequantize(codes, to, scale, p)
+        got = gpu.column_norms(Aq, col_scale=sc).cpu().numpy()
+        np.testing.assert_allclose(got, np.sqrt((deq ** 2).sum(axis=0)), rtol=1e-14, atol=0)

@@ -292,5 +292,33 @@ def test_autotune_of_small_matrices(stub):
     _child(stub, "autotune")
 
 
+def child_short_columns(lib):
+    """The kernels that short columns take: what was measured fastest for them."""
+    def norms(p, dtype):
+        assert lib.lib.gpspca_column_norms(ctypes.byref(lib.matrix(p, 1000, dtype)), lib.OUT,
+                                           None) == 0
+        return "short" in lib.names()[0]
+
+    for dtype, last in ((0, 256), (1, 512), (2, 1024)):
+        assert norms(last, dtype) and not norms(last + 1, dtype)
+
+    def corr(p, n, m, dtype):
+        assert lib.solve(lib.matrix(p, n, dtype), m, max_iter=1) >= 0
+        names = lib.names()
+        return [k for k in ("k_corr_sh", "k_corr_qw", "k_small") if any(k in x for x in names)]
+
+    for dtype in (1, 2):
+        assert corr(64, 200000, 5, dtype) == ["k_corr_qw"]
+        assert corr(256, 40000, 16, dtype) == ["k_corr_qw"]
+        assert corr(512, 200000, 17, dtype) == ["k_corr_qw"]
+        assert corr(600, 60000, 16, dtype) == ["k_corr_sh"]
+        assert corr(2000, 20000, 32, dtype) == ["k_corr_sh"]
+    assert corr(400, 8000, 16, 1) == ["k_corr_sh"]
+
+
+def test_short_columns(stub):
+    _child(stub, "short_columns")
+
+
 if __name__ == "__main__":
     globals()["child_" + sys.argv[1]](Lib(sys.argv[2]))
