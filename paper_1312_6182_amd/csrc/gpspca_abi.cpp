@@ -1464,7 +1464,7 @@ int gpspca_step(const gpspca_matrix* A, int form, int m, double gamma, const dou
     rc = device_cus(&ncu);
     if (rc) return rc;
     Plan pl;
-    make_plan(A, form, m, 1, ncu, &pl);
+    make_plan_fit(A, form, m, 1, ncu, &pl, 0, 0, ws_bytes);
     if (ws_bytes < pl.total) return fail(GPSPCA_ENOMEM, "workspace too small");
     const Ptrs P = carve(pl, workspace);
     PassParams pp = make_params(A, pl, gamma, mu);

@@ -320,5 +320,34 @@ def test_short_columns(stub):
     _child(stub, "short_columns")
 
 
+def child_workspace(lib):
+    """A step takes the workspace that a solve of one pass takes: where only the
+    default correlation's buffers are too large, the leaner one runs."""
+    ENOMEM = lib.L.ENOMEM
+    for p, n, dtype, m, odd in ((1001, 20001, 0, 12, True), (1003, 30000, 0, 64, False),
+                                (2000, 30000, 1, 16, False), (4000, 40000, 2, 8, False)):
+        M = lib.matrix(p, n, dtype, odd)
+
+        def step(nb):
+            return lib.lib.gpspca_step(ctypes.byref(M), lib.L.BL1, m, 0.1, None, lib.OUT, lib.WS,
+                                       nb, None, lib.OUT, None, None, None)
+
+        def solve(nb):
+            return lib.lib.gpspca_solve(ctypes.byref(M), lib.L.BL1, m, 0.1, None, None, 0.0, 1,
+                                        lib.WS, nb, None, lib.OUT, None, None, None, None)
+
+        lo, hi = 0, lib.lib.gpspca_workspace_bytes(ctypes.byref(M), lib.L.BL1, m, 1) // 256
+        assert solve(256 * hi) >= 0 and step(256 * hi) >= 0
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (lo, mid) if solve(256 * mid) >= 0 else (mid, hi)
+        assert step(256 * hi) >= 0, (p, n, m)
+        assert solve(256 * lo) == step(256 * lo) == ENOMEM
+
+
+def test_step_and_solve_take_the_same_workspace(stub):
+    _child(stub, "workspace")
+
+
 if __name__ == "__main__":
     globals()["child_" + sys.argv[1]](Lib(sys.argv[2]))
