@@ -268,3 +268,42 @@ def test_column_norms_of_short_columns(gpu, p):
         deq = O.dequantize(codes, to, scale, p)
         got = gpu.column_norms(Aq, col_scale=sc).cpu().numpy()
         np.testing.assert_allclose(got, np.sqrt((deq ** 2).sum(axis=0)), rtol=1e-14, atol=0)
+
+
+@pytest.mark.parametrize("store", ["f32", "odd", "bf16", "e4m3"])
+@pytest.mark.parametrize("m", [2, 5, 16, 17, 32, 33, 64])
+def test_forced_shared_x_kernel_is_the_one_that_runs(gpu, m, store, monkeypatch):
+    """GPSPCA_CORR_KERNEL=sh gives k_corr_sh for every storage type, alignment and
+    component group, except 8-bit codes with more than 32 components."""
+    monkeypatch.setenv("GPSPCA_CORR_KERNEL", "sh")
+    p, n = 203, 1500
+    A, scale = to_device(W.gaussian(p, n, m), lda=203 if store == "odd" else 204), None
+    if store in ("bf16", "e4m3"):
+        A, scale = gpu.quantize(A, torch.bfloat16 if store == "bf16" else torch.float8_e4m3fn)
+    _, name, launches = _kernels(gpu, lambda: gpu.solve(A, gpu.BL1, m, 0.5, tol=0.0, max_iter=3,
+                                                        col_scale=scale))
+    assert name == ("k_corr_qw" if store == "e4m3" and m > 32 else "k_corr_sh") and launches == 3
+
+
+@pytest.mark.parametrize("m", [1, 2, 5, 8, 9, 16, 17, 32, 33, 48, 49, 64])
+def test_start_projection_beyond_the_gram_matrix(gpu, m):
+    """A start whose singular values fall to 1e-12 of the largest (to 1e-8 after its
+    rounding to FP32, whose squares are the rounding of the Gram matrix): the call
+    refuses it, or returns a finite X in which the direction of the largest value,
+    resolved like in any other start, is that of the polar factor."""
+    p, n = 200, 400
+    rng = np.random.default_rng(m)
+    U = np.linalg.qr(rng.standard_normal((p, m)))[0]
+    V = np.linalg.qr(rng.standard_normal((m, m)))[0]
+    sv = np.geomspace(1.0, 1e-12, m) if m > 1 else np.ones(1)
+    X0 = fp32_round(3.0 * (U * sv) @ V.T)
+    A = to_device(W.gaussian(p, n, 11))
+    try:
+        X = gpu.solve(A, gpu.BL1, m, 0.5, X0=x_to_device(X0), tol=0.0, max_iter=1).X
+    except gpu.GpspcaError as e:
+        assert m > 1 and e.code == gpu.EINVAL
+        return
+    X = X.double().cpu().numpy()
+    u, _, vt = np.linalg.svd(X0, full_matrices=False)
+    assert np.isfinite(X).all()
+    np.testing.assert_allclose(X @ vt[0], u[:, 0], atol=1e-5)
