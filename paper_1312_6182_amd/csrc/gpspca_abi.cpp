@@ -23,7 +23,6 @@
 #include <cstring>
 #include <functional>
 #include <map>
-#include <memory>
 #include <mutex>
 #include <tuple>
 #include <string>
@@ -915,6 +914,10 @@ static int small_cus(int nb, int ncu) {
     return nb > 1 ? (nb + xcds - 1) / xcds : 0;
 }
 static int small_room(int ncu) { return std::min(ncu, kXcdCus); }
+// A solve may hold its CUs while it is still queued behind earlier work of its
+// stream as long as no more than half the room is taken; the other half is for
+// solves whose streams have got that far.  So no solve is larger than half.
+static int small_half(int ncu) { return small_room(ncu) / 2; }
 
 // Whether every CU is open to the stream's kernels.
 static bool all_cus(hipStream_t st, int ncu) {
@@ -929,30 +932,33 @@ static bool all_cus(hipStream_t st, int ncu) {
     return on >= ncu;
 }
 
-static bool stream_busy(hipStream_t st) {
-    const hipError_t e = hipStreamQuery(st);
-    if (e != hipSuccess) (void)hipGetLastError();
-    return e != hipSuccess;
-}
-
 // Admission of the persistent solves (k_small.hip) of this process: their
 // workgroups wait for each other, so all of a solve's must be resident at once.
-// The solves in flight on a device never hold more CUs than its XCDs have (a
-// solve that could not be resident alone is not taken).  A thread that
-// finds no room waits for another's solve to end.  Other kernels end by
+// The solves in flight on a device never hold more CUs than its XCDs have.  Beyond
+// half the room a thread first waits for its stream: earlier work there may
+// take long, or depend on a solve of another thread, and a wait for that one's CUs
+// would never end; then for the solves that hold the rest.  Other kernels end by
 // themselves; should workgroups wait in vain all the same (another process's
 // persistent kernels), the kernel's bounded wait ends it.
 class SmallRoom {
   public:
-    SmallRoom(int nb, int ncu, int dev) : need_(small_cus(nb, ncu)), dev_(dev) {
-        if (!need_) return;
+    SmallRoom(int nb, int ncu, int dev) : need_(small_cus(nb, ncu)), dev_(dev), ncu_(ncu) {}
+    hipError_t enter(hipStream_t st) {
+        if (!need_) return hipSuccess;
         std::unique_lock<std::mutex> lk(mu());
-        const int cap = small_room(ncu);
-        cv().wait(lk, [&] { return used()[dev_] + need_ <= cap; });
+        if (used()[dev_] + need_ > small_half(ncu_)) {
+            lk.unlock();
+            const hipError_t e = hipStreamSynchronize(st);
+            if (e != hipSuccess) return e;
+            lk.lock();
+            cv().wait(lk, [&] { return used()[dev_] + need_ <= small_room(ncu_); });
+        }
         used()[dev_] += need_;
+        in_ = true;
+        return hipSuccess;
     }
     ~SmallRoom() {
-        if (!need_) return;
+        if (!in_) return;
         {
             std::lock_guard<std::mutex> lk(mu());
             used()[dev_] -= need_;
@@ -966,7 +972,8 @@ class SmallRoom {
     static std::mutex& mu() { static std::mutex m; return m; }
     static std::condition_variable& cv() { static std::condition_variable c; return c; }
     static int* used() { static int u[64] = {0}; return u; }
-    int need_, dev_;
+    int need_, dev_, ncu_;
+    bool in_ = false;
 };
 
 // Limit of a barrier's wait in ticks of the 100 MHz clock: 100 ms, a hundred times
@@ -1002,7 +1009,7 @@ static thread_local SmallRetreat t_retreat[64];
 static void small_route(Plan* pl, int ncu, int dev, hipStream_t st) {
     pl->small_nb = small_workgroups(*pl, &pl->small_whole);
     if (pl->small_nb > 1 &&
-        (small_cus(pl->small_nb, ncu) > small_room(ncu) || !all_cus(st, ncu) ||
+        (small_cus(pl->small_nb, ncu) > small_half(ncu) || !all_cus(st, ncu) ||
          t_retreat[dev].holds(small_wait())))
         pl->small_nb = 0;
 }
@@ -1011,18 +1018,14 @@ static void small_route(Plan* pl, int ncu, int dev, hipStream_t st) {
 constexpr int kSmallChunk = 256;
 constexpr int kSmallAborted = 1000;   // internal: run the passes as separate launches
 
-// queued: earlier work of others was in the stream when the solve began.
 static int run_small(const Plan& pl, const PassParams& pp, const Ptrs& P, int max_iter, int ncu,
-                     int dev, hipStream_t st, bool queued, Ctrl* fin, bool noalloc,
+                     int dev, hipStream_t st, Ctrl* fin, bool noalloc,
                      const std::function<int()>& tail) {
     Ctrl stack_snap;
     Ctrl* snap = &stack_snap;
     int rc = noalloc ? GPSPCA_OK : pinned_ctrl(&snap);
     if (rc) return rc;
     const int64_t wait = small_wait();
-    // the room is not held while the solve waits behind that work, which may take
-    // long or depend on a solve of another thread
-    if (queued && pl.small_nb > 1) GPSPCA_HIP(hipStreamSynchronize(st));
     TimedLaunches tl;
     if (!noalloc) {
         std::lock_guard<std::mutex> lk(g_prof.mu);
@@ -1030,6 +1033,7 @@ static int run_small(const Plan& pl, const PassParams& pp, const Ptrs& P, int ma
         tl.every = g_prof.every;
     }
     SmallRoom room(pl.small_nb, ncu, dev);
+    GPSPCA_HIP(room.enter(st));
     uint32_t bar0 = 0;
     for (int kk = 0; kk < max_iter; kk += kSmallChunk) {
         const int c = std::min(kSmallChunk, max_iter - kk);
@@ -1138,13 +1142,13 @@ static const char* status_text(int s) {
 //  server caches them with a resident matrix).
 //  multistart (path, no X0): problem j starts at the normalized column of the
 //  j-th largest norm instead of all at the largest.
-//  route: kRouteIdle, kRouteLaunches.
+//  no_small: the passes are launches, not one persistent kernel.
 int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const double* mu,
                const double* gammas, int path, const uint32_t* mask, const float* X0,
                double tol, int max_iter, void* workspace, size_t ws_bytes, hipStream_t st,
                float* X, float* Z, uint32_t* support, double* obj_trace, int* n_iter,
                int* status_out, const double* norms_in, int multistart, const double* defl_q,
-               int defl_k, int exact, int noalloc, int route) {
+               int defl_k, int exact, int noalloc, int no_small) {
     int ncu = 0, dev = 0;
     int rc = device_cus(&ncu, &dev);
     if (rc) return rc;
@@ -1155,11 +1159,7 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     pl.defl_q = defl_q;
     pl.defl_k = defl_q ? defl_k : 0;
     pl.exact = (exact && !path) ? 1 : 0;
-    bool queued = false;
-    if (!(route & kRouteLaunches) && small_enabled(A, m, path)) {
-        small_route(&pl, ncu, dev, st);
-        if (pl.small_nb > 1 && !(route & kRouteIdle)) queued = stream_busy(st);
-    }
+    if (!no_small && small_enabled(A, m, path)) small_route(&pl, ncu, dev, st);
     const Ptrs P = carve(pl, workspace);
     PassParams pp = make_params(A, pl, gamma, mu, gammas);
     pp.nact = &P.ctrl->nact;
@@ -1274,11 +1274,11 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
     };
     Ctrl fin;
     if (pl.small_nb) {
-        rc = run_small(pl, pp, P, max_iter, ncu, dev, st, queued, &fin, noalloc != 0, outputs);
+        rc = run_small(pl, pp, P, max_iter, ncu, dev, st, &fin, noalloc != 0, outputs);
         if (rc == kSmallAborted)
             return solve_core(A, form, m, gamma, mu, gammas, path, mask, X0, tol, max_iter,
                               workspace, ws_bytes, st, X, Z, support, obj_trace, n_iter, status_out,
-                              norms_in, multistart, defl_q, defl_k, exact, noalloc, kRouteLaunches);
+                              norms_in, multistart, defl_q, defl_k, exact, noalloc, 1);
     } else {
         rc = run_passes(pl, pp, P, max_iter, tol, st, &fin, noalloc != 0, &outputs);
     }
@@ -1598,9 +1598,6 @@ int gpspca_solve_deflated(const gpspca_matrix* A, int form, int m, double gamma,
     make_plan(A, form, 1, max_iter, ncu, &p1);
     int worst = GPSPCA_OK;
     for (int k = 0; k < m; ++k) {
-        // after the first component's solve, which waits for the stream, only the
-        // launches below are in it
-        const int route = k > 0 ? kRouteIdle : 0;
         const float* start = nullptr;
         if (k > 0) {
             // default start of the deflated matrix: its column of largest norm,
@@ -1618,7 +1615,7 @@ int gpspca_solve_deflated(const gpspca_matrix* A, int form, int m, double gamma,
         rc = solve_core(A, form, 1, gamma, nullptr, nullptr, 0, nullptr, start, tol, max_iter,
                         workspace, core, st, X + (size_t)k * P, Z + (size_t)k * A->n,
                         support + (size_t)k * words, obj_trace + (size_t)k * max_iter,
-                        &n_iter[k], nullptr, nullptr, 0, k > 0 ? Q : nullptr, k, 0, 0, route);
+                        &n_iter[k], nullptr, nullptr, 0, k > 0 ? Q : nullptr, k);
         if (rc < 0) return rc;
         status[k] = rc;
         if (rc > worst) worst = rc;
@@ -1698,7 +1695,7 @@ static int time_config(const gpspca_matrix* A, int pform, int m, double gamma, i
         GPSPCA_HIP(launch_x_interleave(pl, P.x[0], P.xil[0], st));
     }
     TimedLaunches tl;
-    std::unique_ptr<SmallRoom> room;
+    SmallRoom room(small_nb, ncu, dev);
     uint32_t arrived = 0;
     auto small = [&](int count) -> int {
         GPSPCA_HIP(launch_small(pl, pp, P.x[0], P.x[1], P.S, P.gpart, P.fpart, P.nnzpart, P.g64,
@@ -1707,10 +1704,7 @@ static int time_config(const gpspca_matrix* A, int pform, int m, double gamma, i
         arrived += (uint32_t)count * (uint32_t)pl.small_nb * (pl.small_whole ? 1u : 2u);
         return GPSPCA_OK;
     };
-    if (small_nb) {
-        GPSPCA_HIP(hipStreamSynchronize(st));   // nothing else is waited for in the room
-        room = std::make_unique<SmallRoom>(small_nb, ncu, dev);
-    }
+    GPSPCA_HIP(room.enter(st));
     int rc = small_nb ? small(1) : enqueue_pass(pl, pp, P, 0, st, tl);
     if (rc) return rc;
     hipEvent_t a = nullptr, b = nullptr;

@@ -325,9 +325,6 @@ int solve_core(const gpspca_matrix* A, int form, int m, double gamma, const doub
                float* X, float* Z, uint32_t* support, double* obj_trace, int* n_iter,
                int* status_out, const double* norms_in, int multistart = 0,
                const double* defl_q = nullptr, int defl_k = 0, int exact = 0,
-               int noalloc = 0, int route = 0);
-// route: the caller knows that the stream holds its own short launches at most; the
-// passes are separate launches, not one persistent one
-constexpr int kRouteIdle = 1, kRouteLaunches = 2;
+               int noalloc = 0, int no_small = 0);
 
 }  // namespace gpspca

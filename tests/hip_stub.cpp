@@ -9,7 +9,6 @@
 #include <functional>
 #include <map>
 #include <mutex>
-#include <set>
 #include <string>
 #include <vector>
 
@@ -25,7 +24,6 @@ struct State {
     gpspca::Ctrl ctrl;
     float first_ms = 1.f, later_ms = 1.f;     // measured times: the first one, the others
     void (*on_sync)(hipStream_t) = nullptr;   // called by hipStreamSynchronize
-    std::set<hipStream_t> busy;               // streams with unfinished work
 };
 struct Pushed {   // the thread's configuration between push and pop
     dim3 grid, block;
@@ -74,7 +72,6 @@ void stub_times(float first, float later) {
     S().later_ms = later;
 }
 void stub_on_sync(void (*f)(hipStream_t)) { S().on_sync = f; }
-void stub_busy(hipStream_t st) { S().busy.insert(st); }
 size_t stub_log(char* out, size_t len) {
     std::lock_guard<std::mutex> lk(S().mu);
     std::snprintf(out, len, "%s", S().log.c_str());
@@ -139,10 +136,6 @@ hipError_t hipStreamSynchronize(hipStream_t st) {
     return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)(uintptr_t)64; return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t st) {
-    std::lock_guard<std::mutex> lk(S().mu);
-    return S().busy.count(st) ? hipErrorNotReady : hipSuccess;
-}
 hipError_t hipExtStreamGetCUMask(hipStream_t, uint32_t words, uint32_t* mask) {
     std::memset(mask, 0, 4 * words);
     for (int c = S().masked; c < S().cus && c < 32 * (int)words; ++c) mask[c / 32] |= 1u << (c % 32);
