@@ -26,16 +26,16 @@
 //     made there, once per workgroup instead of once per wave.
 //
 // Times (10000 x 100000 unless stated; in brackets the kernels that served these
-// before): FP32, 64 components 993 us (one wave per workgroup, parts of X made
+// before): FP32, 64 components 950 us (one wave per workgroup, parts of X made
 // by every wave: 1245); FP32, 32 components 757 us (LDS DMA, 16x16x4 products:
 // 759 + 9 for its leftover tiles); e4m3, 32 components 296 us (372); odd leading
 // dimension, FP32: 12 components 756 us, 32 components 913, 64 components 1145
 // (n = 100000, p = 10001), 1999 x 20011, 12 components 39 us (two vector-ALU
 // launches of 37); bfloat16 2003 x 20021, 16 components 34 us (38).
-// At 64 components the six part products are the bound, with their totals (70
-// us, for an error of 3.4e-7 instead of 1.6e-6 at p = 10000) and the conversions
-// on two waves per SIMD to overlap them; below that, HBM and the latency of
-// the stages.
+// At 64 components the six part products are the bound, with the conversions
+// on two waves per SIMD to overlap them; the totals take 35 us, for an error of
+// 2.7e-7 instead of 1.6e-6 at p = 10000 (in registers, added to after every stage:
+// 75 us, 3.4e-7).  Below that, HBM and the latency of the stages.
 // Modes (the arithmetic stays FP32-accurate in each):
 //   0  FP32 A, v_mfma_f32_16x16x4_f32 (at most 2 component groups: at 4 the
 //      FP32 matrix cores, not HBM, are the bound);
@@ -69,6 +69,7 @@ constexpr int kShWaves = 8;
 constexpr int kShThreads = 64 * kShWaves;
 constexpr int kShTiles = 4;   // tiles per wave and round, at most
 constexpr int kShFlush = 4;   // stages per accumulator
+constexpr int kShLdsTiles = 3;   // tiles of a wave whose totals are in LDS (mode 1)
 
 template <int MODE, int J, int SB>
 struct Sh {
@@ -82,8 +83,9 @@ struct Sh {
     static constexpr int XI = (XItems + kShThreads - 1) / kShThreads;
     static constexpr int XBytes = MODE == 0 ? RS * 16 * J * 4 : RS * 16 * J * 6;
     static constexpr int AWave = 2 * 16 * SB;                       // a pair of tiles
+    static constexpr int Tot = MODE == 1 ? kShLdsTiles * J * 1024 : 0;   // totals of a wave
     static constexpr int Lds = 2 * XBytes + kShWaves * AWave;
-    static_assert(Lds <= 160 * 1024, "LDS of a CU");
+    static_assert(Lds + kShWaves * Tot <= 160 * 1024, "LDS of a CU");
 };
 
 __device__ __forceinline__ uint32_t sh_pack_hi(float lo, float hi) {
@@ -240,28 +242,38 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
     // The matrix cores chain their additions (FP32 operands: one rounding per
     // row; bfloat16: one truncation per 32 rows), so an accumulator through all
     // rows would be off by sqrt(rows) roundings.  STEP: it carries 16 rows (FINE
-    // == 8: 8; mode 1: 32) from zero and is added to tot, in FP64 with FINE.
+    // == 8: 8; mode 1: 32) from zero and is added to tot in FP64.
     // Otherwise acc carries kShFlush stages before it is added to tot; with 4
     // component groups of 16/8-bit codes it is all there is.
-    constexpr bool STEP = MODE == 1 || FINE > 0;
+    // Mode 1 without FINE: acc carries 2 kShFlush stages, and the totals of three
+    // of a wave's four tiles are in LDS (there are no registers for them).
+    constexpr bool STEP = FINE > 0, LTOT = MODE == 1 && !STEP;
     constexpr bool kTot = STEP || J < 4;
-    using TotV = typename std::conditional<(FINE > 0), d4s, f4s>::type;
+    using TotV = typename std::conditional<STEP, d4s, f4s>::type;
     f4s acc[STEP ? 1 : NA][STEP ? 1 : J];
-    TotV tot[kTot ? NA : 1][kTot ? J : 1];
+    TotV tot[kTot ? NA : 1][kTot || LTOT ? J : 1];
+    f4s* const lt = reinterpret_cast<f4s*>(lds + 2 * T::XBytes + kShWaves * T::AWave + wv * T::Tot) +
+                    lane;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int jb = 0; jb < J; ++jb) {
             if constexpr (!STEP) acc[t][jb] = f4s{0.f, 0.f, 0.f, 0.f};
             if constexpr (kTot) tot[t][jb] = TotV{0, 0, 0, 0};
+            else if constexpr (LTOT) {
+                if (t < kShLdsTiles) lt[64 * (t * J + jb)] = f4s{0.f, 0.f, 0.f, 0.f};
+                else tot[0][jb] = TotV{0, 0, 0, 0};
+            }
         }
     auto flush = [&] {
-        if constexpr (kTot && !STEP) {
+        if constexpr ((kTot && !STEP) || LTOT) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int jb = 0; jb < J; ++jb) {
-                    tot[t][jb] += acc[t][jb];
+                    if constexpr (kTot) tot[t][jb] += acc[t][jb];
+                    else if (t < kShLdsTiles) lt[64 * (t * J + jb)] += acc[t][jb];
+                    else tot[0][jb] += acc[t][jb];
                     acc[t][jb] = f4s{0.f, 0.f, 0.f, 0.f};
                 }
         }
@@ -403,7 +415,7 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                     if constexpr (NT == 4) tiles(std::integral_constant<int, 2>{}, 2, areg[u % D], so, xb);
                     if constexpr (NT == 1) tiles(std::integral_constant<int, 1>{}, 0, areg[u % D], so, xb);
                     if constexpr (NT == 3) tiles(std::integral_constant<int, 1>{}, 2, areg[u % D], so, xb);
-                    if ((s + 1) % kShFlush == 0) flush();
+                    if ((s + 1) % (LTOT ? 2 * kShFlush : kShFlush) == 0) flush();
                 }
             }
         }
@@ -428,6 +440,8 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
 #pragma unroll
                 for (int jb = 0; jb < J; ++jb) {
                     if constexpr (kTot) y[jb] = (float)tot[t][jb][v];
+                    else if constexpr (LTOT)
+                        y[jb] = t < kShLdsTiles ? lt[64 * (t * J + jb)][v] : tot[0][jb][v];
                     else y[jb] = acc[t][jb][v];
                 }
                 for (int r = rows_main; r < p; ++r) {
@@ -484,7 +498,7 @@ __global__ __launch_bounds__(kShThreads, 2) void k_corr_sh(PassParams pp, const 
                                                         const Ctrl* __restrict__ ctrl) {
     if (ctrl->done) return;
     using T = Sh<MODE, J, SB>;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[T::Lds];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[T::Lds + (FINE ? 0 : kShWaves * T::Tot)];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = pp.m;

@@ -60,8 +60,8 @@ def test_unaligned_columns_keep_the_vector_kernels_accuracy(gpu, p, n, m, monkey
 
 def test_64_components_keep_the_accuracy_of_short_chains(gpu, monkeypatch):
     """Aligned FP32 with 64 components: an accumulator through all 10000 rows is off
-    by 1.6e-6; totals every 32 rows leave the rounding of p / 32 additions,
-    0.3 sqrt(313) 2^-24 = 3.2e-7, and that of a step's own products."""
+    by 1.6e-6; with totals every 32 to 256 rows the rounding of the totals and of the
+    products in between stays below a third of that."""
     p, n, m = 10000, 6000, 64
     gen = torch.Generator(device="cuda").manual_seed(4)
     A = torch.randn((n, p), device="cuda", generator=gen).t()
