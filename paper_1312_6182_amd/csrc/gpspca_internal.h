@@ -218,6 +218,17 @@ hipError_t launch_corr_qw(const Plan& pl, const PassParams& pp, const float* X, 
 // Every pass of a solve on a small matrix in one launch (k_small.hip): the
 // workgroups for the plan (0: not taken), and `passes` passes from the control
 // block's state; bar0: barrier arrivals of the solve's earlier launches.
+// us per pass:
+//   kSmallTiles   a tile for each of the 8 waves; with 4 / 8 / 16 100 x 1000, m = 1 takes
+//                 7.8 / 7.6 / 9.0, 300 x 3000 11.1 / 10.2 / 10.2, 200 x 2000, m = 5 22.1 /
+//                 21.6 / 21.7, 100 x 1000, m = 16 14.6 / 15.9 / 18.0
+//   kSmallWgs     one lane of a wave per workgroup's objective term; with 32, 400 x 4000,
+//                 m = 1 and 300 x 3000, m = 5 no longer fit and take launches
+//   kSmallWhole   one barrier per pass and more to read, or two: with 4096 / 16384 /
+//                 65536 300 x 3000, m = 1 (12000 entries) takes 13.0 / 10.2 / 10.2, 200 x 2000,
+//                 m = 2 (6400) 20.6 / 18.0 / 18.1, 300 x 3000, m = 5 (36000) 26.8 / 26.9 /
+//                 30.8, 200 x 2000, m = 8 (25600) 26.6 / 26.6 / 29.3; for it only 400 x 4000,
+//                 m = 1 (20000), 14.7 / 14.7 / 12.8
 constexpr int kSmallTiles = 8;                        // tiles of 16 columns per workgroup, at least
 constexpr int kSmallWgs = 64;                         // most workgroups
 constexpr int64_t kSmallWhole = 16384;                // partial entries each workgroup sums alone

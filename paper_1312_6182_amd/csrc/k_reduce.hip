@@ -563,7 +563,9 @@ hipError_t launch_reduce_gram(const Plan& pl, const float* gpart, const int* tou
                               const Ctrl* ctrl, hipStream_t st) {
     // up to 256 row blocks there is a CU for each
     const bool wide = pl.p <= 64 * 256;
-#define GPSPCA_RG(MB, NSL)                                                                          (wide ? launch_reduce_gram_t<MB, NSL>(pl, gpart, touched, X, with_x, g64, gram, ctrl, st)            : launch_reduce_gram_t<MB, 4>(pl, gpart, touched, X, with_x, g64, gram, ctrl, st))
+#define GPSPCA_RG(MB, NSL)                                                                     \
+    (wide ? launch_reduce_gram_t<MB, NSL>(pl, gpart, touched, X, with_x, g64, gram, ctrl, st)  \
+          : launch_reduce_gram_t<MB, 4>(pl, gpart, touched, X, with_x, g64, gram, ctrl, st))
     if (pl.m <= 1) GPSPCA_RG(1, 16);
     else if (pl.m <= 2) GPSPCA_RG(2, 16);
     else if (pl.m <= 4) GPSPCA_RG(4, 16);

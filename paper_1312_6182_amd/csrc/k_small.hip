@@ -2,8 +2,8 @@
 //
 // On a small matrix a pass is latency: 3 to 6 launches of 4-16 us each, while
 // its arithmetic takes one.  Here nb <= 64 workgroups of 8 waves hold their
-// columns in LDS (FP32, at most about 100 KB each, so 6 MB in all) for the whole
-// solve and meet at grid barriers.  A read from L2 instead is bound by the 64
+// columns in LDS (FP32, what 146 KB leave beside the other arrays: up to about 135
+// KB each, 8.5 MB in all) for the whole solve and meet at grid barriers.  A read from L2 instead is bound by the 64
 // bytes per clock of a CU's cache: at 400 x 4000 it took 25 us per pass against 12.
 //
 //   1  y = A^T X and the threshold for the workgroup's tiles of 16 columns, then
