@@ -922,6 +922,8 @@ static int small_half(int ncu) { return small_room(ncu) / 2; }
 // Whether every CU is open to the stream's kernels.
 static bool all_cus(hipStream_t st, int ncu) {
     uint32_t mask[32] = {0};
+    // the mask of a stream can only be asked for by a real handle (or NULL)
+    if (st == hipStreamLegacy || st == hipStreamPerThread) st = nullptr;
     const int words = std::min(32, (ncu + 31) / 32);
     if (hipExtStreamGetCUMask(st, (uint32_t)words, mask) != hipSuccess) {
         (void)hipGetLastError();

@@ -136,7 +136,9 @@ hipError_t hipStreamSynchronize(hipStream_t st) {
     return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)(uintptr_t)64; return hipSuccess; }
-hipError_t hipExtStreamGetCUMask(hipStream_t, uint32_t words, uint32_t* mask) {
+hipError_t hipExtStreamGetCUMask(hipStream_t st, uint32_t words, uint32_t* mask) {
+    // the runtime takes these two for addresses here
+    if (st == hipStreamLegacy || st == hipStreamPerThread) std::abort();
     std::memset(mask, 0, 4 * words);
     for (int c = S().masked; c < S().cus && c < 32 * (int)words; ++c) mask[c / 32] |= 1u << (c % 32);
     return hipSuccess;

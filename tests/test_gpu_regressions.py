@@ -307,3 +307,22 @@ def test_start_projection_beyond_the_gram_matrix(gpu, m):
     u, _, vt = np.linalg.svd(X0, full_matrices=False)
     assert np.isfinite(X).all()
     np.testing.assert_allclose(X @ vt[0], u[:, 0], atol=1e-5)
+
+
+@pytest.mark.parametrize("stream", [0, 1, 2], ids=["null", "legacy", "per_thread"])
+def test_small_solve_on_the_default_streams(gpu, stream):
+    """The NULL stream and the special handles of the default streams."""
+    A = to_device(W.planted_block(100, 1000, 2, 3, k=30)[0])
+    gamma = 0.1 * float(A.norm(dim=0).max())
+    want = gpu.solve(A, gpu.SL1, 1, gamma, tol=0.0, max_iter=7)
+    M = gpu.matrix(A)
+    ws = torch.empty(gpu.workspace_bytes(A, gpu.SL1, 1, 7) + 256, dtype=torch.uint8, device="cuda")
+    ws = ws[(-ws.data_ptr()) % 256:]
+    X, Z = torch.empty((1, 100), device="cuda"), torch.empty((1, 1000), device="cuda")
+    torch.cuda.synchronize()
+    rc = gpu.load().gpspca_solve(ctypes.byref(M), gpu.SL1, 1, gamma, None, None, 0.0, 7,
+                                 ws.data_ptr(), ws.numel(), stream, X.data_ptr(), Z.data_ptr(),
+                                 None, None, None)
+    assert rc == gpu.MAXITER
+    torch.cuda.synchronize()
+    assert torch.equal(X.t(), want.X) and torch.equal(Z.t(), want.Z)

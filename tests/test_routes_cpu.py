@@ -250,7 +250,16 @@ def child_queued(lib):
     assert min(rc) >= 0 and _small(lib) == [64] * 5
 
 
-@pytest.mark.parametrize("scenario", ["few_cus", "masked_stream", "run_out", "queued"])
+def child_special_streams(lib):
+    """The handles of the legacy and the per-thread default stream (1 and 2) are no
+    addresses: the query of a stream's CU mask must not be given them."""
+    for stream in (None, 1, 2):
+        assert lib.solve(lib.matrix(100, 1000), 1, max_iter=4, stream=stream) >= 0
+        assert _small(lib) == [8]
+
+
+@pytest.mark.parametrize("scenario", ["few_cus", "masked_stream", "run_out", "queued",
+                                      "special_streams"])
 def test_persistent_solves_need_their_cus(stub, scenario):
     _child(stub, scenario)
 
