@@ -24,6 +24,7 @@
 //     4(l/16)+v), so the threshold runs directly on them.
 // LDS reads are issued with inline asm and every wait is explicit, because
 // the compiler cannot count LDS DMA completions across the loop back-edge.
+#include "corr.h"
 #include "gpspca_internal.h"
 #include "storage.h"
 
@@ -71,22 +72,6 @@ __device__ __forceinline__ void dma16(const float* gptr, uint32_t lds_base) {
     __builtin_amdgcn_global_load_lds(
         (const void __attribute__((address_space(1)))*)gptr,
         (void __attribute__((address_space(3)))*)(uintptr_t)lds_base, 16, 0, 0);
-}
-
-__device__ __forceinline__ bool threshold_m(bool l0, double mu, double gamma, float y, float& s,
-                                            double& fv) {
-    const double yd = (double)y;
-    if (l0) {
-        const double my = mu * yd;
-        const double q = my * my - gamma;
-        if (q > 0.0) { s = (float)my; fv = q; return true; }
-    } else {
-        const double t = mu * fabs(yd) - gamma;
-        if (t > 0.0) { s = (float)(yd > 0.0 ? t : -t); fv = t * t; return true; }
-    }
-    s = 0.f;
-    fv = 0.0;
-    return false;
 }
 
 // Balanced partition: a wave's row-split share of a leftover tile, the 16
@@ -390,7 +375,7 @@ __device__ __forceinline__ void mfma_chunk(const PassParams& pp, int64_t c0, int
                 if (cvalid && comp < m) {
                     float s;
                     double fv;
-                    const bool a = threshold_m(l0, pp.mu[comp], pp.gam[comp], acc[t][jb][v], s, fv);
+                    const bool a = threshold(l0, pp.mu[comp], pp.gam[comp], acc[t][jb][v], s, fv);
                     S[col * m + comp] = s;
                     if (a) {
                         f_acc[jb] += fv;
@@ -595,7 +580,7 @@ __global__ __launch_bounds__(64) void k_corr_bal_fix(PassParams pp, BalArgs bal,
             if (cvalid && comp < m) {
                 float sv;
                 double fv;
-                if (threshold_m(l0, pp.mu[comp], pp.gam[comp], acc[jb][v], sv, fv)) {
+                if (threshold(l0, pp.mu[comp], pp.gam[comp], acc[jb][v], sv, fv)) {
                     f[jb] += fv;
                     cnt[jb] += 1;
                     any = true;
@@ -813,7 +798,7 @@ __device__ __forceinline__ void wg_round(const PassParams& pp, int64_t c0, int64
                     if (cvalid && comp < m) {
                         float s;
                         double fv;
-                        const bool a = threshold_m(l0, pp.mu[comp], pp.gam[comp], acc[t][jb][v], s, fv);
+                        const bool a = threshold(l0, pp.mu[comp], pp.gam[comp], acc[t][jb][v], s, fv);
                         S[col * m + comp] = s;
                         if (a) {
                             f_acc[jb] += fv;
@@ -1062,7 +1047,7 @@ __device__ __forceinline__ void rd_chunk(const PassParams& pp, int64_t c0, int64
                 if (cvalid && comp < m) {
                     float s;
                     double fv;
-                    const bool a = threshold_m(l0, pp.mu[comp], pp.gam[comp], acc[t][jb][v], s, fv);
+                    const bool a = threshold(l0, pp.mu[comp], pp.gam[comp], acc[t][jb][v], s, fv);
                     S[col * m + comp] = s;
                     if (a) {
                         f_acc[jb] += fv;
@@ -1171,28 +1156,6 @@ hipError_t launch_corr_rd(const Plan& pl, const PassParams& pp, const float* X, 
 // component lj of X from the interleaved copy.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf8m __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ void split3_bf16(const f4m& q0, const f4m& q1, bf8m& v1, bf8m& v2,
-                                            bf8m& v3) {
-    float r[8];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        r[e] = q0[e];
-        r[4 + e] = q1[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        v1[e] = (__bf16)r[e];
-        r[e] -= (float)v1[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        v2[e] = (__bf16)r[e];
-        r[e] -= (float)v2[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v3[e] = (__bf16)r[e];
-}
 
 template <int NT, int J, int D>
 __device__ __forceinline__ void x3_chunk(const PassParams& pp, int64_t c0, int64_t cend,
@@ -1305,7 +1268,7 @@ __device__ __forceinline__ void x3_chunk(const PassParams& pp, int64_t c0, int64
                 if (cvalid && comp < m) {
                     float s;
                     double fv;
-                    const bool a = threshold_m(l0, pp.mu[comp], pp.gam[comp], acc[t][jb][v], s, fv);
+                    const bool a = threshold(l0, pp.mu[comp], pp.gam[comp], acc[t][jb][v], s, fv);
                     S[col * m + comp] = s;
                     if (a) {
                         f_acc[jb] += fv;
@@ -1517,7 +1480,7 @@ __global__ __launch_bounds__(64) void k_corr_mv(PassParams pp, const float* __re
                 if (valid) {
                     float sv;
                     double fv;
-                    a = threshold_m(l0, pp.mu[lj], pp.gam[lj], acc[t][v], sv, fv);
+                    a = threshold(l0, pp.mu[lj], pp.gam[lj], acc[t][v], sv, fv);
                     S[col * m + lj] = sv;
                     if (a) {
                         f_acc += fv;

@@ -49,6 +49,7 @@
 // the parts of an infinity or of a value near the FP32 limit are NaN, and in
 // every mode the slots of the last stage past a column's end repeat its last
 // full slot against zeros of X, where an infinity gives NaN.
+#include "corr.h"
 #include "gpspca_internal.h"
 #include "storage.h"
 
@@ -97,45 +98,6 @@ __device__ __forceinline__ bf8s sh_widen8(uint32_t w0, uint32_t w1) {
     const qf2 c = e4m3_pair(w1, false), d = e4m3_pair(w1, true);
     return __builtin_bit_cast(bf8s, u4s{sh_pack_hi(a.x, a.y), sh_pack_hi(b.x, b.y),
                                         sh_pack_hi(c.x, c.y), sh_pack_hi(d.x, d.y)});
-}
-
-// v = v1 + v2 + v3, each part bfloat16 (8 significant bits of the 24).
-__device__ __forceinline__ void sh_split3(const f4s& q0, const f4s& q1, bf8s& v1, bf8s& v2,
-                                          bf8s& v3) {
-    float r[8];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        r[e] = q0[e];
-        r[4 + e] = q1[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        v1[e] = (__bf16)r[e];
-        r[e] -= (float)v1[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        v2[e] = (__bf16)r[e];
-        r[e] -= (float)v2[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v3[e] = (__bf16)r[e];
-}
-
-__device__ __forceinline__ bool sh_threshold(bool l0, double mu, double gamma, float y, float& s,
-                                             double& fv) {
-    const double yd = (double)y;
-    if (l0) {
-        const double my = mu * yd;
-        const double q = my * my - gamma;
-        if (q > 0.0) { s = (float)my; fv = q; return true; }
-    } else {
-        const double t = mu * fabs(yd) - gamma;
-        if (t > 0.0) { s = (float)(yd > 0.0 ? t : -t); fv = t * t; return true; }
-    }
-    s = 0.f;
-    fv = 0.0;
-    return false;
 }
 
 template <int MODE>
@@ -230,7 +192,7 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                 *reinterpret_cast<f4s*>(xb + 16 * it) = src[k][0];
             } else {
                 bf8s x1, x2, x3;
-                sh_split3(src[k][0], src[k][1], x1, x2, x3);
+                split3_bf16(src[k][0], src[k][1], x1, x2, x3);
                 uint8_t* at = xb + 3072 * (it >> 6) + 16 * lane;   // (jb KS + h) x 3 parts
                 *reinterpret_cast<bf8s*>(at) = x1;
                 *reinterpret_cast<bf8s*>(at + 1024) = x2;
@@ -346,7 +308,7 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                     if constexpr (MODE == 1) {
                         const f4s q0 = *reinterpret_cast<const f4s*>(a_at(u, lj, 8 * h + 2 * lk));
                         const f4s q1 = *reinterpret_cast<const f4s*>(a_at(u, lj, 8 * h + 2 * lk + 1));
-                        sh_split3(q0, q1, a1[u], a2[u], a3[u]);
+                        split3_bf16(q0, q1, a1[u], a2[u], a3[u]);
                     } else if constexpr (MODE == 2) {
                         a1[u] = *reinterpret_cast<const bf8s*>(a_at(u, lj, 4 * h + lk));
                     } else {
@@ -467,8 +429,8 @@ __device__ __forceinline__ void sh_round(const PassParams& pp, int64_t c0, int64
                     if (cvalid && comp < m) {
                         float sv;
                         double fv;
-                        const bool on = sh_threshold(l0, pp.mu[comp], pp.gam[comp],
-                                                     MODE >= 2 ? sc * y[jb] : y[jb], sv, fv);
+                        const bool on = threshold(l0, pp.mu[comp], pp.gam[comp],
+                                                  MODE >= 2 ? sc * y[jb] : y[jb], sv, fv);
                         S[col * m + comp] = sv;
                         if (on) {
                             f_acc[jb] += fv;

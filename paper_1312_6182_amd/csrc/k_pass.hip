@@ -26,6 +26,7 @@
 //  k_colnorm   ||a_i|| in FP64 (default start).
 #include <algorithm>
 
+#include "corr.h"
 #include "gpspca_internal.h"
 #include "storage.h"
 
@@ -74,32 +75,6 @@ __device__ __forceinline__ float dot4(f4 a, f4 b, float acc) {
     acc = __builtin_fmaf(a.z, b.z, acc);
     acc = __builtin_fmaf(a.w, b.w, acc);
     return acc;
-}
-
-// Threshold of one correlation (Table 1).  Returns true when the entry is in
-// the support; s is the thresholded value and fv its objective term.
-__device__ __forceinline__ bool threshold(bool l0, double mu, double gamma, float y, float& s,
-                                          double& fv) {
-    const double yd = (double)y;
-    if (l0) {
-        const double my = mu * yd;
-        const double q = my * my - gamma;
-        if (q > 0.0) {
-            s = (float)my;
-            fv = q;
-            return true;
-        }
-    } else {
-        const double t = mu * fabs(yd) - gamma;
-        if (t > 0.0) {
-            s = (float)(yd > 0.0 ? t : -t);
-            fv = t * t;
-            return true;
-        }
-    }
-    s = 0.f;
-    fv = 0.0;
-    return false;
 }
 
 template <typename T>

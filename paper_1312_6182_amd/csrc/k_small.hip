@@ -41,6 +41,7 @@
 // CU, and none on a stream that is kept off some CUs (gpspca_abi.cpp), and a wait that lasts 100 ms ends the kernel
 // with Ctrl::abort set: the host then runs the passes as separate launches, and
 // the thread's next solves as well.
+#include "corr.h"
 #include "gpspca_internal.h"
 #include "retract.h"
 #include "storage.h"
@@ -137,22 +138,6 @@ __device__ __forceinline__ f4c quad_edge(const void* colv, int q, int nqf, int p
         const qf4 v = load_quad_st<ST>(colv, q, nqf, p);
         return f4c{v.x, v.y, v.z, v.w};
     }
-}
-
-__device__ __forceinline__ bool threshold_s(bool l0, double mu, double gamma, float y, float& s,
-                                            double& fv) {
-    const double yd = (double)y;
-    if (l0) {
-        const double my = mu * yd;
-        const double q = my * my - gamma;
-        if (q > 0.0) { s = (float)my; fv = q; return true; }
-    } else {
-        const double t = mu * fabs(yd) - gamma;
-        if (t > 0.0) { s = (float)(yd > 0.0 ? t : -t); fv = t * t; return true; }
-    }
-    s = 0.f;
-    fv = 0.0;
-    return false;
 }
 
 // Every wave's stores acknowledged, then every workgroup's arrival.  False when
@@ -305,7 +290,7 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
                 if (col < n) {
                     const float sc = ST == kStF32 ? 1.0f : column_scale(pp, col);
                     double fv;
-                    if (threshold_s(l0, mud, gamd, ST == kStF32 ? y : sc * y, s, fv)) {
+                    if (threshold(l0, mud, gamd, ST == kStF32 ? y : sc * y, s, fv)) {
                         f_acc += fv;
                         nnz_acc += 1;
                     }
@@ -341,7 +326,7 @@ __global__ __launch_bounds__(kSmT, 2) void k_small(PassParams pp, SmallArgs a) {
                     if (c < n) {
                         const float sc = ST == kStF32 ? 1.0f : column_scale(pp, c);
                         double fv;
-                        on = threshold_s(l0, mud, gamd, ST == kStF32 ? y[v] : sc * y[v],
+                        on = threshold(l0, mud, gamd, ST == kStF32 ? y[v] : sc * y[v],
                                          s, fv);
                         if (on) {
                             f_acc += fv;
