@@ -8,7 +8,7 @@ import torch
 import oracle as O
 from workloads import generators as W
 
-from _util import fp32_round, to_device, x_to_device
+from _util import fp32_round, pick_gamma, rel, to_device, x_to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -326,3 +326,29 @@ def test_small_solve_on_the_default_streams(gpu, stream):
     assert rc == gpu.MAXITER
     torch.cuda.synchronize()
     assert torch.equal(X.t(), want.X) and torch.equal(Z.t(), want.Z)
+
+
+@pytest.mark.parametrize("store", ["f32", "bf16"])
+@pytest.mark.parametrize("form,m,p,n", [(O.SL0, 1, 100, 1000), (O.SL0, 1, 300, 3100),
+                                        (O.BL0, 2, 120, 900), (O.BL0, 5, 200, 2000),
+                                        (O.BL0, 8, 130, 1400)])
+def test_small_solves_of_the_l0_forms(gpu, form, m, p, n, store):
+    """Hard-threshold solves by the persistent kernel against the oracle, with gamma
+    picked away from ties along the oracle's iterates."""
+    iters = 6
+    A = W.planted_block(p, n, min(m, 2), p + m, k=max(4, n // 25))[0]
+    Ad, A64 = to_device(A, lda=p | 1), A.astype(np.float64)
+    if store == "bf16":
+        Ad, _ = gpu.quantize(to_device(A), torch.bfloat16)
+        A64 = O.dequantize(O.quantize(A, O.BF16)[0], O.BF16, None, p)
+    X0 = fp32_round(O.init(A64, m)[0])
+    mu = None if m == 1 else list(np.linspace(1.0, 0.8, m))
+    gamma = pick_gamma(A64, form, m, mu, X0, W.gamma_absolute(A64, True, 0.05), iters=iters)
+    ref = O.solve(A64, form, m, gamma, mu=mu, X0=X0, tol=0.0, max_iter=iters)
+    r, name, launches = _kernels(gpu, lambda: gpu.solve(
+        Ad, int(form), m, gamma, mu=mu, X0=x_to_device(X0), tol=0.0, max_iter=iters))
+    assert (name, launches) == ("k_small", 1)
+    assert rel(r.X.cpu().numpy(), ref["X"]) <= 1e-5
+    assert rel(r.Z.cpu().numpy(), ref["Z"]) <= 1e-5
+    np.testing.assert_allclose(r.trace, ref["trace"], rtol=1e-5)
+    np.testing.assert_array_equal(r.Z.cpu().numpy() != 0, ref["Z"] != 0)
