@@ -242,8 +242,8 @@ __global__ __launch_bounds__(1024) void k_topm_final(int nl, int m, const double
 hipError_t launch_topm(const Plan& pl, const double* norms, double* cand_v, int64_t* cand_i,
                        int64_t* idx, hipStream_t st) {
     static const bool lds_once =
-        (hipFuncSetAttribute((const void*)k_topm_final, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             256 * kMaxM * (int)sizeof(double)),
+        ((void)hipFuncSetAttribute((const void*)k_topm_final, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   256 * kMaxM * (int)sizeof(double)),
          (void)hipGetLastError(), true);   // advisory: no sticky error is left behind
     (void)lds_once;
     if (pl.topm_grid > 256 || pl.m > kMaxM) return hipErrorInvalidValue;
